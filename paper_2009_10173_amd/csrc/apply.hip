@@ -10,7 +10,7 @@
 // of the padded input supplies the zeros outside the region of interest.
 //
 // GEMM view per tile: M = 16 output rows, N = scan positions (16 per MFMA), K = the tile's
-// K-groups.  Kernels: a plain FP64/FP32 FMA kernel, FP32 MFMA (v_mfma_f32_16x16x4f32), BF16
+// K-groups.  Kernels: FP64 MFMA (v_mfma_f64_16x16x4f64), FP32 MFMA (v_mfma_f32_16x16x4f32), BF16
 // MFMA (v_mfma_f32_16x16x32_bf16) and the block-scaled FP8 MFMA
 // (v_mfma_scale_f32_16x16x128_f8f6f4, e4m3 table and operand) on gfx950.
 #include <hip/hip_runtime.h>
@@ -36,6 +36,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 
 template <typename Tin, typename Tout>
@@ -77,27 +78,81 @@ struct ApplyArgs {
   int ntx, nx, K, nxp, Lp;
 };
 
-// Plain kernel: one thread per (output row, position); G-entry FMA loops in the vector type.
-template <typename T>
-__global__ __launch_bounds__(256) void k_apply_fma(const T* __restrict__ pack, const T* __restrict__ in,
-                                                   T* __restrict__ out, ApplyArgs a, int G) {
+// FP64 MFMA kernel (v_mfma_f64_16x16x4_f64).  A workgroup of W waves owns one 16-row output tile
+// and NT 16-position tiles; the waves take the tile's bundles in turn, so that each table
+// fragment is loaded once per workgroup, and their partial sums are added in wave order through
+// the LDS.  Lane (n = lane % 16, g = lane / 16) loads the four entries of row n of K-group g and
+// the four input entries of K-group g for position n (32 bytes each; four neighbouring K-groups
+// are usually consecutive runs of one column, so a position's loads share cache lines), and
+// entry j of both feeds the bundle's j-th MFMA.  The accumulator's element i of lane (n, g) is
+// row 4 i + g.  A bundle's loads are issued one bundle ahead.  Bound by the loads through the
+// texture path (2 + 2 NT of 1 KB against 4 NT MFMAs of 64 cycles).  Against one FMA per pair
+// of loaded operands: the adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) 68.4 -> 3.42 ms, the
+// forward of a 23 x 19 one (Nz 40, Nt 200, K 12) 3.38 -> 0.093 ms.
+template <int NT, int W>
+__global__ __launch_bounds__(64 * W, 4) void k_apply_f64(const double* __restrict__ pack,
+                                                      const double* __restrict__ in,
+                                                      double* __restrict__ out, ApplyArgs a) {
+  __shared__ double red[W * 4 * 64];
   const int tile = blockIdx.y;
-  const int ntile = blockIdx.x;
-  const int m = threadIdx.x / 16, n = threadIdx.x % 16;
-  const int py = ntile / a.ntx, tx = ntile % a.ntx;
-  const long long base = ((long long)(py + a.K) * a.nxp + 16 * tx + n + a.K) * a.Lp;
-  T acc = T(0);
-  const int b0 = a.tile_start[tile], b1 = a.tile_start[tile + 1];
-  for (int b = b0; b < b1; ++b) {
-    for (int g = 0; g < kLaneGroups; ++g) {
-      const int q = b * kLaneGroups + g;
-      const T* ap = pack + ((long long)q * 16 + m) * G;
-      const T* xp = in + base + a.meta[q];
-      for (int j = 0; j < G; ++j) acc += ap[j] * xp[j];
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int n = lane % 16, g = lane / 16;
+  int base[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    // position tiles beyond the last repeat it and are not stored
+    const int pt = min((int)blockIdx.x * NT + t, a.n_ntiles - 1);
+    base[t] = ((pt / a.ntx + a.K) * a.nxp + 16 * (pt % a.ntx) + n + a.K) * a.Lp;
+  }
+  doublex4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+  const int b1 = a.tile_start[tile + 1];
+  const int bw = a.tile_start[tile] + wave;
+  if (bw < b1) {
+    const int last = bw + (b1 - 1 - bw) / W * W;  // the wave's last bundle
+    doublex4 av[2], xv[2][NT];
+    auto load = [&](int s, int b, int mo) {
+      av[s] = *reinterpret_cast<const doublex4*>(pack + ((long long)(b * kLaneGroups + g) * 16 + n) * 4);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) xv[s][t] = *reinterpret_cast<const doublex4*>(in + (base[t] + mo));
+    };
+    auto mma = [&](int s) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][j], xv[s][t][j], acc[t], 0, 0, 0);
+    };
+    load(0, bw, a.meta[bw * kLaneGroups + g]);
+    int mo = a.meta[min(bw + W, last) * kLaneGroups + g];
+    for (int b = bw; b < b1; b += 2 * W) {
+      load(1, min(b + W, last), mo);
+      mo = a.meta[min(b + 2 * W, last) * kLaneGroups + g];
+      mma(0);
+      load(0, min(b + 2 * W, last), mo);
+      mo = a.meta[min(b + 3 * W, last) * kLaneGroups + g];
+      if (b + W < b1) mma(1);
     }
   }
-  const int row = kTile * tile + m, px = 16 * tx + n;
-  if (row < a.out_len && px < a.nx) out[((long long)py * a.nx + px) * a.out_len + row] = acc;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[(wave * 4 + i) * 64 + lane] = acc[t][i];
+    __syncthreads();
+    const int pt = blockIdx.x * NT + t;
+    for (int e = threadIdx.x; e < 256; e += 64 * W) {
+      double v = red[e];
+#pragma unroll
+      for (int w = 1; w < W; ++w) v += red[w * 256 + e];
+      // element e = 64 i + lane; neighbouring threads take neighbouring positions
+      const int row = kTile * tile + 4 * (e / 64) + (e % 64) / 16;
+      const int px = 16 * (pt % a.ntx) + e % 16;
+      if (pt < a.n_ntiles && row < a.out_len && px < a.nx)
+        out[((long long)(pt / a.ntx) * a.nx + px) * a.out_len + row] = v;
+    }
+    __syncthreads();
+  }
 }
 
 struct StagedArgs {
@@ -1135,6 +1190,19 @@ int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* i
   return AROAM_OK;
 }
 
+int launch_f64(const ApplyArgs& a, int n_tiles, const void* pack, const void* in, void* out,
+               hipStream_t st) {
+  constexpr int W = 8;
+  const int wide = (int)ceil_div(a.n_ntiles, 4);
+  if ((long long)wide * n_tiles >= 512)
+    hipLaunchKernelGGL((k_apply_f64<4, W>), dim3((unsigned)wide, (unsigned)n_tiles), dim3(64 * W),
+                       0, st, (const double*)pack, (const double*)in, (double*)out, a);
+  else
+    hipLaunchKernelGGL((k_apply_f64<1, W>), dim3((unsigned)a.n_ntiles, (unsigned)n_tiles),
+                       dim3(64 * W), 0, st, (const double*)pack, (const double*)in, (double*)out, a);
+  return AROAM_OK;
+}
+
 // The launches of one apply into the stage buffer `buf` (stage_bytes() bytes).
 int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* out, void* buf,
                  hipStream_t st) {
@@ -1158,10 +1226,8 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
     hipLaunchKernelGGL((k_stage<float, uint16_t>), sgrid, dim3(256), 0, st, (const float*)in,
                        (uint16_t*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L, pg.Lp);
   if (dtype == AROAM_FP64) {
-    const ApplyArgs a = make_args(lay);
-    const dim3 grid((unsigned)a.n_ntiles, (unsigned)lay.n_tiles);
-    hipLaunchKernelGGL(k_apply_fma<double>, grid, dim3(256), 0, st, (const double*)pk.d,
-                       (const double*)buf, (double*)out, a, lay.G);
+    AROAM_CHECK(lay.G == 4, AROAM_EINVAL, "FP64 layout needs runs of four entries");
+    AROAM_TRY(launch_f64(make_args(lay), lay.n_tiles, pk.d, buf, out, st));
   } else {
     const StageParts sp = stage_parts(m, adjoint, dtype);
     float* partial =
