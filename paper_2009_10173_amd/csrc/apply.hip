@@ -10,8 +10,8 @@
 // of the padded input supplies the zeros outside the region of interest.
 //
 // GEMM view per tile: M = 16 output rows, N = scan positions (16 per MFMA), K = the tile's
-// K-groups.  Kernels: FP64 MFMA (v_mfma_f64_16x16x4f64), FP32 MFMA (v_mfma_f32_16x16x4f32), BF16
-// MFMA (v_mfma_f32_16x16x32_bf16) and the block-scaled FP8 MFMA
+// K-groups.  Kernels: FP64 MFMA (v_mfma_f64_16x16x4f64), FP32 as products of three-part BF16
+// splits on the BF16 MFMA, BF16 MFMA (v_mfma_f32_16x16x32_bf16) and the block-scaled FP8 MFMA
 // (v_mfma_scale_f32_16x16x128_f8f6f4, e4m3 table and operand) on gfx950.
 #include <hip/hip_runtime.h>
 
@@ -19,6 +19,7 @@
 #include <atomic>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -42,10 +43,6 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 template <typename Tin, typename Tout>
 __device__ inline Tout conv(Tin v);
 template <>
-__device__ inline double conv<double, double>(double v) { return v; }
-template <>
-__device__ inline float conv<float, float>(float v) { return v; }
-template <>
 __device__ inline uint16_t conv<float, uint16_t>(float f) {  // bf16, round to nearest even
   uint32_t u = __float_as_uint(f);
   if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffff) ? 0x40 : 0));
@@ -67,91 +64,6 @@ __global__ __launch_bounds__(256) void k_stage(const Tin* __restrict__ in, Tout*
     Tout v = Tout(0);
     if (inside && l < L) v = conv<Tin, Tout>(src[l]);
     o[l] = v;
-  }
-}
-
-struct ApplyArgs {
-  const int* tile_start;
-  const int* meta;
-  int out_len;
-  int n_ntiles;  // 16-position tiles over the whole scan grid
-  int ntx, nx, K, nxp, Lp;
-};
-
-// FP64 MFMA kernel (v_mfma_f64_16x16x4_f64).  A workgroup of W waves owns one 16-row output tile
-// and NT 16-position tiles; the waves take the tile's bundles in turn, so that each table
-// fragment is loaded once per workgroup, and their partial sums are added in wave order through
-// the LDS.  Lane (n = lane % 16, g = lane / 16) loads the four entries of row n of K-group g and
-// the four input entries of K-group g for position n (32 bytes each; four neighbouring K-groups
-// are usually consecutive runs of one column, so a position's loads share cache lines), and
-// entry j of both feeds the bundle's j-th MFMA.  The accumulator's element i of lane (n, g) is
-// row 4 i + g.  A bundle's loads are issued one bundle ahead.  Bound by the loads through the
-// texture path (2 + 2 NT of 1 KB against 4 NT MFMAs of 64 cycles).  Against one FMA per pair
-// of loaded operands: the adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) 68.4 -> 3.42 ms, the
-// forward of a 23 x 19 one (Nz 40, Nt 200, K 12) 3.38 -> 0.093 ms.
-template <int NT, int W>
-__global__ __launch_bounds__(64 * W, 4) void k_apply_f64(const double* __restrict__ pack,
-                                                      const double* __restrict__ in,
-                                                      double* __restrict__ out, ApplyArgs a) {
-  __shared__ double red[W * 4 * 64];
-  const int tile = blockIdx.y;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int n = lane % 16, g = lane / 16;
-  int base[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    // position tiles beyond the last repeat it and are not stored
-    const int pt = min((int)blockIdx.x * NT + t, a.n_ntiles - 1);
-    base[t] = ((pt / a.ntx + a.K) * a.nxp + 16 * (pt % a.ntx) + n + a.K) * a.Lp;
-  }
-  doublex4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const int b1 = a.tile_start[tile + 1];
-  const int bw = a.tile_start[tile] + wave;
-  if (bw < b1) {
-    const int last = bw + (b1 - 1 - bw) / W * W;  // the wave's last bundle
-    doublex4 av[2], xv[2][NT];
-    auto load = [&](int s, int b, int mo) {
-      av[s] = *reinterpret_cast<const doublex4*>(pack + ((long long)(b * kLaneGroups + g) * 16 + n) * 4);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) xv[s][t] = *reinterpret_cast<const doublex4*>(in + (base[t] + mo));
-    };
-    auto mma = [&](int s) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][j], xv[s][t][j], acc[t], 0, 0, 0);
-    };
-    load(0, bw, a.meta[bw * kLaneGroups + g]);
-    int mo = a.meta[min(bw + W, last) * kLaneGroups + g];
-    for (int b = bw; b < b1; b += 2 * W) {
-      load(1, min(b + W, last), mo);
-      mo = a.meta[min(b + 2 * W, last) * kLaneGroups + g];
-      mma(0);
-      load(0, min(b + 2 * W, last), mo);
-      mo = a.meta[min(b + 3 * W, last) * kLaneGroups + g];
-      if (b + W < b1) mma(1);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) red[(wave * 4 + i) * 64 + lane] = acc[t][i];
-    __syncthreads();
-    const int pt = blockIdx.x * NT + t;
-    for (int e = threadIdx.x; e < 256; e += 64 * W) {
-      double v = red[e];
-#pragma unroll
-      for (int w = 1; w < W; ++w) v += red[w * 256 + e];
-      // element e = 64 i + lane; neighbouring threads take neighbouring positions
-      const int row = kTile * tile + 4 * (e / 64) + (e % 64) / 16;
-      const int px = 16 * (pt % a.ntx) + e % 16;
-      if (pt < a.n_ntiles && row < a.out_len && px < a.nx)
-        out[((long long)(pt / a.ntx) * a.nx + px) * a.out_len + row] = v;
-    }
-    __syncthreads();
   }
 }
 
@@ -264,20 +176,9 @@ __device__ __forceinline__ void stage_rows(const StagedArgs& a, const T* __restr
   }
 }
 
-// Position fragments of one bundle for the NT tiles of this lane: 16 bytes each from LDS.
-// Tiles t with t % TPR >= NTC (16-position tiles beyond the last scan column, in a patch at
-// the grid's edge) are left out.
-template <typename T, int NT, int TPR = 1, int NTC = TPR>
-__device__ __forceinline__ void read_x(const T* lds, const int (&lbase)[NT], int mo,
-                                       u32x4 (&x)[NT]) {
-  mo &= (1 << kMetaMaskShift) - 1;  // the top bits hold the bundle's mask
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-    if (t % TPR < NTC) x[t] = *reinterpret_cast<const u32x4*>(lds + lbase[t] + mo);
-}
-
-// read_x for a lane whose tile t sits at row base rb[t / TPR] plus column offset
-// (t % TPR) * 16 * CSC (compile-time column stride CSC, so the offsets are immediates).
+// Position fragments of one bundle for the NT tiles of this lane, 16 bytes each from the LDS: tile
+// t sits at row base rb[t / TPR] plus column offset (t % TPR) * 16 * CSC (compile-time column
+// stride CSC, so the offsets are immediates).
 template <typename T, int NT, int TPR, int CSC, int NR>
 __device__ __forceinline__ void read_x_rows(const T* lds, const int (&rb)[NR], int mo,
                                             u32x4 (&x)[NT]) {
@@ -287,188 +188,21 @@ __device__ __forceinline__ void read_x_rows(const T* lds, const int (&rb)[NR], i
     x[t] = *reinterpret_cast<const u32x4*>(lds + rb[t / TPR] + mo + (t % TPR) * 16 * CSC);
 }
 
-// MFMAs of one bundle whose position fragments are already in registers (tiles as read_x).
-template <typename T, int MH, int NT, int TPR = 1, int NTC = TPR>
+// MFMAs of one bundle whose position fragments are already in registers.
+template <typename T, int MH, int NT>
 __device__ __forceinline__ void bundle_mma(const AFrag<T, MH>& f, const u32x4 (&xraw)[NT],
                                            floatx4 (&acc)[MH][NT]) {
-  // the bundle's mask: for FP32 the entries of its runs (one MFMA each) that a K-group's band
-  // reaches, for BF16 the 16-row halves; uniform over the wave
+  // the bundle's mask: the 16-row halves that a K-group's band reaches; uniform over the wave
   const unsigned bm = (unsigned)__builtin_amdgcn_readfirstlane(f.mo) >> kMetaMaskShift;
-  if constexpr (sizeof(T) == 4) {
-    static_assert(MH == 1, "FP32 tiles have one 16-row half");
-    const floatx4 av = __builtin_bit_cast(floatx4, f.v[0]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (!((bm >> j) & 1)) continue;
+  for (int h = 0; h < MH; ++h) {
+    if (MH > 1 && !((bm >> h) & 1)) continue;  // the bundle's bands miss this half
+    const bf16x8 av = __builtin_bit_cast(bf16x8, f.v[h]);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (t % TPR >= NTC) continue;
-        const floatx4 xv = __builtin_bit_cast(floatx4, xraw[t]);
-        acc[0][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], xv[j], acc[0][t], 0, 0, 0);
-      }
+    for (int t = 0; t < NT; ++t) {
+      const bf16x8 xv = __builtin_bit_cast(bf16x8, xraw[t]);
+      acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, xv, acc[h][t], 0, 0, 0);
     }
-  } else {
-#pragma unroll
-    for (int h = 0; h < MH; ++h) {
-      if (MH > 1 && !((bm >> h) & 1)) continue;  // the bundle's bands miss this half
-      const bf16x8 av = __builtin_bit_cast(bf16x8, f.v[h]);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (t % TPR >= NTC) continue;
-        const bf16x8 xv = __builtin_bit_cast(bf16x8, xraw[t]);
-        acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, xv, acc[h][t], 0, 0, 0);
-      }
-    }
-  }
-}
-
-// FP32 bundles [U.z, U.w) of one stage unit for the tiles of the NTC live tile columns: the
-// next bundle's position fragments are read while this bundle's 16 MFMAs run (two register
-// sets), and ring slot (j + 1) mod PD holds the next bundle (or a clamped copy of the last).
-template <int MH, int NT, int TPR, int NTC, int PD>
-__device__ __forceinline__ void fp32_unit_bundles(const float* lds, const int (&lbase)[NT],
-                                                  AFrag<float, MH> (&ring)[PD],
-                                                  floatx4 (&acc)[MH][NT],
-                                                  const void* __restrict__ pack_raw,
-                                                  const StagedArgs& a, int4 U, int g, int n) {
-  u32x4 xa[NT], xb[NT];
-  read_x<float, NT, TPR, NTC>(lds, lbase, ring[0].mo, xa);
-  for (int b0 = U.z; b0 < U.w; b0 += PD) {
-#pragma unroll
-    for (int j = 0; j < PD; ++j) {
-      read_x<float, NT, TPR, NTC>(lds, lbase, ring[(j + 1) % PD].mo, (j % 2) ? xa : xb);
-      if (b0 + j < U.w) bundle_mma<float, MH, NT, TPR, NTC>(ring[j], (j % 2) ? xb : xa, acc);
-      // refill unconditionally (clamped to the unit's last bundle) so that the number of
-      // loads in flight is fixed and the waits can count them
-      load_a<float, MH>(pack_raw, a.meta, min(b0 + j + PD, U.w - 1), g, n, ring[j]);
-    }
-  }
-}
-
-// LDS-staged FP32 MFMA kernel.  A workgroup (4 waves) owns one output tile (16 MH rows) and
-// one patch of BR scan rows x BC scan columns; each wave owns BR/4 rows x BC columns = NT
-// 16-position tiles.  The tile's bundles are grouped into stage units (chunk, input row
-// offset).  The LDS holds the BR input rows a unit reads (all BC + 2K columns, the chunk's CH
-// inner entries) plus one free row, as a ring of BR + 1 slots indexed by padded row: a unit
-// loads only the rows it adds to the ring, and those rows are fetched into registers while
-// the previous unit computes.  Table fragments stream through a PD-deep register ring, whose
-// refill for the next unit is issued before that unit's rows are staged.  Lane (n = lane % 16,
-// g = lane / 16) holds row n of K-group g of the table and the entries of K-group g for
-// position n.
-// Two waves per SIMD (the LDS holds two workgroups of the 81 x 81 footprint): with that
-// target the compiler keeps the accumulators in VGPRs and the next bundle's reads ahead of the
-// MFMAs.
-template <typename T, int BR, int BC, int MH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_staged(const void* __restrict__ pack_raw,
-                                                      const T* __restrict__ in,
-                                                      float* __restrict__ out, StagedArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  T* lds = reinterpret_cast<T*>(lds_raw);
-  static_assert(sizeof(T) == 4, "the staged kernel is the FP32 path");
-  constexpr int VEC = 16 / sizeof(T);  // entries per 16-byte vector == K-group width G
-  constexpr int TPR = BC / 16;
-  constexpr int RW = BR / 4;
-  constexpr int NT = RW * TPR;
-  constexpr int PF = 4;                // prefetched stage vectors per thread (>= one row)
-  constexpr int PD = 4;                // table-fragment ring depth (even)
-  constexpr int CH = 4 * VEC;          // chunk = one bundle's four K-groups... per lane group
-  const int4 piece = a.pieces[blockIdx.y];
-  const int tile = piece.x;
-  const int py0 = (blockIdx.x / a.ncc) * BR, px0 = (blockIdx.x % a.ncc) * BC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int n = lane % 16, g = lane / 16;
-  constexpr int nvec = CH / VEC;       // 16-byte vectors per staged column
-  const int rowvec = a.NCOL * nvec;    // 16-byte vectors per staged row
-  floatx4 acc[MH][NT];
-#pragma unroll
-  for (int h = 0; h < MH; ++h)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[h][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int u0 = piece.y, u1 = piece.z;
-  if (u0 < u1) {
-    // the ring has one slot more than the BR rows a unit reads: when the next unit adds the
-    // single row after the current unit's rows (consecutive row offsets in one chunk), that
-    // row goes to the free slot while other waves still read the current unit, and one
-    // barrier per unit suffices
-    constexpr int RS = BR + 1;
-    u32x4 pf[PF];
-    int pf_off[PF];
-    // table fragments stream through a ring of PD slots per stage unit, unrolled so that
-    // every slot stays in fixed registers (shifting a ring would move registers that loads
-    // in flight still target, which forces full waits)
-    AFrag<T, MH> ring[PD];
-    {
-      const int4 U = a.units[u0];
-#pragma unroll
-      for (int j = 0; j < PD; ++j)
-        load_a<T, MH>(pack_raw, a.meta, min(U.z + j, U.w - 1), g, n, ring[j]);
-      stage_prefetch<T, RS, PF>(a, in, u0, py0, px0, rowvec, nvec, pf, pf_off);
-      stage_rows<T, RS, PF>(a, in, lds, u0, py0, px0, rowvec, nvec, pf, pf_off);
-      __syncthreads();
-      if (u0 + 1 < u1) stage_prefetch<T, RS, PF>(a, in, u0 + 1, py0, px0, rowvec, nvec, pf, pf_off);
-    }
-    for (int u = u0; u < u1; ++u) {
-      const int4 U = a.units[u];
-      // LDS base of this lane's positions for the unit's row offset
-      const int R = U.x + a.K;
-      int lbase[NT];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int r = wave * RW + t / TPR, c = (t % TPR) * 16 + n;
-        lbase[t] = (((r + R) % RS) * a.NCOL + c) * a.CS;
-      }
-      // a wave whose rows read only the zero rows around the scan grid at this unit's row
-      // offset skips the unit's MFMAs (it still stages its share of the unit's rows)
-      const int src_row = py0 + wave * RW + U.x;
-      const bool live = src_row + RW > 0 && src_row < a.ny;
-      if (!live) {
-      } else if constexpr (TPR == 2) {
-        // a patch at the grid's last columns computes only its tiles that hold scan columns
-        if (px0 + 16 >= a.nx)
-          fp32_unit_bundles<MH, NT, TPR, 1, PD>(lds, lbase, ring, acc, pack_raw, a, U, g, n);
-        else
-          fp32_unit_bundles<MH, NT, TPR, TPR, PD>(lds, lbase, ring, acc, pack_raw, a, U, g, n);
-      } else {
-        fp32_unit_bundles<MH, NT, TPR, TPR, PD>(lds, lbase, ring, acc, pack_raw, a, U, g, n);
-      }
-      if (u + 1 < u1) {
-        const int4 Un = a.units[u + 1];
-        const int2 Rn = a.urows[u + 1];
-        // the next unit's first table fragments; their loads overlap the staging below
-#pragma unroll
-        for (int j = 0; j < PD; ++j)
-          load_a<T, MH>(pack_raw, a.meta, min(Un.z + j, Un.w - 1), g, n, ring[j]);
-        // one new row right after this unit's rows: its slot is the free one
-        const bool free_slot = Rn.y - Rn.x == 1 && Rn.x == R + BR;
-        if (!free_slot) __syncthreads();  // every wave is done reading the rows replaced
-        stage_rows<T, RS, PF>(a, in, lds, u + 1, py0, px0, rowvec, nvec, pf, pf_off);
-        __syncthreads();  // the next unit's rows are in LDS; every wave is done with this unit
-        if (u + 2 < u1) stage_prefetch<T, RS, PF>(a, in, u + 2, py0, px0, rowvec, nvec, pf, pf_off);
-      }
-    }
-  }
-  // the output, or for a piece of a cut tile its partial slot (the patch's positions in order,
-  // TM rows each), which k_add_slots adds up
-  constexpr int PS = BR * BC * 16 * MH;  // floats per slot and patch
-  float* slot =
-      piece.w >= 0 ? a.partial + ((long long)piece.w * a.n_patches + blockIdx.x) * PS : nullptr;
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int py = py0 + wave * RW + t / TPR, px = px0 + (t % TPR) * 16 + n;
-    if (py >= a.ny || px >= a.nx) continue;
-    const int local = (wave * RW + t / TPR) * BC + (t % TPR) * 16 + n;
-    // element offset of output row `row` of this position: in the slot the rows of the tile
-    // start at 0, in the output at 0 of the position's column
-    float* dst = slot ? slot : out;
-    const long long off = slot ? (long long)local * (16 * MH) - 16 * MH * tile
-                               : ((long long)py * a.nx + px) * a.out_len;
-#pragma unroll
-    for (int h = 0; h < MH; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 16 * MH * tile + 16 * h + 4 * g + i;
-        if (row < a.out_len) dst[off + row] = acc[h][t][i];
-      }
   }
 }
 
@@ -607,42 +341,390 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // LDS bytes of the split kernel's final sums: S tiles of MH halves per wave, four waves.
 constexpr size_t red_bytes(int S, int MH) { return (size_t)4 * S * MH * 64 * 16; }
 
+// ------------------------------------------------------------------------------------------
+// LDS-ring applies (FP32 and FP64).
+//
+// A workgroup (W waves) owns one 16-row output tile and a patch of BR x BC scan positions.  The
+// tile's bundles are grouped into stage units (chunk of the inner axis, input row offset) in
+// the order chunk, row.  The LDS holds the BR input rows a unit reads (the patch's columns and
+// K more on each side, the chunk's entries) plus one free row, as a ring indexed by padded row
+// modulo BR + 1: a unit loads only the rows it adds, usually one, into registers while the unit
+// before it computes.  The rows come straight from the caller's vector; positions outside the
+// scan and entries past the end of the axis are written as zeros.  The waves form P row groups
+// of BR / P patch rows, and the S = W / P waves of a group take the bundles of each unit in
+// turn, so that a table fragment is loaded once per row group; at the end the S partial sums of
+// a position are added in wave order through the LDS.
+//
+// The element type's part is an operation class: how a staged vector is written to the LDS,
+// what a lane holds of a table bundle and of a position, and the MFMAs that combine them.
+// Lane (n = lane % 16, g = lane / 16) holds row n of K-group g of the table and K-group g's
+// entries of position n.
+
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// FP32 on the BF16 MFMA: every FP32 value is the exact sum of three BF16 values (8 bits each,
+// rounded to nearest in turn), and a product is the six products of parts whose exponents
+// add up to no less than 2^-16 of the leading one; the three left out are below 2^-24 of it.
+// The sums run in FP32.  Six BF16 MFMAs of K = 32 take 96 cycles where the eight FP32 MFMAs of
+// K = 4 take 256, and round the sum less often: the 400 x 400 forward took 181 ms on
+// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 116 ms at 1.7e-6 (200 x 200
+// adjoint: 8.05 ms, 2.3e-6 and 4.88 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
+// the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
+struct OpF32 {
+  using In = float;
+  using Vec = floatx4;             // 16 staged bytes
+  using VecU = floatx4u;           // the same with the alignment of one entry
+  using Acc = floatx4;
+  static constexpr int kVec = 4;   // entries of a staged vector
+  static constexpr int kCol = kRingF32.col_bytes;
+  static constexpr int kVecs = kRingF32.CH / kVec;  // staged vectors per column
+  static constexpr int kTiles = 4;                  // position tiles per phase
+  static constexpr int kPlane = 2 * kRingF32.CH;    // LDS bytes of one part of a column
+  struct A {
+    u32x4 v[3];
+  };
+  struct X {
+    u32x4 v[3];
+  };
+  static __device__ __forceinline__ void load_a(const void* __restrict__ pack, int b, int lane,
+                                                A& f) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(pack) + (long long)b * 192 + lane;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) f.v[i] = p[64 * i];
+  }
+  static __device__ __forceinline__ X read_x(const unsigned char* p) {
+    X x;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) x.v[i] = *reinterpret_cast<const u32x4*>(p + i * kPlane);
+    return x;
+  }
+  static __device__ __forceinline__ void write(unsigned char* col, int v, Vec f) {
+    u32x2 part[3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      floatx2 r = {f[2 * h], f[2 * h + 1]};
+      // the largest finite BF16, so that rounding a finite value never gives an infinity
+      constexpr float kMax = 3.3895313892515355e38f;
+      floatx2 c = {__builtin_amdgcn_fmed3f(r[0], -kMax, kMax),
+                   __builtin_amdgcn_fmed3f(r[1], -kMax, kMax)};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(i ? r : c, bf16x2));
+        part[i][h] = w;
+        r[0] -= __uint_as_float(w << 16);
+        r[1] -= __uint_as_float(w & 0xffff0000u);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      *reinterpret_cast<u32x2*>(col + 8 * v + i * kPlane) = part[i];
+  }
+  // the MFMAs of a bundle for NX tiles whose accumulators lie STEP apart
+  template <int NX, int STEP>
+  static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, px[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int t = 0; t < NX; ++t)
+        acc[t * STEP] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, a.v[pa[i]]), __builtin_bit_cast(bf16x8, x[t].v[px[i]]),
+            acc[t * STEP], 0, 0, 0);
+  }
+  // output row (within the tile) of accumulator element i of lane group g
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+};
+
+// FP64 on v_mfma_f64_16x16x4_f64: entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
+// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.69 ms; with positions read from
+// global memory it took 3.42 ms (bound by the texture path), with one FMA per load 68.4 ms.
+struct OpF64 {
+  using In = double;
+  using Vec = doublex2;
+  using VecU = doublex2u;
+  using Acc = doublex4;
+  static constexpr int kVec = 2;
+  static constexpr int kCol = kRingF64.col_bytes;
+  static constexpr int kVecs = kRingF64.CH / kVec;
+  static constexpr int kTiles = 4;
+  struct A {
+    doublex4 v;
+  };
+  struct X {
+    doublex2 v[2];
+  };
+  static __device__ __forceinline__ void load_a(const void* __restrict__ pack, int b, int lane,
+                                                A& f) {
+    f.v = reinterpret_cast<const doublex4*>(pack)[(long long)b * 64 + lane];
+  }
+  static __device__ __forceinline__ X read_x(const unsigned char* p) {
+    X x;
+    x.v[0] = *reinterpret_cast<const doublex2*>(p);
+    x.v[1] = *reinterpret_cast<const doublex2*>(p + 16);
+    return x;
+  }
+  static __device__ __forceinline__ void write(unsigned char* col, int v, Vec f) {
+    *reinterpret_cast<doublex2*>(col + 16 * v) = f;
+  }
+  template <int NX, int STEP>
+  static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int t = 0; t < NX; ++t)
+        acc[t * STEP] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[j], x[t].v[j / 2][j % 2],
+                                                             acc[t * STEP], 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
+};
+
+struct RingArgs {
+  const int4* pieces;  // (tile, unit begin, unit end, partial slot or -1)
+  const int4* units;   // (row offset, chunk start, bundle begin, bundle end)
+  const int* meta;     // per K-group: LDS byte offset of its run from the position's column
+  void* partial;       // [slot][patch][position][16 rows] partial sums of cut tiles
+  int n_patches;
+  int out_len, nx, ny, K, L;
+  int ncc;             // patch columns
+  int NCOL;            // staged columns
+};
+
+// Staged vectors in flight: the 16-byte pieces of the rows a unit adds.  off < 0: none.
+template <class Op, int PF>
+struct RingFetch {
+  typename Op::Vec v[PF];
+  int off[PF];
+  unsigned zero;  // bit i: vector i lies outside the scan or past the end of the axis
+};
+
+// Address of staged vector idx of the rows from padded patch row `lo`, for the chunk at e0; the
+// loads are unconditional (an invalid one reads the vector's first entries), so that the waits
+// of the table fragments in flight can count them.
+template <class Op, int RS, bool RAGGED>
+__device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
+                                                      const typename Op::In* __restrict__ in,
+                                                      int lo, int e0, int idx, int nv, int py0,
+                                                      int px0, int rowvec, int& off, bool& zero) {
+  const int G = lo + idx / rowvec, rem = idx % rowvec;
+  const int c = rem / Op::kVecs, v = rem % Op::kVecs;
+  const int py = py0 + G - a.K, px = px0 + c - a.K, l = e0 + v * Op::kVec;
+  const bool ok = idx < nv && py >= 0 && py < a.ny && px >= 0 && px < a.nx && l < a.L;
+  off = idx < nv ? ((G % RS) * a.NCOL + c) * Op::kCol + (v << 8 * 3) : -1;
+  zero = !ok;
+  const typename Op::In* p = in + (ok ? ((long long)py * a.nx + px) * a.L + l : 0);
+  typename Op::Vec r;
+  if constexpr (RAGGED) {
+#pragma unroll
+    for (int i = 0; i < Op::kVec; ++i) {
+      const bool in_axis = ok && l + i < a.L;
+      const typename Op::In e = p[in_axis ? i : 0];
+      r[i] = in_axis ? e : typename Op::In(0);
+    }
+  } else {
+    r = *reinterpret_cast<const typename Op::VecU*>(p);
+  }
+  return r;
+}
+
+template <class Op, int BR, int BC, int W, int P, bool RAGGED>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void k_apply_ring(
+    const void* __restrict__ pack, const typename Op::In* __restrict__ in,
+    typename Op::In* __restrict__ out, RingArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  using Acc = typename Op::Acc;
+  constexpr int S = W / P;        // waves that share a row group's bundles
+  constexpr int RW = BR / P;      // patch rows per group
+  constexpr int TPR = BC / 16;
+  constexpr int NT = RW * TPR;    // position tiles per wave
+  constexpr int XT = Op::kTiles;  // tiles per phase
+  constexpr int PH = NT / XT;
+  constexpr int RPP = XT / TPR;   // patch rows per phase
+  constexpr int RS = BR + 1;
+  constexpr int PF = 2, PD = 2;   // staged vectors, bundles in flight
+  constexpr int TH = 64 * W;
+  static_assert(W % P == 0 && BR % P == 0 && NT % XT == 0 && XT % TPR == 0 && NT % S == 0, "shape");
+  const int4 piece = a.pieces[blockIdx.y];
+  const int tile = piece.x;
+  const int py0 = (blockIdx.x / a.ncc) * BR, px0 = (blockIdx.x % a.ncc) * BC;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int grp = wave / S, sw = wave % S;
+  const int n = lane % 16, g = lane / 16;
+  const int rowvec = a.NCOL * Op::kVecs;
+  Acc acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = Acc{0, 0, 0, 0};
+
+  RingFetch<Op, PF> f;
+  // the rows unit U adds: padded patch rows [lo, U.x + K + BR) of its chunk
+  auto fetch = [&](const int4& U, int lo) {
+    const int nv = (U.x + a.K + BR - lo) * rowvec;
+    f.zero = 0;
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      bool z;
+      f.v[i] = ring_load<Op, RS, RAGGED>(a, in, lo, U.y, threadIdx.x + TH * i, nv, py0, px0, rowvec,
+                                         f.off[i], z);
+      f.zero |= z ? 1u << i : 0u;
+    }
+  };
+  auto put = [&](typename Op::Vec v, int off, bool zero) {
+    if (off >= 0) {
+      const typename Op::Vec z = {};
+      Op::write(lds + (off & 0xffffff), off >> 24, zero ? z : v);
+    }
+  };
+  auto stage = [&](const int4& U, int lo) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) put(f.v[i], f.off[i], (f.zero >> i) & 1);
+    const int nv = (U.x + a.K + BR - lo) * rowvec;
+    for (int base = TH * PF; base < nv; base += TH * 4) {
+      typename Op::Vec v[4];
+      int off[4];
+      bool z[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        v[i] = ring_load<Op, RS, RAGGED>(a, in, lo, U.y, base + threadIdx.x + TH * i, nv, py0, px0,
+                                         rowvec, off[i], z[i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put(v[i], off[i], z[i]);
+    }
+  };
+
+  const int u0 = piece.y, u1 = piece.z;
+  if (u0 < u1) {
+    typename Op::A ring[PD];
+    int mo[PD];
+    auto refill = [&](int j, int b) {
+      Op::load_a(pack, b, lane, ring[j]);
+      mo[j] = a.meta[b * kLaneGroups + g];
+    };
+    // the bundles of unit U for this wave, the tiles of the first NTC tile columns
+    auto bundles = [&](const int4& U, const int (&rb)[RW], unsigned live, auto ntc) {
+      constexpr int NTC = decltype(ntc)::value;
+      constexpr int NX = RPP * NTC;
+      for (int b0 = U.z + sw; b0 < U.w; b0 += S * PD) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j) {
+          const int b = b0 + S * j;
+          if (b < U.w) {
+#pragma unroll
+            for (int p = 0; p < PH; ++p) {
+              if (!((live >> p) & 1)) continue;
+              typename Op::X x[NX];
+#pragma unroll
+              for (int t = 0; t < NX; ++t)
+                x[t] = Op::read_x(lds + (rb[p * RPP + t / NTC] + mo[j]) + (t % NTC) * 16 * Op::kCol);
+              Op::template mma<NX, TPR / NTC>(ring[j], x, acc + p * XT);
+            }
+          }
+          refill(j, min(b + S * PD, U.w - 1));
+        }
+      }
+    };
+    int4 U = a.units[u0];
+#pragma unroll
+    for (int j = 0; j < PD; ++j) refill(j, min(U.z + sw + S * j, U.w - 1));
+    fetch(U, U.x + a.K);
+    stage(U, U.x + a.K);
+    __syncthreads();
+    int4 Un = a.units[min(u0 + 1, u1 - 1)];
+    // rows the next unit finds in the ring: those of this unit, in the same chunk
+    int lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
+    if (u0 + 1 < u1) fetch(Un, lo);
+    for (int u = u0; u < u1; ++u) {
+      // LDS base of this lane's position in each of the wave's rows, and the phases that have
+      // both an output row and an input row inside the scan
+      int rb[RW];
+#pragma unroll
+      for (int r = 0; r < RW; ++r)
+        rb[r] = (((grp * RW + r + U.x + a.K) % RS) * a.NCOL + n) * Op::kCol;
+      unsigned live = 0;
+#pragma unroll
+      for (int p = 0; p < PH; ++p) {
+        const int o = py0 + grp * RW + p * RPP, i = o + U.x;
+        live |= o < a.ny && i + RPP > 0 && i < a.ny ? 1u << p : 0u;
+      }
+      if (live) {
+        if (px0 + 16 >= a.nx)  // the patch's second tile column lies outside the scan
+          bundles(U, rb, live, std::integral_constant<int, 1>{});
+        else
+          bundles(U, rb, live, std::integral_constant<int, TPR>{});
+      }
+      if (u + 1 < u1) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j) refill(j, min(Un.z + sw + S * j, Un.w - 1));
+        // one new row right after this unit's rows goes to the free slot while other waves
+        // still read this unit
+        if (!(Un.x == U.x + 1 && Un.y == U.y)) __syncthreads();
+        stage(Un, lo);
+        __syncthreads();
+        U = Un;
+        Un = a.units[min(u + 2, u1 - 1)];
+        lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
+        if (u + 2 < u1) fetch(Un, lo);
+      }
+    }
+  }
+  // the output, or for a piece of a cut tile its partial slot: the sums over the S waves of a
+  // group in wave order, S tiles per phase
+  using In = typename Op::In;
+  In* slot = piece.w >= 0 ? reinterpret_cast<In*>(a.partial) +
+                                ((long long)piece.w * a.n_patches + blockIdx.x) * (BR * BC * 16)
+                          : nullptr;
+  Acc* red = reinterpret_cast<Acc*>(lds);
+#pragma unroll
+  for (int p = 0; p < NT; p += S) {
+    Acc v = acc[p];
+    if constexpr (S > 1) {
+      __syncthreads();  // the ring, or the phase before
+#pragma unroll
+      for (int k = 0; k < S; ++k) red[(wave * S + k) * 64 + lane] = acc[p + k];
+      __syncthreads();
+      v = red[(grp * S * S + sw) * 64 + lane];
+#pragma unroll
+      for (int s = 1; s < S; ++s) v += red[((grp * S + s) * S + sw) * 64 + lane];
+    }
+    const int t = p + sw;
+    const int r = grp * RW + t / TPR, c = (t % TPR) * 16 + n;
+    const int py = py0 + r, px = px0 + c;
+    if (py < a.ny && px < a.nx) {
+      In* dst = slot ? slot + (r * BC + c) * 16
+                     : out + ((long long)py * a.nx + px) * a.out_len + kTile * tile;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (kTile * tile + Op::row(i, g) < a.out_len) dst[Op::row(i, g)] = v[i];
+    }
+  }
+}
+
 // Output of the cut tiles: the sum of a tile's partial slots in slot order (the order of the
-// tile's stage units), written like the staged kernel's own output.  Grid: (patch, tile);
-// workgroups of tiles that were not cut return at once.
-template <int BR, int BC, int MH>
+// tile's stage units).  Grid: (patch, tile); workgroups of tiles that were not cut return at
+// once.  A thread adds four consecutive rows of a position.
+template <typename T, int BR, int BC, int TM>
 __global__ __launch_bounds__(256) void k_add_slots(const int2* __restrict__ tile_split,
-                                                   const float* __restrict__ partial,
-                                                   float* __restrict__ out, int n_patches,
-                                                   int ncc, int nx, int ny, int out_len) {
-  constexpr int TPR = BC / 16, RW = BR / 4, NT = RW * TPR, TM = 16 * MH;
-  constexpr long long PS = (long long)BR * BC * TM;  // floats per slot and patch
+                                                   const T* __restrict__ partial,
+                                                   T* __restrict__ out, int n_patches, int ncc,
+                                                   int nx, int ny, int out_len) {
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  constexpr int PS4 = BR * BC * TM / 4;  // quads per slot and patch
   const int tile = blockIdx.y;
   const int2 sp = tile_split[tile];
   if (sp.x < 2) return;
   const int py0 = (blockIdx.x / ncc) * BR, px0 = (blockIdx.x % ncc) * BC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int n = lane % 16, g = lane / 16;
-  const float* base = partial + ((long long)sp.y * n_patches + blockIdx.x) * PS;
-  const long long stride = (long long)n_patches * PS;
+  const T4* base = reinterpret_cast<const T4*>(partial) + ((long long)sp.y * n_patches + blockIdx.x) * PS4;
+  const long long stride = (long long)n_patches * PS4;
+  for (int e = threadIdx.x; e < PS4; e += 256) {
+    const int pos = e / (TM / 4), row = TM * tile + 4 * (e % (TM / 4));
+    const int py = py0 + pos / BC, px = px0 + pos % BC;
+    if (py >= ny || px >= nx || row >= out_len) continue;
+    T4 v = base[e];
+    for (int j = 1; j < sp.x; ++j) v += base[j * stride + e];
+    T* o = out + ((long long)py * nx + px) * out_len + row;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int py = py0 + wave * RW + t / TPR, px = px0 + (t % TPR) * 16 + n;
-    if (py >= ny || px >= nx) continue;
-    const int local = (wave * RW + t / TPR) * BC + (t % TPR) * 16 + n;
-    float* o = out + ((long long)py * nx + px) * out_len;
-#pragma unroll
-    for (int h = 0; h < MH; ++h) {
-      // four consecutive rows per lane: 16-byte loads and stores
-      const long long e = (long long)local * TM + 16 * h + 4 * g;
-      floatx4 v = *reinterpret_cast<const floatx4*>(base + e);
-      for (int j = 1; j < sp.x; ++j) v += *reinterpret_cast<const floatx4*>(base + j * stride + e);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = TM * tile + 16 * h + 4 * g + i;
-        if (row < out_len) o[row] = v[i];
-      }
-    }
+    for (int i = 0; i < 4; ++i)
+      if (row + i < out_len) o[i] = v[i];
   }
 }
 
@@ -975,20 +1057,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-ApplyArgs make_args(const Layout& lay) {
-  ApplyArgs a;
-  a.tile_start = lay.d_tile_start;
-  a.meta = lay.d_meta;
-  a.out_len = lay.out_len;
-  a.n_ntiles = lay.in.ny * lay.in.ntx;
-  a.ntx = lay.in.ntx;
-  a.nx = lay.in.nx;
-  a.K = lay.in.K;
-  a.nxp = lay.in.nxp;
-  a.Lp = lay.in.Lp;
-  return a;
-}
-
 size_t elem_bytes(int dtype) {
   switch (dtype) {
     case AROAM_FP64: return 8;
@@ -1003,18 +1071,20 @@ constexpr int kAmaxParts = 512;  // position slices of the FP8 operand's chunk m
 }  // namespace
 
 const Layout& layout_for(const Model& m, bool adjoint, int dtype) {
-  if (dtype == AROAM_FP64) return adjoint ? m.g4a : m.g4f;
-  if (dtype == AROAM_FP32) return adjoint ? m.s4a : m.s4f;
+  if (dtype == AROAM_FP64) return adjoint ? m.r64a : m.r64f;
+  if (dtype == AROAM_FP32) return adjoint ? m.r32a : m.r32f;
   if (dtype == AROAM_BF16) return adjoint ? m.s8a : m.s8f;
   return adjoint ? m.f8a : m.f8f;
 }
 
 namespace {
 
-// The stage buffer of an apply: the padded input, then, for a staged layout with cut tiles,
-// the partial slots [slot][patch][position of the patch][TM rows] (FP32), then for FP8 the
-// operand's chunk scales: partial maxima [chunk][kAmaxParts] (FP32), E8M0 bytes [chunk] (int)
-// and inverse scales [chunk] (FP32).
+// The stage buffer of an apply.  FP32 and FP64: the partial slots of a layout with cut tiles,
+// [slot][patch][position of the patch][16 rows]; the size is never below that of the zero-padded
+// input, which limits the allocation-free apply and is charged to a solve.  BF16 and FP8: the
+// padded input, then the partial slots [slot][patch][position of the patch][TM rows] (FP32),
+// then for FP8 the operand's chunk scales: partial maxima [chunk][kAmaxParts] (FP32), E8M0
+// bytes [chunk] (int) and inverse scales [chunk] (FP32).
 struct StageParts {
   size_t input = 0, partial = 0, scales = 0;
   int chunks = 0;
@@ -1024,10 +1094,9 @@ StageParts stage_parts(const Model& m, bool adjoint, int dtype) {
   const Layout& lay = layout_for(m, adjoint, dtype);
   StageParts p;
   p.input = (size_t)round_up(lay.in.elems() * elem_bytes(dtype), 256);
-  if (dtype != AROAM_FP64 && lay.n_slots > 0) {
-    p.partial = (size_t)lay.n_slots * lay.n_patches * lay.TM * kPatchRows * kPatchCols *
-                sizeof(float);
-  }
+  if (lay.n_slots > 0)
+    p.partial = (size_t)lay.n_slots * lay.n_patches * lay.TM * lay.BR * lay.BC *
+                (dtype == AROAM_FP64 ? sizeof(double) : sizeof(float));
   if (dtype == AROAM_FP8E4M3) {
     p.chunks = (int)ceil_div(lay.in.L, 64);
     p.scales = (size_t)round_up((size_t)p.chunks * (kAmaxParts + 2) * 4, 256);
@@ -1039,6 +1108,7 @@ StageParts stage_parts(const Model& m, bool adjoint, int dtype) {
 
 size_t stage_bytes(const Model& m, bool adjoint, int dtype) {
   const StageParts p = stage_parts(m, adjoint, dtype);
+  if (dtype == AROAM_FP64 || dtype == AROAM_FP32) return std::max(p.input, p.partial);
   return p.input + p.partial + p.scales;
 }
 
@@ -1101,31 +1171,49 @@ int launch_split(const Layout& lay, const Pack& pk, const void* buf, float* part
   hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, (const void*)pk.d, (const uint16_t*)buf,
                      (float*)out, a);
   if (lay.n_slots > 0)
-    hipLaunchKernelGGL((k_add_slots<kPatchRows, kPatchCols, MH>),
+    hipLaunchKernelGGL((k_add_slots<float, kPatchRows, kPatchCols, 16 * MH>),
                        dim3((unsigned)lay.n_patches, (unsigned)lay.n_tiles), dim3(256), 0, st,
                        lay.d_tile_split, (const float*)partial, (float*)out, lay.n_patches, a.ncc,
                        a.nx, a.ny, a.out_len);
   return AROAM_OK;
 }
 
-template <typename T, int MH>
-int launch_staged(const Layout& lay, const Pack& pk, const void* buf, float* partial, void* out,
-                  hipStream_t st) {
-  static_assert(kPatchRows % 4 == 0 && kPatchCols % 16 == 0, "patch shape");
-  AROAM_CHECK(lay.TM == 16 * MH, AROAM_EINVAL, "tile height mismatch");
-  auto kern = k_apply_staged<T, kPatchRows, kPatchCols, MH>;
-  static std::atomic<unsigned long long> attr_set{0};
-  AROAM_TRY(allow_full_lds(kern, attr_set));
-  StagedArgs a;
-  AROAM_TRY(staged_args(lay, partial, (int)sizeof(T), a));
+template <class Op, int BR, int W, int P>
+int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial, void* out,
+                hipStream_t st) {
+  using In = typename Op::In;
+  const bool ragged = lay.in.L % Op::kVec != 0;
+  auto kern = ragged ? k_apply_ring<Op, BR, kPatchCols, W, P, true>
+                     : k_apply_ring<Op, BR, kPatchCols, W, P, false>;
+  static std::atomic<unsigned long long> attr_set[2];
+  AROAM_TRY(allow_full_lds(kern, attr_set[ragged]));
+  RingArgs a;
+  a.pieces = lay.d_pieces;
+  a.units = lay.d_units;
+  a.meta = lay.d_meta;
+  a.partial = partial;
+  a.n_patches = lay.n_patches;
+  a.out_len = lay.out_len;
+  a.nx = lay.in.nx;
+  a.ny = lay.in.ny;
+  a.K = lay.in.K;
+  a.L = lay.in.L;
+  a.ncc = (int)ceil_div(lay.in.nx, kPatchCols);
+  a.NCOL = lay.NCOL;
+  AROAM_CHECK(lay.TM == kTile && lay.BR == BR && lay.BC == kPatchCols &&
+                  lay.NCOL == kPatchCols + 2 * a.K && lay.CH == Op::kVec * Op::kVecs,
+              AROAM_EINVAL, "ring layout shape mismatch");
+  AROAM_CHECK(lay.n_patches == ceil_div(lay.in.ny, BR) * a.ncc, AROAM_EINVAL, "patch count mismatch");
+  AROAM_CHECK(lay.n_slots == 0 || partial, AROAM_EINVAL, "no partial slots for a cut layout");
+  const size_t red = (size_t)W * (W / P) * 64 * sizeof(typename Op::Acc);
   const dim3 grid((unsigned)lay.n_patches, (unsigned)lay.n_pieces);
-  hipLaunchKernelGGL(kern, grid, dim3(256), lay.lds_bytes, st, (const void*)pk.d, (const T*)buf,
-                     (float*)out, a);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * W), std::max(lay.lds_bytes, red), st, (const void*)pk.d,
+                     (const In*)in, (In*)out, a);
   if (lay.n_slots > 0)
-    hipLaunchKernelGGL((k_add_slots<kPatchRows, kPatchCols, MH>),
+    hipLaunchKernelGGL((k_add_slots<In, BR, kPatchCols, kTile>),
                        dim3((unsigned)lay.n_patches, (unsigned)lay.n_tiles), dim3(256), 0, st,
-                       lay.d_tile_split, (const float*)partial, (float*)out, lay.n_patches, a.ncc,
-                       a.nx, a.ny, a.out_len);
+                       lay.d_tile_split, (const In*)partial, (In*)out, lay.n_patches, a.ncc, a.nx,
+                       a.ny, a.out_len);
   return AROAM_OK;
 }
 
@@ -1183,23 +1271,10 @@ int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* i
   hipLaunchKernelGGL(kern, grid, dim3(256), std::max(lay.lds_bytes, red_bytes(kSplit8, 2)), st,
                      (const uint8_t*)pk.d, (const uint8_t*)staged, (float*)out, a);
   if (lay.n_slots > 0)
-    hipLaunchKernelGGL((k_add_slots<kPatchRows, kPatchCols, 2>),
+    hipLaunchKernelGGL((k_add_slots<float, kPatchRows, kPatchCols, kTileRows8>),
                        dim3((unsigned)lay.n_patches, (unsigned)lay.n_tiles), dim3(256), 0, st,
                        lay.d_tile_split, (const float*)partial, (float*)out, lay.n_patches, a.ncc,
                        a.nx, a.ny, a.out_len);
-  return AROAM_OK;
-}
-
-int launch_f64(const ApplyArgs& a, int n_tiles, const void* pack, const void* in, void* out,
-               hipStream_t st) {
-  constexpr int W = 8;
-  const int wide = (int)ceil_div(a.n_ntiles, 4);
-  if ((long long)wide * n_tiles >= 512)
-    hipLaunchKernelGGL((k_apply_f64<4, W>), dim3((unsigned)wide, (unsigned)n_tiles), dim3(64 * W),
-                       0, st, (const double*)pack, (const double*)in, (double*)out, a);
-  else
-    hipLaunchKernelGGL((k_apply_f64<1, W>), dim3((unsigned)a.n_ntiles, (unsigned)n_tiles),
-                       dim3(64 * W), 0, st, (const double*)pack, (const double*)in, (double*)out, a);
   return AROAM_OK;
 }
 
@@ -1209,33 +1284,21 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
   const Layout& lay = layout_for(m, adjoint, dtype);
   const Pack& pk = adjoint ? m.adj_pack[dtype] : m.fwd_pack[dtype];
   const PadGeom& pg = lay.in;
-  const dim3 sgrid((unsigned)(pg.nyp * pg.nxp));
   if (dtype == AROAM_FP8E4M3) {
     AROAM_TRY(launch_fp8(m, lay, pk, (const float*)in, buf, stage_parts(m, adjoint, dtype), out,
                          st));
-    AROAM_HIP(hipGetLastError());
-    return AROAM_OK;
-  }
-  if (dtype == AROAM_FP64)
-    hipLaunchKernelGGL((k_stage<double, double>), sgrid, dim3(256), 0, st, (const double*)in,
-                       (double*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L, pg.Lp);
-  else if (dtype == AROAM_FP32)
-    hipLaunchKernelGGL((k_stage<float, float>), sgrid, dim3(256), 0, st, (const float*)in,
-                       (float*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L, pg.Lp);
-  else
-    hipLaunchKernelGGL((k_stage<float, uint16_t>), sgrid, dim3(256), 0, st, (const float*)in,
-                       (uint16_t*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L, pg.Lp);
-  if (dtype == AROAM_FP64) {
-    AROAM_CHECK(lay.G == 4, AROAM_EINVAL, "FP64 layout needs runs of four entries");
-    AROAM_TRY(launch_f64(make_args(lay), lay.n_tiles, pk.d, buf, out, st));
+  } else if (dtype == AROAM_FP64) {
+    AROAM_TRY((launch_ring<OpF64, kRingRows, kRingWaves, kRingGroups>(lay, pk, in, buf, out, st)));
+  } else if (dtype == AROAM_FP32) {
+    AROAM_TRY((launch_ring<OpF32, kRingRows, kRingWaves, kRingGroups>(lay, pk, in, buf, out, st)));
   } else {
+    hipLaunchKernelGGL((k_stage<float, uint16_t>), dim3((unsigned)(pg.nyp * pg.nxp)), dim3(256), 0,
+                       st, (const float*)in, (uint16_t*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L,
+                       pg.Lp);
     const StageParts sp = stage_parts(m, adjoint, dtype);
     float* partial =
         sp.partial > 0 ? reinterpret_cast<float*>(static_cast<char*>(buf) + sp.input) : nullptr;
-    if (dtype == AROAM_FP32)
-      AROAM_TRY((launch_staged<float, 1>(lay, pk, buf, partial, out, st)));
-    else
-      AROAM_TRY((launch_split<kTileRows8 / 16>(lay, pk, buf, partial, out, st)));
+    AROAM_TRY((launch_split<kTileRows8 / 16>(lay, pk, buf, partial, out, st)));
   }
   AROAM_HIP(hipGetLastError());
   return AROAM_OK;

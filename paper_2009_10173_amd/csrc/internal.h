@@ -70,6 +70,18 @@ struct PadGeom {
 // with one (FP32, runs of 4) the entries of the runs, one MFMA each, that they reach.
 constexpr int kMetaMaskShift = 28;
 
+// LDS form of the ring layouts (FP64, FP32): entries of a K-group, entries of a chunk, LDS bytes
+// of a staged column (its chunk and 16 bytes of padding, an odd number of 16-byte groups, which
+// spreads neighbouring columns over the LDS banks) and of a run within it.  FP64 holds the
+// chunk's eight doubles.  FP32 holds each of the chunk's sixteen values as three BF16 parts, the
+// parts of the chunk after one another.
+struct RingShape {
+  int G, CH, col_bytes, run_bytes;
+};
+constexpr RingShape kRingF64{4, 8, 80, 32};
+constexpr RingShape kRingF32{8, 16, kRing32ColumnBytes, 16};
+constexpr int kRingWaves = 4, kRingGroups = 1;  // waves of a workgroup, row groups they form
+
 // Band tiles of one operator (forward: rows = time, K = (offset, depth); adjoint: rows =
 // depth, K = (offset, time)) at one K-group width G.  A K-group is G consecutive entries of
 // one table column block; four K-groups form a bundle, which one MFMA step consumes.
@@ -147,8 +159,8 @@ struct Model {
   int* d_colidx = nullptr;       // [n_off][nz]
   int* d_lo = nullptr;           // [n_stored]
   long long* d_off = nullptr;    // [n_stored + 1]
-  Layout g4f, g4a;               // direct form, G = 4: FP64 forward / adjoint
-  Layout s4f, s4a;               // LDS-staged, G = 4: FP32
+  Layout r64f, r64a;             // LDS ring: FP64 forward / adjoint
+  Layout r32f, r32a;             // LDS ring: FP32
   Layout s8f, s8a;               // LDS-staged, G = 8: BF16
   Layout f8f, f8a;               // LDS-staged, G = 8, bundles of the block-scaled FP8 MFMA
   Pack fwd_pack[4], adj_pack[4]; // indexed by aroam_dtype

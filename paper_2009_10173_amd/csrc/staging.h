@@ -17,6 +17,16 @@ constexpr int kChunkBytes = 64;      // inner-axis entries of one staged column 
 constexpr int kColumnBytes = 80;     // LDS stride of a staged column: chunk + 16 bytes of padding
 constexpr long long kLdsBytes = 160 * 1024;  // LDS of one gfx950 compute unit
 
+// The FP64 and FP32 applies own patches of kRingRows x kPatchCols positions (a ring of
+// kRingRows + 1 rows); their staged columns take up to kRing32ColumnBytes.
+constexpr int kRingRows = 4;
+constexpr int kRing32ColumnBytes = 112;
+
+// LDS bytes of their row ring.
+constexpr long long ring_lds_bytes(int k_half, int column_bytes) {
+  return (long long)(kRingRows + 1) * (kPatchCols + 2 * k_half) * column_bytes;
+}
+
 // LDS bytes of the row ring of a staged apply with offsets -k_half .. k_half.
 constexpr long long staged_lds_bytes(int k_half) {
   return (long long)(kPatchRows + 1) * (kPatchCols + 2 * k_half) * kColumnBytes;
@@ -28,5 +38,8 @@ constexpr int max_k_half() {
   while (staged_lds_bytes(k + 1) <= kLdsBytes) ++k;
   return k;
 }
+
+static_assert(ring_lds_bytes(max_k_half(), kRing32ColumnBytes) <= kLdsBytes,
+              "the FP32 ring fits wherever the BF16 and FP8 stage does");
 
 }  // namespace aroam

@@ -240,6 +240,30 @@ __global__ void k_pack(long long total, int G, int TM, bool adjoint,
   }
 }
 
+// FP32 pack of the ring layout: part p (three BF16 values whose sum is the FP32 value) of entry j
+// of row m of K-group 4 b + g goes to [b][p][g][m][j].
+__global__ void k_pack_f32(long long total, bool adjoint, const int4* __restrict__ groups, int nz,
+                           int nt, const int* __restrict__ colidx, const int* __restrict__ lo,
+                           const long long* __restrict__ off, const double* __restrict__ band,
+                           uint16_t* __restrict__ pack) {
+  constexpr int G = kRingF32.G;
+  for (long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x; idx < total;
+       idx += (long long)gridDim.x * blockDim.x) {
+    const long long grp = idx / (kTile * G);
+    const int m = (int)((idx / G) % kTile), j = (int)(idx % G);
+    const int4 gd = groups[grp];  // (offset index, start, tile, active)
+    const int n = adjoint ? gd.y + j : kTile * gd.z + m;
+    const int k = adjoint ? kTile * gd.z + m : gd.y + j;
+    float r = (float)table_value(gd.x, n, k, nz, nt, colidx, lo, off, band);
+    for (int p = 0; p < 3; ++p) {
+      const float c = p ? r : fminf(fmaxf(r, -3.3895313892515355e38f), 3.3895313892515355e38f);
+      const uint16_t b = cvt<uint16_t>((double)c);
+      pack[(((grp / kLaneGroups) * 3 + p) * kLaneGroups + grp % kLaneGroups) * (kTile * G) + m * G + j] = b;
+      r -= __uint_as_float((uint32_t)b << 16);
+    }
+  }
+}
+
 // Per (offset, 16-depth block) FP32 scale: the smallest power of two >= amax / 448 of the
 // block's table values (powers of two let the kernel apply the scale inside the FP8 -> BF16
 // conversion).
@@ -349,53 +373,6 @@ bool tile_hits(const Model& m, bool adjoint, int G, int TM, int t, int oi, std::
   return any;
 }
 
-// Build the K-group lists of one operator (direct form).  For output tile t (rows 16t ..
-// 16t+15) and each offset, the K-groups are the G-aligned runs of the inner axis that meet
-// some column's band inside the tile; runs with no band entry are skipped; each tile's list
-// is padded with empty groups to a multiple of four (one bundle = four groups).
-int build_layout(const Model& m, bool adjoint, int G, Layout& lay, size_t& bytes) {
-  const aroam_grid& g = m.grid;
-  const int K = m.K, W = 2 * K + 1, nz = g.nz, nt = g.nt;
-  lay.G = G;
-  lay.out_len = adjoint ? nz : nt;
-  lay.n_tiles = (int)ceil_div(lay.out_len, kTile);
-  lay.in = pad_geom(g, adjoint ? nt : nz);
-  const int inner = adjoint ? nt : nz;
-  std::vector<int4> groups;
-  std::vector<int> meta;
-  lay.h_tile_start.assign(lay.n_tiles + 1, 0);
-  std::vector<char> hit((size_t)ceil_div(inner, G) + 1);
-  for (int t = 0; t < lay.n_tiles; ++t) {
-    lay.h_tile_start[t] = (int)(groups.size() / kLaneGroups);
-    for (int oi = 0; oi < m.n_off; ++oi) {
-      const int dy = oi / W - K, dx = oi % W - K;
-      if (!tile_hits(m, adjoint, G, kTile, t, oi, hit)) continue;
-      for (size_t q = 0; q < hit.size(); ++q) {
-        if (!hit[q]) continue;
-        const int start = (int)q * G;
-        groups.push_back(make_int4(oi, start, t, 1));
-        const long long delta =
-            adjoint ? ((long long)(-dy) * lay.in.nxp - dx) * lay.in.Lp + start
-                    : ((long long)dy * lay.in.nxp + dx) * lay.in.Lp + start;
-        meta.push_back((int)delta);
-      }
-    }
-    while (groups.size() % kLaneGroups) {
-      groups.push_back(make_int4(-1, 0, t, 0));
-      meta.push_back(0);
-    }
-  }
-  lay.h_tile_start[lay.n_tiles] = (int)(groups.size() / kLaneGroups);
-  lay.n_bundles = (long long)groups.size() / kLaneGroups;
-  lay.mac_exec = lay.n_bundles * kLaneGroups * kTile * G * (long long)g.ny * 16 * lay.in.ntx;
-  AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
-              "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
-  AROAM_TRY(alloc_copy(&lay.d_tile_start, lay.h_tile_start, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
-  return AROAM_OK;
-}
-
 // LDS-staged form (see Layout).  For tile t, the hit runs of every lateral offset are
 // grouped by chunk (CH inner entries = CH / G runs) and by input row offset; each non-empty
 // (chunk, row offset) is one stage unit whose K-groups (dx, run) are packed four to a
@@ -413,9 +390,13 @@ int build_layout(const Model& m, bool adjoint, int G, Layout& lay, size_t& bytes
 // groups.  Lane (n, g) of a bundle reads vector run_g of staged column c + n + col_g; with a
 // column stride of 80 bytes (5 groups of 16 bytes) its bank group is 5 (c + n + col_g) + run_g
 // (mod 16).  The patch offset c and the row start shift all lanes of a read alike.
-constexpr int kColumnGroups = kColumnBytes / 16;  // LDS column stride in 16-byte groups
+struct BankShape {
+  int col, run;  // LDS strides of a column and of a run, in 16-byte groups
+  int nrun;      // runs per staged column (at most four)
+};
+constexpr BankShape kBanks16{kColumnBytes / 16, 1, 4};  // BF16
 
-bool pair_conflict_free(int col_a, int run_a, int col_b, int run_b) {
+bool pair_conflict_free(const BankShape& sh, int col_a, int run_a, int col_b, int run_b) {
   static const int lo_hi[8] = {0, 1, 2, 3, 12, 13, 14, 15};
   static const int mid[8] = {4, 5, 6, 7, 8, 9, 10, 11};
   for (int pass = 0; pass < 2; ++pass) {
@@ -423,8 +404,8 @@ bool pair_conflict_free(int col_a, int run_a, int col_b, int run_b) {
     const int* nb = pass ? lo_hi : mid;  // lanes of the odd group
     unsigned used = 0;
     for (int i = 0; i < 8; ++i) {
-      const int ba = (kColumnGroups * (na[i] + col_a) + run_a) & 15;
-      const int bb = (kColumnGroups * (nb[i] + col_b) + run_b) & 15;
+      const int ba = (sh.col * (na[i] + col_a) + sh.run * run_a) & 15;
+      const int bb = (sh.col * (nb[i] + col_b) + sh.run * run_b) & 15;
       used |= (1u << ba) | (1u << bb);
     }
     if (used != 0xffffu) return false;
@@ -447,17 +428,20 @@ struct UnitEntry {
 // matching class.  The result has an even number of entries; with pad4 it is padded to a
 // multiple of four (whole bundles).
 struct CompatTable {
+  BankShape sh;
   std::vector<int> partners[64];  // classes whose K-groups pair with this one without conflicts
-  CompatTable() {
+  explicit CompatTable(const BankShape& s) : sh(s) {
     for (int a = 0; a < 64; ++a)
       for (int b = 0; b < 64; ++b)
-        if (pair_conflict_free(a >> 2, a & 3, b >> 2, b & 3)) partners[a].push_back(b);
+        if ((a & 3) < sh.nrun && (b & 3) < sh.nrun &&
+            pair_conflict_free(sh, a >> 2, a & 3, b >> 2, b & 3))
+          partners[a].push_back(b);
   }
 };
 
-std::vector<UnitEntry> pair_unit(const std::vector<UnitEntry>& in, int maxcol, int t,
-                                 bool pad4 = true) {
-  static const CompatTable table;  // classes (column mod 16, run)
+std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<UnitEntry>& in,
+                                 int maxcol, int t, bool pad4 = true) {
+  const BankShape& sh = table.sh;
   std::vector<int> cls_items[64];
   for (int i = (int)in.size() - 1; i >= 0; --i)
     cls_items[((in[i].col & 15) << 2) | in[i].run].push_back(i);
@@ -504,8 +488,8 @@ std::vector<UnitEntry> pair_unit(const std::vector<UnitEntry>& in, int maxcol, i
     UnitEntry p = pad0;
     bool found = false;
     for (int c = 0; c <= maxcol && !found; ++c)
-      for (int r = 0; r < 4 && !found; ++r)
-        if (pair_conflict_free(e.col, e.run, c, r)) {
+      for (int r = 0; r < sh.nrun && !found; ++r)
+        if (pair_conflict_free(sh, e.col, e.run, c, r)) {
           p.col = c;
           p.run = r;
           found = true;
@@ -515,8 +499,8 @@ std::vector<UnitEntry> pair_unit(const std::vector<UnitEntry>& in, int maxcol, i
   }
   if (pad4 && out.size() % 4) {
     UnitEntry p = pad0;
-    for (int r = 1; r < 4; ++r)
-      if (pair_conflict_free(0, 0, 0, r)) {
+    for (int r = 1; r < sh.nrun; ++r)
+      if (pair_conflict_free(sh, 0, 0, 0, r)) {
         p.run = r;
         break;
       }
@@ -526,26 +510,24 @@ std::vector<UnitEntry> pair_unit(const std::vector<UnitEntry>& in, int maxcol, i
   return out;
 }
 
-// Order a stage unit's K-groups into bundles.  With two 16-row halves per tile, K-groups
-// are first grouped by the halves their bands reach, so that most bundles reach only one
-// half and the kernel skips the other half's MFMAs; with one half (FP32, runs of 4), by the
-// entries of their run that the band reaches in the tile, so that the kernel skips the
-// MFMAs of entries no K-group of the bundle reaches.  Each group is paired for the LDS as
-// above.
+// Order a stage unit's K-groups into bundles of a tile of NH 16-row halves: K-groups are first
+// grouped by the halves their bands reach, so that most bundles reach only one half and the
+// kernel skips the other half's MFMAs.  Each group is paired for the LDS as above.
 std::vector<UnitEntry> order_unit(const std::vector<UnitEntry>& in, int maxcol, int t, int NH) {
+  static const CompatTable table(kBanks16);
+  const BankShape& sh = table.sh;
   std::vector<UnitEntry> out;
-  const int nmask = NH > 1 ? 1 << NH : 16;  // half masks, or masks of a run's four entries
-  for (int mask = 1; mask < nmask; ++mask) {
+  for (int mask = 1; mask < 1 << NH; ++mask) {
     std::vector<UnitEntry> cls;
     for (const UnitEntry& e : in)
       if (e.mask == mask) cls.push_back(e);
     if (cls.empty()) continue;
-    for (const UnitEntry& e : pair_unit(cls, maxcol, t, false)) out.push_back(e);
+    for (const UnitEntry& e : pair_unit(table, cls, maxcol, t, false)) out.push_back(e);
   }
   if (out.size() % 4) {
     UnitEntry p{make_int4(-1, 0, t, 0), 0, 0, 0};
-    for (int r = 1; r < 4; ++r)
-      if (pair_conflict_free(0, 0, 0, r)) {
+    for (int r = 1; r < sh.nrun; ++r)
+      if (pair_conflict_free(sh, 0, 0, 0, r)) {
         p.run = r;
         break;
       }
@@ -559,10 +541,11 @@ std::vector<UnitEntry> order_unit(const std::vector<UnitEntry>& in, int maxcol, 
 // capped at 1 GiB.
 int plan_pieces(Layout& lay, const std::vector<int>& tile_units,
                 const std::vector<std::vector<int>>& chunk_starts,
-                const std::vector<double>& unit_work, int slots, size_t& bytes) {
-  const double slot_bytes = (double)lay.TM * kPatchRows * kPatchCols * sizeof(float);
+                const std::vector<double>& unit_work, int slots, size_t& bytes,
+                size_t esize = sizeof(float), double max_slots = (double)(1ll << 30)) {
+  const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * esize;
   const LaunchPlan plan = plan_launch(tile_units, chunk_starts, unit_work, lay.n_patches, slots,
-                                      /*allow_cut=*/true, slot_bytes, (double)(1ll << 30));
+                                      /*allow_cut=*/true, slot_bytes, max_slots);
   std::vector<int4> pieces;
   for (const PlanPiece& p : plan.pieces) pieces.push_back(make_int4(p.tile, p.u0, p.u1, p.slot));
   std::vector<int2> split(lay.n_tiles);
@@ -604,8 +587,7 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   std::vector<int> meta, tile_units(lay.n_tiles + 1, 0);
   std::vector<std::vector<char>> hits(W, std::vector<char>((size_t)nq + 1));
   const int NH = TM / kTile;  // 16-row halves per tile
-  std::vector<std::vector<char>> hhits(NH > 1 ? (size_t)W * NH : 0,
-                                       std::vector<char>((size_t)nq + 1));
+  std::vector<std::vector<char>> hhits((size_t)W * NH, std::vector<char>((size_t)nq + 1));
   std::vector<int> bmask;
   std::vector<char> dx_any(W);
   std::vector<std::vector<int>> chunk_starts(lay.n_tiles);  // first unit of each chunk
@@ -620,7 +602,7 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
       const int slot = adjoint ? (W - 1 - a) : a;
       for (int b = 0; b < W; ++b) {
         dx_any[b] = tile_hits(m, adjoint, G, TM, t, a * W + b, hits[b]);
-        if (NH > 1 && dx_any[b])
+        if (dx_any[b])
           for (int h = 0; h < NH; ++h)
             tile_hits(m, adjoint, G, kTile, t * NH + h, a * W + b, hhits[(size_t)b * NH + h]);
       }
@@ -630,13 +612,8 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
         for (int q = 0; q < nq; ++q) {
           if (!hits[b][q]) continue;
           const int c = q / qpc;
-          // two row halves: the halves the K-group's band reaches; one half (G = 4): the
-          // entries of the run the band reaches in this tile (one MFMA each)
-          int mask = (unsigned char)hits[b][q] & 15;
-          if (NH > 1) {
-            mask = 0;
-            for (int h = 0; h < NH; ++h) mask |= hhits[(size_t)b * NH + h][q] ? 1 << h : 0;
-          }
+          int mask = 0;  // the halves the K-group's band reaches
+          for (int h = 0; h < NH; ++h) mask |= hhits[(size_t)b * NH + h][q] ? 1 << h : 0;
           per[(size_t)c * W + slot].push_back(
               UnitEntry{make_int4(a * W + b, q * G, t, 1), col, (q * G - c * CH) / G, mask});
         }
@@ -664,9 +641,9 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
         units.push_back(make_int4(R - K, c * CH, (int)(first / kLaneGroups),
                                   (int)(groups.size() / kLaneGroups)));
         urows.push_back(make_int2(lo, R + BR));
-        double w = 0;  // MFMA halves (one-half tiles: quarters of a bundle's four MFMAs)
+        double w = 0;
         for (size_t b = first / kLaneGroups; b < groups.size() / kLaneGroups; ++b)
-          w += __builtin_popcount((unsigned)bmask[b]) * (NH > 1 ? 1.0 : 0.25);
+          w += __builtin_popcount((unsigned)bmask[b]);
         unit_work.push_back(w);
         prevR = R;
       }
@@ -675,35 +652,10 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   tile_units[lay.n_tiles] = (int)units.size();
   lay.n_units = (long long)units.size();
   lay.n_bundles = (long long)groups.size() / kLaneGroups;
-  // MACs the kernel issues: per bundle, its 16-row halves times the positions of every patch.
-  // The FP32 kernel (esize 4) leaves out two things: a wave's MFMAs for a unit whose row
-  // offset makes its BR / 4 rows read only the zero rows around the grid, and the second
-  // 16-position tile column of a patch that holds at most 16 scan columns.
-  long long mac_exec = 0;
-  {
-    const int RW = BR / 4;
-    const long long cols =
-        esize == 4 && BC == 32 && g.nx % BC > 0 && g.nx % BC <= 16
-            ? (long long)(g.nx / BC) * BC + 16
-            : round_up(g.nx, BC);
-    std::vector<long long> rows_live(W, 0);  // computed rows per row offset dy (index dy + K)
-    for (int d = 0; d < W; ++d)
-      for (int py0 = 0; py0 < g.ny; py0 += BR)
-        for (int w = 0; w < 4; ++w) {
-          const int src = py0 + w * RW + d - K;
-          if (esize != 4 || (src + RW > 0 && src < g.ny)) rows_live[d] += RW;
-        }
-    // per position, a bundle issues 16 rows x 4 K-groups x G entries per reached half, or,
-    // with one half (G = 4), 16 rows x 4 K-groups for each of its four MFMAs it issues
-    const long long per_bit = (long long)kLaneGroups * kTile * (NH > 1 ? G : 1);
-    for (size_t u = 0; u < units.size(); ++u) {
-      long long bits = 0;
-      for (int b = units[u].z; b < units[u].w; ++b) bits += __builtin_popcount((unsigned)bmask[b]);
-      mac_exec += bits * rows_live[units[u].x + K];
-    }
-    mac_exec *= per_bit * cols;
-  }
-  lay.mac_exec = mac_exec;
+  // MACs the kernel issues: per bundle, its 16-row halves times the positions of every patch
+  long long halves = 0;
+  for (int bm : bmask) halves += __builtin_popcount((unsigned)bm);
+  lay.mac_exec = halves * kLaneGroups * kTile * G * round_up(g.ny, BR) * round_up(g.nx, BC);
   AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
               "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
   AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
@@ -715,6 +667,89 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   int cus = 0;
   AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
   return plan_pieces(lay, tile_units, chunk_starts, unit_work, 3 * std::max(cus, 1), bytes);
+}
+
+// LDS-ring form (FP64, FP32; see Layout and RingShape): tiles of 16 rows, stage units as above,
+// no masks (every bundle reaches its tile).  `pad` is the geometry of the zero-padded input,
+// which bounds the partial slots.
+int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const PadGeom& pad,
+                      size_t esize, Layout& lay, size_t& bytes) {
+  const aroam_grid& g = m.grid;
+  const int K = m.K, W = 2 * K + 1, TM = kTile, BR = kRingRows, BC = kPatchCols;
+  lay.G = rs.G;
+  lay.TM = TM;
+  lay.staged = true;
+  lay.CH = rs.CH;
+  lay.BR = BR;
+  lay.BC = BC;
+  lay.NCOL = BC + 2 * K;
+  lay.CS = rs.col_bytes;
+  lay.out_len = adjoint ? g.nz : g.nt;
+  lay.n_tiles = (int)ceil_div(lay.out_len, TM);
+  lay.in = pad;
+  lay.lds_bytes = (size_t)ring_lds_bytes(K, rs.col_bytes);
+  const int inner = adjoint ? g.nt : g.nz;
+  const int nq = (int)ceil_div(inner, rs.G), qpc = rs.CH / rs.G, nch = (int)ceil_div(inner, rs.CH);
+  const CompatTable table(BankShape{rs.col_bytes / 16, rs.run_bytes / 16, qpc});
+  std::vector<int4> groups, units;
+  std::vector<int> meta, tile_units(lay.n_tiles + 1, 0);
+  std::vector<char> hits((size_t)nq + 1);
+  std::vector<std::vector<int>> cuts(lay.n_tiles);  // a piece may start at any unit
+  std::vector<double> unit_work;                    // bundles of a unit
+  std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
+  for (int t = 0; t < lay.n_tiles; ++t) {
+    tile_units[t] = (int)units.size();
+    for (auto& v : per) v.clear();
+    for (int a = 0; a < W; ++a) {
+      const int slot = adjoint ? (W - 1 - a) : a;  // input row offset + K
+      for (int b = 0; b < W; ++b) {
+        if (!tile_hits(m, adjoint, rs.G, TM, t, a * W + b, hits)) continue;
+        const int col = adjoint ? (W - 1 - b) : b;  // input column offset + K
+        for (int q = 0; q < nq; ++q)
+          if (hits[q])
+            per[(size_t)(q / qpc) * W + slot].push_back(
+                UnitEntry{make_int4(a * W + b, q * rs.G, t, 1), col, q % qpc, 1});
+      }
+    }
+    for (int c = 0; c < nch; ++c)
+      for (int R = 0; R < W; ++R) {
+        const auto& lst = per[(size_t)c * W + R];
+        if (lst.empty()) continue;
+        const int first = (int)(groups.size() / kLaneGroups);
+        for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
+          groups.push_back(e.group);
+          meta.push_back(e.col * rs.col_bytes + e.run * rs.run_bytes);
+        }
+        cuts[t].push_back((int)units.size());
+        units.push_back(make_int4(R - K, c * rs.CH, first, (int)(groups.size() / kLaneGroups)));
+        unit_work.push_back(units.back().w - units.back().z);
+      }
+  }
+  tile_units[lay.n_tiles] = (int)units.size();
+  lay.n_units = (long long)units.size();
+  lay.n_bundles = (long long)groups.size() / kLaneGroups;
+  // MACs the kernel issues: per bundle 16 rows x 4 G entries for every computed position, which
+  // leaves out row pairs of a patch that have no output or input row inside the scan and the
+  // second 16-position tile column of a patch that holds at most 16 scan columns
+  const long long cols = g.nx % BC > 0 && g.nx % BC <= 16 ? (long long)(g.nx / BC) * BC + 16
+                                                          : round_up(g.nx, BC);
+  lay.mac_exec = 0;
+  for (const int4& u : units) {
+    long long rows = 0;
+    for (int o = 0; o < g.ny; o += 2) rows += o + u.x + 2 > 0 && o + u.x < g.ny ? 2 : 0;
+    lay.mac_exec += (u.w - u.z) * rows;
+  }
+  lay.mac_exec *= (long long)kLaneGroups * rs.G * TM * cols;
+  AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
+              "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
+  AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
+  AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
+  AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
+  lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
+  int cus = 0;
+  AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
+  return plan_pieces(lay, tile_units, cuts, unit_work, 3 * std::max(cus, 1), bytes, esize,
+                     std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)));
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
@@ -913,6 +948,21 @@ int pack_dtype(const Model& m, const Layout& lay, bool adjoint, Pack& p, hipStre
     hipLaunchKernelGGL(k_pack<T>, dim3(blocks), dim3(256), 0, st, total, lay.G, lay.TM, adjoint,
                        lay.d_groups, m.grid.nz, m.grid.nt, m.d_colidx, m.d_lo, m.d_off,
                        m.d_band, (T*)p.d);
+    AROAM_HIP(hipGetLastError());
+  }
+  return AROAM_OK;
+}
+
+int pack_f32(const Model& m, const Layout& lay, bool adjoint, Pack& p, hipStream_t st,
+             size_t& bytes) {
+  const long long total = lay.n_bundles * kLaneGroups * kTile * kRingF32.G;
+  p.bytes = std::max<long long>(1, total) * 3 * sizeof(uint16_t);
+  AROAM_HIP(hipMalloc(&p.d, p.bytes));
+  bytes += p.bytes;
+  if (total > 0) {
+    const int blocks = (int)std::min<long long>(ceil_div(total, 256), 1 << 16);
+    hipLaunchKernelGGL(k_pack_f32, dim3(blocks), dim3(256), 0, st, total, adjoint, lay.d_groups,
+                       m.grid.nz, m.grid.nt, m.d_colidx, m.d_lo, m.d_off, m.d_band, (uint16_t*)p.d);
     AROAM_HIP(hipGetLastError());
   }
   return AROAM_OK;
@@ -1264,14 +1314,18 @@ int set_columns(Model& m, const std::vector<int>& foi, const std::vector<int>& f
 // Band tiles of the always-packed dtypes (FP64 direct form, FP32 staged form).
 int pack_fp(Model& m, hipStream_t st, size_t& bytes) {
   // band tiles
-  AROAM_TRY(build_layout(m, false, 4, m.g4f, bytes));
-  AROAM_TRY(build_layout(m, true, 4, m.g4a, bytes));
-  AROAM_TRY(pack_dtype<double>(m, m.g4f, false, m.fwd_pack[AROAM_FP64], st, bytes));
-  AROAM_TRY(pack_dtype<double>(m, m.g4a, true, m.adj_pack[AROAM_FP64], st, bytes));
-  AROAM_TRY(build_staged_layout(m, false, 4, kTile, 16, kPatchRows, kPatchCols, 4, m.s4f, bytes));
-  AROAM_TRY(build_staged_layout(m, true, 4, kTile, 16, kPatchRows, kPatchCols, 4, m.s4a, bytes));
-  AROAM_TRY(pack_dtype<float>(m, m.s4f, false, m.fwd_pack[AROAM_FP32], st, bytes));
-  AROAM_TRY(pack_dtype<float>(m, m.s4a, true, m.adj_pack[AROAM_FP32], st, bytes));
+  for (const bool adj : {false, true}) {
+    const int L = adj ? m.grid.nt : m.grid.nz;
+    Layout& r64 = adj ? m.r64a : m.r64f;
+    Layout& r32 = adj ? m.r32a : m.r32f;
+    AROAM_TRY(build_ring_layout(m, adj, kRingF64, pad_geom(m.grid, L), sizeof(double), r64, bytes));
+    AROAM_TRY(build_ring_layout(m, adj, kRingF32,
+                                pad_geom(m.grid, L, kPatchRows, kPatchCols, kRingF32.CH),
+                                sizeof(float), r32, bytes));
+    Pack* pack = adj ? m.adj_pack : m.fwd_pack;
+    AROAM_TRY(pack_dtype<double>(m, r64, adj, pack[AROAM_FP64], st, bytes));
+    AROAM_TRY(pack_f32(m, r32, adj, pack[AROAM_FP32], st, bytes));
+  }
   m.dtype_mask = (1u << AROAM_FP64) | (1u << AROAM_FP32);
   return AROAM_OK;
 }
@@ -1344,7 +1398,7 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
   const size_t n_groups = (size_t)lay.n_bundles * (fp8 ? 16 : kLaneGroups);
   std::vector<int4> groups;
   AROAM_TRY(download(groups, lay.d_groups, n_groups));
-  const size_t esize = dtype == AROAM_FP32 ? 4 : dtype == AROAM_BF16 ? 2 : 1;
+  const size_t esize = dtype == AROAM_FP32 ? 6 : dtype == AROAM_BF16 ? 2 : 1;
   std::vector<uint8_t> raw;
   AROAM_TRY(download(raw, pk.d, n_groups * TM * G * esize));
   std::vector<int> rec;
@@ -1364,9 +1418,15 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
         if (n >= nt || k >= nz) continue;
         double v;
         if (dtype == AROAM_FP32) {
-          float f;
-          std::memcpy(&f, &raw[4 * (q * TM * G + (size_t)r * G + j)], 4);
-          v = f;
+          v = 0;  // the sum of the three parts
+          for (size_t p = 0; p < 3; ++p) {
+            const size_t e = (((q / kLaneGroups) * 3 + p) * kLaneGroups + q % kLaneGroups) * TM * G +
+                             (size_t)r * G + j;
+            const uint32_t bits = (uint32_t)(raw[2 * e] | (raw[2 * e + 1] << 8)) << 16;
+            float f;
+            std::memcpy(&f, &bits, 4);
+            v += f;
+          }
         } else if (dtype == AROAM_BF16) {
           const size_t e = q * TM * G + (size_t)r * G + j;
           const uint32_t bits = (uint32_t)(raw[2 * e] | (raw[2 * e + 1] << 8)) << 16;
@@ -1494,7 +1554,7 @@ int finish_model(Model* m, int rc, unsigned mask, hipStream_t st, Model** out) {
   // account device memory
   size_t b = (size_t)std::max<long long>(1, m->nnz_stored) * sizeof(double);
   b += m->h_colidx.size() * sizeof(int) + m->n_stored * sizeof(int) + m->h_off.size() * 8;
-  for (const Layout* l : {&m->g4f, &m->g4a, &m->s4f, &m->s4a, &m->s8f, &m->s8a, &m->f8f, &m->f8a})
+  for (const Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->s8f, &m->s8a, &m->f8f, &m->f8a})
     b += l->n_bundles * kLaneGroups * (sizeof(int) + sizeof(int4)) * (l == &m->f8f || l == &m->f8a ? 4 : 1) +
          (l->staged ? l->n_bundles * sizeof(int) + l->n_pieces * sizeof(int4) +
                           l->n_tiles * sizeof(int2)
@@ -1515,7 +1575,7 @@ void destroy_model(Model* m) {
   (void)hipFree(m->d_colidx);
   (void)hipFree(m->d_lo);
   (void)hipFree(m->d_off);
-  for (Layout* l : {&m->g4f, &m->g4a, &m->s4f, &m->s4a, &m->s8f, &m->s8a, &m->f8f, &m->f8a}) {
+  for (Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->s8f, &m->s8a, &m->f8f, &m->f8a}) {
     (void)hipFree(l->d_tile_start);
     (void)hipFree(l->d_meta);
     (void)hipFree(l->d_groups);
