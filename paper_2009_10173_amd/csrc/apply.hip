@@ -369,8 +369,8 @@ typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));
 // add up to no less than 2^-16 of the leading one; the three left out are below 2^-24 of it.
 // The sums run in FP32.  Six BF16 MFMAs of K = 32 take 96 cycles where the eight FP32 MFMAs of
 // K = 4 take 256, and round the sum less often: the 400 x 400 forward took 181 ms on
-// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 116 ms at 1.7e-6 (200 x 200
-// adjoint: 8.05 ms, 2.3e-6 and 4.88 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
+// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 102 ms at 1.7e-6 (200 x 200
+// adjoint: 8.05 ms, 2.3e-6 and 4.46 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
 // the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
 struct OpF32 {
   using In = float;
@@ -380,7 +380,7 @@ struct OpF32 {
   static constexpr int kVec = 4;   // entries of a staged vector
   static constexpr int kCol = kRingF32.col_bytes;
   static constexpr int kVecs = kRingF32.CH / kVec;  // staged vectors per column
-  static constexpr int kTiles = 4;                  // position tiles per phase
+  static constexpr int kTiles = 2;                  // position tiles per phase
   static constexpr int kPlane = 2 * kRingF32.CH;    // LDS bytes of one part of a column
   struct A {
     u32x4 v[3];
@@ -438,7 +438,7 @@ struct OpF32 {
 };
 
 // FP64 on v_mfma_f64_16x16x4_f64: entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
-// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.69 ms; with positions read from
+// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.56 ms; with positions read from
 // global memory it took 3.42 ms (bound by the texture path), with one FMA per load 68.4 ms.
 struct OpF64 {
   using In = double;
@@ -448,7 +448,7 @@ struct OpF64 {
   static constexpr int kVec = 2;
   static constexpr int kCol = kRingF64.col_bytes;
   static constexpr int kVecs = kRingF64.CH / kVec;
-  static constexpr int kTiles = 4;
+  static constexpr int kTiles = 2;
   struct A {
     doublex4 v;
   };
@@ -528,8 +528,17 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
   return r;
 }
 
+// The bundle loop is a pipeline of phases of kTiles position tiles: the fragments of a phase are
+// read from the LDS while the phase before multiplies, the LDS offset of a bundle is loaded two
+// bundles ahead and its table fragments between one and two.  Left to the compiler, which
+// issued each read next to its use, the 400 x 400 FP32 forward took 114 ms (MFMA busy 0.61,
+// waves waiting 0.46 of their time); phases of four tiles take 105 ms, of two 104.6, and of
+// two within 168 registers (three waves per SIMD where the LDS allows) 102 ms and, for the 200 x
+// 200 adjoint, 4.46 ms instead of 4.71.  At that issue rate (1.4 PFLOP/s of BF16, a large library
+// product reaches 1.1) the chip lowers its clock from 2.1 to 1.7-1.8 GHz: what is left is power,
+// spent on the table stream (L2 and beyond) and on the zeros of the tiles besides the products.
 template <class Op, int BR, int BC, int W, int P, bool RAGGED>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void k_apply_ring(
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void k_apply_ring(
     const void* __restrict__ pack, const typename Op::In* __restrict__ in,
     typename Op::In* __restrict__ out, RingArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -542,7 +551,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
   constexpr int PH = NT / XT;
   constexpr int RPP = XT / TPR;   // patch rows per phase
   constexpr int RS = BR + 1;
-  constexpr int PF = 2, PD = 2;   // staged vectors, bundles in flight
+  constexpr int PF = 2;           // staged vectors in flight per thread
   constexpr int TH = 64 * W;
   static_assert(W % P == 0 && BR % P == 0 && NT % XT == 0 && XT % TPR == 0 && NT % S == 0, "shape");
   const int4 piece = a.pieces[blockIdx.y];
@@ -556,6 +565,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = Acc{0, 0, 0, 0};
 
+  struct Bundle {
+    typename Op::A a;
+    int mo;
+  };
   RingFetch<Op, PF> f;
   // the rows unit U adds: padded patch rows [lo, U.x + K + BR) of its chunk
   auto fetch = [&](const int4& U, int lo) {
@@ -594,76 +607,80 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
 
   const int u0 = piece.y, u1 = piece.z;
   if (u0 < u1) {
-    typename Op::A ring[PD];
-    int mo[PD];
-    auto refill = [&](int j, int b) {
-      Op::load_a(pack, b, lane, ring[j]);
-      mo[j] = a.meta[b * kLaneGroups + g];
-    };
-    // the bundles of unit U for this wave, the tiles of the first NTC tile columns
-    auto bundles = [&](const int4& U, const int (&rb)[RW], unsigned live, auto ntc) {
-      constexpr int NTC = decltype(ntc)::value;
-      constexpr int NX = RPP * NTC;
-      for (int b0 = U.z + sw; b0 < U.w; b0 += S * PD) {
-#pragma unroll
-        for (int j = 0; j < PD; ++j) {
-          const int b = b0 + S * j;
-          if (b < U.w) {
-#pragma unroll
-            for (int p = 0; p < PH; ++p) {
-              if (!((live >> p) & 1)) continue;
-              typename Op::X x[NX];
-#pragma unroll
-              for (int t = 0; t < NX; ++t)
-                x[t] = Op::read_x(lds + (rb[p * RPP + t / NTC] + mo[j]) + (t % NTC) * 16 * Op::kCol);
-              Op::template mma<NX, TPR / NTC>(ring[j], x, acc + p * XT);
-            }
-          }
-          refill(j, min(b + S * PD, U.w - 1));
-        }
-      }
-    };
+    // Table fragments: two bundles of the unit (r0, r1), and the first of the next one (n0), whose
+    // loads are issued when the unit starts.
+    Bundle r0, r1, n0;
+    auto load_mo = [&](Bundle& r, int b) { r.mo = a.meta[b * kLaneGroups + g]; };
+    auto load_a = [&](Bundle& r, int b) { Op::load_a(pack, b, lane, r.a); };
     int4 U = a.units[u0];
-#pragma unroll
-    for (int j = 0; j < PD; ++j) refill(j, min(U.z + sw + S * j, U.w - 1));
+    load_mo(n0, min(U.z + sw, U.w - 1));
+    load_a(n0, min(U.z + sw, U.w - 1));
     fetch(U, U.x + a.K);
     stage(U, U.x + a.K);
     __syncthreads();
-    int4 Un = a.units[min(u0 + 1, u1 - 1)];
-    // rows the next unit finds in the ring: those of this unit, in the same chunk
-    int lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
-    if (u0 + 1 < u1) fetch(Un, lo);
     for (int u = u0; u < u1; ++u) {
-      // LDS base of this lane's position in each of the wave's rows, and the phases that have
-      // both an output row and an input row inside the scan
+      const int4 Un = a.units[min(u + 1, u1 - 1)];
+      // rows the next unit finds in the ring: those of this unit, in the same chunk
+      const int lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
+      r0 = n0;
+      load_mo(r1, min(U.z + sw + S, U.w - 1));
+      load_a(r1, min(U.z + sw + S, U.w - 1));
+      load_mo(n0, min(Un.z + sw, Un.w - 1));
+      load_a(n0, min(Un.z + sw, Un.w - 1));
+      fetch(Un, lo);
+      // LDS base of this lane's position in each of the wave's rows; a wave whose rows have no
+      // output row or no input row inside the scan skips the unit
       int rb[RW];
 #pragma unroll
       for (int r = 0; r < RW; ++r)
         rb[r] = (((grp * RW + r + U.x + a.K) % RS) * a.NCOL + n) * Op::kCol;
-      unsigned live = 0;
+      const int o = py0 + grp * RW, i0 = o + U.x;
+      const bool live = o < a.ny && i0 + RW > 0 && i0 < a.ny;
+      auto read = [&](auto ntc, int p, int mo, auto& x) {
+        constexpr int NTC = decltype(ntc)::value;
 #pragma unroll
-      for (int p = 0; p < PH; ++p) {
-        const int o = py0 + grp * RW + p * RPP, i = o + U.x;
-        live |= o < a.ny && i + RPP > 0 && i < a.ny ? 1u << p : 0u;
-      }
-      if (live) {
-        if (px0 + 16 >= a.nx)  // the patch's second tile column lies outside the scan
-          bundles(U, rb, live, std::integral_constant<int, 1>{});
-        else
-          bundles(U, rb, live, std::integral_constant<int, TPR>{});
-      }
+        for (int t = 0; t < RPP * NTC; ++t)
+          x[t] = Op::read_x(lds + (rb[p * RPP + t / NTC] + mo) + (t % NTC) * 16 * Op::kCol);
+      };
+      // The wave's bundles for the tiles of the first NTC tile columns, all PH phases: the
+      // position fragments of a phase are read while the phase before multiplies (the barriers
+      // keep the compiler from moving the reads next to their use).
+      auto all = [&](auto ntc) {
+        constexpr int NTC = decltype(ntc)::value, NX = RPP * NTC;
+        typename Op::X x[2][NX];
+        auto body = [&](Bundle& r, const int& mo_next, int b) {
+#pragma unroll
+          for (int p = 0; p < PH; ++p) {
+            read(ntc, (p + 1) % PH, p + 1 < PH ? r.mo : mo_next, x[(p + 1) % 2]);
+            if (p + 2 == PH) load_mo(r, min(b + 2 * S, U.w - 1));
+            __builtin_amdgcn_sched_barrier(0);
+            Op::template mma<NX, TPR / NTC>(r.a, x[p % 2], acc + p * XT);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          load_a(r, min(b + 2 * S, U.w - 1));
+        };
+        static_assert(PH % 2 == 0, "a bundle's first phase is in x[0]");
+        int b = U.z + sw;
+        if (b >= U.w) return;
+        read(ntc, 0, r0.mo, x[0]);
+        for (; b + S < U.w; b += 2 * S) {
+          body(r0, r1.mo, b);
+          body(r1, r0.mo, b + S);
+        }
+        if (b < U.w) body(r0, r1.mo, b);
+      };
+      if (!live) {
+      } else if (px0 + 16 >= a.nx)  // the patch's second tile column lies outside the scan
+        all(std::integral_constant<int, 1>{});
+      else
+        all(std::integral_constant<int, TPR>{});
       if (u + 1 < u1) {
-#pragma unroll
-        for (int j = 0; j < PD; ++j) refill(j, min(Un.z + sw + S * j, Un.w - 1));
         // one new row right after this unit's rows goes to the free slot while other waves
         // still read this unit
         if (!(Un.x == U.x + 1 && Un.y == U.y)) __syncthreads();
         stage(Un, lo);
         __syncthreads();
         U = Un;
-        Un = a.units[min(u + 2, u1 - 1)];
-        lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
-        if (u + 2 < u1) fetch(Un, lo);
       }
     }
   }

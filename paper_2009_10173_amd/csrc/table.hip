@@ -729,14 +729,13 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
   lay.n_units = (long long)units.size();
   lay.n_bundles = (long long)groups.size() / kLaneGroups;
   // MACs the kernel issues: per bundle 16 rows x 4 G entries for every computed position, which
-  // leaves out row pairs of a patch that have no output or input row inside the scan and the
-  // second 16-position tile column of a patch that holds at most 16 scan columns
+  // leaves out patches that have no input row inside the scan and the second 16-position tile column of a patch that holds at most 16 scan columns
   const long long cols = g.nx % BC > 0 && g.nx % BC <= 16 ? (long long)(g.nx / BC) * BC + 16
                                                           : round_up(g.nx, BC);
   lay.mac_exec = 0;
   for (const int4& u : units) {
     long long rows = 0;
-    for (int o = 0; o < g.ny; o += 2) rows += o + u.x + 2 > 0 && o + u.x < g.ny ? 2 : 0;
+    for (int o = 0; o < g.ny; o += BR) rows += o + u.x + BR > 0 && o + u.x < g.ny ? BR : 0;
     lay.mac_exec += (u.w - u.z) * rows;
   }
   lay.mac_exec *= (long long)kLaneGroups * rs.G * TM * cols;
