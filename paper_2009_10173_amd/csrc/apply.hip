@@ -737,7 +737,16 @@ __global__ __launch_bounds__(256) void k_add_slots(const int2* __restrict__ tile
     const int py = py0 + pos / BC, px = px0 + pos % BC;
     if (py >= ny || px >= nx || row >= out_len) continue;
     T4 v = base[e];
-    for (int j = 1; j < sp.x; ++j) v += base[j * stride + e];
+    int j = 1;
+    for (; j + 3 < sp.x; j += 4) {  // four loads in flight
+      const T4 a = base[j * stride + e], b = base[(j + 1) * stride + e],
+               c = base[(j + 2) * stride + e], d = base[(j + 3) * stride + e];
+      v += a;
+      v += b;
+      v += c;
+      v += d;
+    }
+    for (; j < sp.x; ++j) v += base[j * stride + e];
     T* o = out + ((long long)py * nx + px) * out_len + row;
 #pragma unroll
     for (int i = 0; i < 4; ++i)

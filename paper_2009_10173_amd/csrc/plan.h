@@ -24,6 +24,13 @@ struct PlanPiece {
   double work;
 };
 
+// Costs besides the units', in units of work.
+struct PlanCosts {
+  double workgroup = 1.0;  // start and end of a workgroup
+  double add = 0.0;        // the launch that adds the slots of cut tiles
+  double add_slot = 0.0;   // and each slot of its most cut tile
+};
+
 struct LaunchPlan {
   std::vector<PlanPiece> pieces;     // in dispatch order
   std::vector<int> tile_pieces;      // [tile] pieces of the tile
@@ -38,6 +45,8 @@ struct LaunchPlan {
 // Finishing time of a launch whose workgroups (every patch of each piece, pieces in the given
 // order) take the first of `slots` free places and last as long as their work.
 inline double simulate_launch(const std::vector<double>& piece_work, int n_patches, int slots) {
+  if ((double)piece_work.size() * n_patches <= slots)  // every workgroup has a place at once
+    return piece_work.empty() ? 0.0 : *std::max_element(piece_work.begin(), piece_work.end());
   std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
   for (int i = 0; i < slots; ++i) free_at.push(0.0);
   double end = 0;
@@ -52,18 +61,20 @@ inline double simulate_launch(const std::vector<double>& piece_work, int n_patch
 }
 
 // Plan a launch.  tile_units[t] .. tile_units[t + 1] are tile t's units; chunk_starts[t]
-// lists the units of tile t where a chunk starts (the first is tile_units[t] when the tile
-// has units); unit_work[u] is unit u's work.  For D = 1 .. 8 every tile is cut into about
-// (its work) / (largest tile work / D) pieces of similar work, each cut at the chunk start
+// lists the units of tile t where a piece may start (the first is tile_units[t] when the tile
+// has units); unit_work[u] is unit u's work.  For D = 1 .. max_cut (in steps of a quarter from 8
+// on) every tile is cut into about
+// (its work) / (largest tile work / D) pieces of similar work, each cut at the start
 // whose prefix work is nearest to its share, and the pieces are dispatched in tile order or
 // heaviest first, whichever the simulation (`slots` places, one workgroup per piece and
-// patch, one unit of work added per workgroup for its fixed costs) finishes sooner.  A cut
+// patch, costs.workgroup added to each for its fixed costs and, for a cut, those of adding slots) finishes sooner.  A cut
 // is taken only when `allow_cut`, when it shortens the simulated launch by more than 10 %,
 // and when its slots (slot_bytes per piece and patch) fit in max_slot_bytes.
 inline LaunchPlan plan_launch(const std::vector<int>& tile_units,
                               const std::vector<std::vector<int>>& chunk_starts,
                               const std::vector<double>& unit_work, int n_patches, int slots,
-                              bool allow_cut, double slot_bytes, double max_slot_bytes) {
+                              bool allow_cut, double slot_bytes, double max_slot_bytes,
+                              int max_cut = 8, const PlanCosts& costs = PlanCosts()) {
   const int nT = (int)tile_units.size() - 1;
   std::vector<double> prefix(unit_work.size() + 1, 0.0);
   for (size_t u = 0; u < unit_work.size(); ++u) prefix[u + 1] = prefix[u] + unit_work[u];
@@ -100,13 +111,13 @@ inline LaunchPlan plan_launch(const std::vector<int>& tile_units,
   };
   auto launch_time = [&](const std::vector<PlanPiece>& order) {
     std::vector<double> w;
-    for (const PlanPiece& p : order) w.push_back(p.work + 1.0);
+    for (const PlanPiece& p : order) w.push_back(p.work + costs.workgroup);
     return simulate_launch(w, n_patches, slots);
   };
   LaunchPlan best;
   std::vector<PlanPiece> cur;
   std::vector<int> cur_np;
-  for (int D = 1; D <= (allow_cut ? 8 : 1); ++D) {
+  for (int D = 1; D <= (allow_cut ? max_cut : 1); D += std::max(1, D / 4)) {
     cut(D, cur, cur_np);
     long long nslots = 0;
     for (int t = 0; t < nT; ++t) nslots += cur_np[t] > 1 ? cur_np[t] : 0;
@@ -115,7 +126,13 @@ inline LaunchPlan plan_launch(const std::vector<int>& tile_units,
     std::stable_sort(heavy.begin(), heavy.end(),
                      [](const PlanPiece& x, const PlanPiece& y) { return x.work > y.work; });
     double time = launch_time(cur);
-    const double time_heavy = launch_time(heavy);
+    double time_heavy = launch_time(heavy);
+    if (nslots > 0) {
+      const double add =
+          costs.add + costs.add_slot * *std::max_element(cur_np.begin(), cur_np.end());
+      time += add;
+      time_heavy += add;
+    }
     const bool hf = time_heavy <= time;
     if (hf) {
       time = time_heavy;
@@ -128,6 +145,8 @@ inline LaunchPlan plan_launch(const std::vector<int>& tile_units,
       best.cut = D;
       best.heaviest_first = hf;
       best.time = time;
+    } else if (D > 8 && time > 1.05 * best.time) {
+      break;  // finer cuts only add workgroups and slots from here on
     }
   }
   // slots: consecutive per cut tile, in unit order

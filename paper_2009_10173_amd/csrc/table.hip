@@ -542,10 +542,11 @@ std::vector<UnitEntry> order_unit(const std::vector<UnitEntry>& in, int maxcol, 
 int plan_pieces(Layout& lay, const std::vector<int>& tile_units,
                 const std::vector<std::vector<int>>& chunk_starts,
                 const std::vector<double>& unit_work, int slots, size_t& bytes,
-                size_t esize = sizeof(float), double max_slots = (double)(1ll << 30)) {
+                size_t esize = sizeof(float), double max_slots = (double)(1ll << 30),
+                int max_cut = 8, const PlanCosts& costs = PlanCosts()) {
   const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * esize;
   const LaunchPlan plan = plan_launch(tile_units, chunk_starts, unit_work, lay.n_patches, slots,
-                                      /*allow_cut=*/true, slot_bytes, max_slots);
+                                      /*allow_cut=*/true, slot_bytes, max_slots, max_cut, costs);
   std::vector<int4> pieces;
   for (const PlanPiece& p : plan.pieces) pieces.push_back(make_int4(p.tile, p.u0, p.u1, p.slot));
   std::vector<int2> split(lay.n_tiles);
@@ -669,6 +670,14 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   return plan_pieces(lay, tile_units, chunk_starts, unit_work, 3 * std::max(cus, 1), bytes);
 }
 
+// Costs of a ring launch in bundles (of the 128 positions of a patch, about 0.1 us): a unit's
+// staging and barrier, a workgroup's first and last accesses, the slot sums.  Where few
+// workgroups run, these are what a finer cut has to pay for; measured on the 40 x 40 FISTA
+// (1.13 -> 0.80 ms a pair of applies with them, 1.02 with none), the 64 x 64 FP32 forward (177 ->
+// 162 us, 177 with none) and the 23 x 19 FP64 one (75 -> 51 us, 56 with none).
+constexpr double kUnitWork = 8;
+constexpr PlanCosts kRingCosts{24, 40, 2};
+
 // LDS-ring form (FP64, FP32; see Layout and RingShape): tiles of 16 rows, stage units as above,
 // no masks (every bundle reaches its tile).  `pad` is the geometry of the zero-padded input,
 // which bounds the partial slots.
@@ -722,7 +731,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
         }
         cuts[t].push_back((int)units.size());
         units.push_back(make_int4(R - K, c * rs.CH, first, (int)(groups.size() / kLaneGroups)));
-        unit_work.push_back(units.back().w - units.back().z);
+        unit_work.push_back(units.back().w - units.back().z + kUnitWork);
       }
   }
   tile_units[lay.n_tiles] = (int)units.size();
@@ -748,7 +757,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
   int cus = 0;
   AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
   return plan_pieces(lay, tile_units, cuts, unit_work, 3 * std::max(cus, 1), bytes, esize,
-                     std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)));
+                     std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64, kRingCosts);
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
