@@ -9,7 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <vector>
+#include <utility>
 
 #include "internal.h"
 
@@ -21,18 +21,33 @@ constexpr int kRedBlocks = 1024;
 constexpr int kRedThreads = 256;
 
 // ------------------------------------------------------------------------------------------
-// Deterministic FP64 reductions: each of kRedBlocks blocks sums a fixed strided subset in
-// FP64 and writes one partial; a single block then sums the partials in a fixed order.
+// Deterministic FP64 reductions: each of red_blocks(n) blocks sums a fixed strided subset in
+// FP64 and writes one partial.  The partials are added in a fixed order, by a kernel of one
+// block (k_final) or by every block of the kernel that uses the sum (total): at most 8 KB
+// from the L2, which is cheaper than two launches in between (a small one takes 3 to 5 us).
 
+// Sum over the block's kRedThreads threads, the same in every thread.
 __device__ inline double block_sum(double v, double* sh) {
-  sh[threadIdx.x] = v;
+  for (int s = 1; s < 64; s <<= 1) v += __shfl_xor(v, s);
+  if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = v;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
+  double r = sh[0];
+  for (int w = 1; w < kRedThreads / 64; ++w) r += sh[w];
+  __syncthreads();
+  return r;
+}
+
+// Sum of n partials (and n2 of a second set, if given), the same in every thread of every block.
+__device__ inline double total(const double* __restrict__ part, int n,
+                               const double* __restrict__ part2, int n2, double* sh) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += kRedThreads) v += part[i];
+  double r = block_sum(v, sh);
+  if (part2) {
+    v = 0.0;
+    for (int i = threadIdx.x; i < n2; i += kRedThreads) v += part2[i];
+    r += block_sum(v, sh);
   }
-  const double r = sh[0];
-  __syncthreads();
   return r;
 }
 
@@ -80,20 +95,39 @@ __global__ __launch_bounds__(kRedThreads) void k_amax_partial(const T* __restric
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// out = sum(part0) (+ sum(part1) if given), or the maximum when is_max.
-__global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict__ part0,
-                                                       const double* __restrict__ part1,
-                                                       int nparts, bool is_max,
-                                                       double* __restrict__ out) {
+// part0[b] = sum of a[i] * b[i], part1[b] = sum of b[i]^2 over this block's elements.
+template <typename T>
+__global__ __launch_bounds__(kRedThreads) void k_dot_sq_partial(const T* __restrict__ a,
+                                                                const T* __restrict__ b,
+                                                                long long n,
+                                                                double* __restrict__ part0,
+                                                                double* __restrict__ part1) {
   __shared__ double sh[kRedThreads];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x)
-    acc = is_max ? nan_max(acc, part0[i]) : acc + part0[i];
-  double r = is_max ? block_max(acc, sh) : block_sum(acc, sh);
-  if (part1) {
-    double acc1 = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) acc1 += part1[i];
-    r += block_sum(acc1, sh);
+  double ab = 0.0, bb = 0.0;
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
+    const double x = (double)a[i], y = (double)b[i];
+    ab += x * y;
+    bb += y * y;
+  }
+  const double s0 = block_sum(ab, sh), s1 = block_sum(bb, sh);
+  if (threadIdx.x == 0) {
+    part0[blockIdx.x] = s0;
+    part1[blockIdx.x] = s1;
+  }
+}
+
+// out = sum(part), or the maximum when is_max.
+__global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict__ part, int nparts,
+                                                       bool is_max, double* __restrict__ out) {
+  __shared__ double sh[kRedThreads];
+  double r;
+  if (is_max) {
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += blockDim.x) acc = nan_max(acc, part[i]);
+    r = block_max(acc, sh);
+  } else {
+    r = total(part, nparts, nullptr, 0, sh);
   }
   if (threadIdx.x == 0) *out = r;
 }
@@ -101,6 +135,12 @@ __global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict_
 // ------------------------------------------------------------------------------------------
 // LSQR state on the device.  Stored vectors carry scales: u = su * u_st, v = sv * v_st, so a
 // normalisation costs no extra pass; w and x are stored explicitly.
+//
+// The scalars of a half step are computed by every block of the kernel that needs them first,
+// from the partial sums of the kernel before: beta in k_lsqr_v, alpha and the rotations in
+// k_lsqr_xw.  Block 0 stores them for later kernels.  k_lsqr_v stores only fields that its
+// other blocks do not read; k_lsqr_xw reads one copy of the state and stores the other, so an
+// iteration is the two applies and three kernels.
 struct LsqrDev {
   double alpha, beta, su, sv;
   double rhobar, phibar;
@@ -172,16 +212,30 @@ __global__ __launch_bounds__(kRedThreads) void k_lsqr_u(const T* __restrict__ t,
   }
 }
 
-// v_st <- su * (t + gamma * u2_st) - beta * sv * v_st  (init: b = 0)
+// beta = ||u|| from the partial sums of u (and of the stacked block), su = 1 / beta (u is left
+// unscaled when beta = 0), then v_st <- su * (t + gamma * u2_st) - beta * sv * v_st (init: the
+// last term is left out).
 template <typename T>
 __global__ __launch_bounds__(kRedThreads) void k_lsqr_v(const T* __restrict__ t,
                                                         const T* __restrict__ u2,
                                                         T* __restrict__ v, long long n, int init,
-                                                        const LsqrDev* __restrict__ d,
+                                                        LsqrDev* d,
+                                                        const double* __restrict__ pu, int nu,
+                                                        const double* __restrict__ pu2, int nu2,
                                                         double* __restrict__ part) {
   __shared__ double sh[kRedThreads];
   if (stop(d)) return;
-  const double a = d->su, b = init ? 0.0 : -d->beta * d->sv, g = d->gamma;
+  const double beta = sqrt(total(pu, nu, pu2, nu2, sh));
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (!isfinite(beta)) {
+    if (first) lsqr_fail(d, d->iter);
+    return;
+  }
+  const double a = beta > 0 ? 1.0 / beta : 1.0, b = init ? 0.0 : -beta * d->sv, g = d->gamma;
+  if (first) {
+    d->beta = beta;
+    d->su = a;
+  }
   const long long stride = (long long)gridDim.x * blockDim.x;
   double acc = 0.0;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -195,75 +249,64 @@ __global__ __launch_bounds__(kRedThreads) void k_lsqr_v(const T* __restrict__ t,
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// beta = ||u||, su = 1 / beta (u is left unscaled when beta = 0).
-__global__ void k_lsqr_beta(LsqrDev* d) {
-  if (stop(d)) return;
-  const double b = sqrt(d->red);
-  if (!isfinite(b)) {
-    lsqr_fail(d, d->iter);
-    return;
-  }
-  d->beta = b;
-  d->su = b > 0 ? 1.0 / b : 1.0;
-}
-
-// Initial alpha (after v = A^T u) and the LSQR start values.
-__global__ void k_lsqr_init_alpha(LsqrDev* d, int lambda_rule) {
-  if (stop(d)) return;
-  const double a = sqrt(d->red);
-  if (!isfinite(a)) {
-    lsqr_fail(d, 0);
-    return;
-  }
-  d->alpha = a;
-  d->sv = a > 0 ? 1.0 / a : 1.0;
+// Initial alpha = ||v|| (after v = A^T u) and the LSQR start values.
+__device__ inline void lsqr_start(LsqrDev& d, double a, int lambda_rule) {
+  d.alpha = a;
+  d.sv = a > 0 ? 1.0 / a : 1.0;
   if (lambda_rule) {  // Tikhonov default: 1e-2 ||A^T s||_2, with ||A^T s|| = alpha beta
-    d->lambda = 1e-2 * a * d->beta;
-    d->damp = sqrt(d->lambda);
+    d.lambda = 1e-2 * a * d.beta;
+    d.damp = sqrt(d.lambda);
   }
-  d->phibar = d->beta;
-  d->rhobar = a;
-  d->xc = 0.0;
-  d->wc = 0.0;
-  if (a * d->beta == 0.0) d->done = 1;
+  d.phibar = d.beta;
+  d.rhobar = a;
+  d.xc = 0.0;
+  d.wc = 0.0;
+  if (a * d.beta == 0.0) d.done = 1;
 }
 
 // alpha = ||v||, then the two plane rotations of LSQR (damping row, then beta).
-__global__ void k_lsqr_rotate(LsqrDev* d) {
-  if (stop(d)) return;
-  const double a = sqrt(d->red);
-  if (!isfinite(a)) {
-    lsqr_fail(d, d->iter);
-    return;
-  }
-  d->alpha = a;
-  d->sv = a > 0 ? 1.0 / a : 1.0;
-  const double beta = d->beta;
-  const double rhobar1 = sqrt(d->rhobar * d->rhobar + d->damp * d->damp);
+__device__ inline void lsqr_rotate(LsqrDev& d, double a) {
+  d.alpha = a;
+  d.sv = a > 0 ? 1.0 / a : 1.0;
+  const double beta = d.beta;
+  const double rhobar1 = sqrt(d.rhobar * d.rhobar + d.damp * d.damp);
   if (rhobar1 == 0.0 || rhobar1 * rhobar1 + beta * beta == 0.0) {
-    d->done = 1;  // exact breakdown: x is final
+    d.done = 1;  // exact breakdown: x is final
     return;
   }
-  const double cs1 = d->rhobar / rhobar1;
-  double phibar = cs1 * d->phibar;
+  const double cs1 = d.rhobar / rhobar1;
+  double phibar = cs1 * d.phibar;
   const double rho = sqrt(rhobar1 * rhobar1 + beta * beta);
   const double cs = rhobar1 / rho, sn = beta / rho;
   const double theta = sn * a;
-  d->rhobar = -cs * a;
+  d.rhobar = -cs * a;
   const double phi = cs * phibar;
-  d->phibar = sn * phibar;
-  d->xc = phi / rho;
-  d->wc = theta / rho;
-  d->iter += 1;
+  d.phibar = sn * phibar;
+  d.xc = phi / rho;
+  d.wc = theta / rho;
+  d.iter += 1;
 }
 
-// x += xc w;  w = sv v_st - wc w   (init: w = sv v_st, x = 0)
+// alpha from the partial sums of v and the rotations, then x += xc w; w = sv v_st - wc w
+// (init: the start values, w = sv v_st, x = 0).  The new state goes to *next.
 template <typename T>
-__global__ __launch_bounds__(256) void k_lsqr_xw(T* __restrict__ x, T* __restrict__ w,
-                                                 const T* __restrict__ v, long long n, int init,
-                                                 const LsqrDev* __restrict__ d) {
-  if (stop(d) && !init) return;
-  const double xc = d->xc, wc = d->wc, sv = d->sv;
+__global__ __launch_bounds__(kRedThreads) void k_lsqr_xw(T* __restrict__ x, T* __restrict__ w,
+                                                         const T* __restrict__ v, long long n,
+                                                         int init, int lambda_rule,
+                                                         const LsqrDev* __restrict__ d,
+                                                         LsqrDev* __restrict__ next,
+                                                         const double* __restrict__ pv, int nv) {
+  __shared__ double sh[kRedThreads];
+  LsqrDev h = *d;
+  const double alpha = sqrt(total(pv, nv, nullptr, 0, sh));
+  if (!stop(&h)) {
+    if (!isfinite(alpha)) lsqr_fail(&h, init ? 0 : h.iter);
+    else if (init) lsqr_start(h, alpha, lambda_rule);
+    else lsqr_rotate(h, alpha);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next = h;
+  if (stop(&h) && !init) return;
+  const double xc = h.xc, wc = h.wc, sv = h.sv;
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
     if (init) {
@@ -304,7 +347,7 @@ __global__ void k_scale_dev(T* __restrict__ y, const T* __restrict__ a, const do
 }
 
 struct FistaDev {
-  double L, lambda, rq, ww, vv, inv, amax, ss;
+  double L, lambda, rq, ww, inv, amax, ss;
   int bad;       // a non-finite value was met (sticky: later kernels do nothing)
   int bad_iter;  // FISTA iterations completed before it (0 in the power method / parameters)
 };
@@ -314,12 +357,25 @@ __global__ void k_fista_reset(FistaDev* f) {
   *f = h;
 }
 
-// Power method bookkeeping: rq = <v, w>, inv = 1 / ||w||.
-__global__ void k_power_scalars(FistaDev* f) {
-  f->rq = f->vv;
-  const double nw = sqrt(f->ww);
-  f->inv = nw > 0 ? 1.0 / nw : 0.0;
-  if (!isfinite(nw) || !isfinite(f->vv)) f->bad = 1;
+// A power-method step from the partial sums of <v, w> and <w, w>: rq = <v, w>, y = w / ||w||.
+template <typename T>
+__global__ __launch_bounds__(kRedThreads) void k_power_step(T* __restrict__ y,
+                                                            const T* __restrict__ w, long long n,
+                                                            FistaDev* f,
+                                                            const double* __restrict__ pvw,
+                                                            const double* __restrict__ pww,
+                                                            int nparts) {
+  __shared__ double sh[kRedThreads];
+  const double vw = total(pvw, nparts, nullptr, 0, sh);
+  const double nw = sqrt(total(pww, nparts, nullptr, 0, sh));
+  const double inv = nw > 0 ? 1.0 / nw : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    f->rq = vw;
+    if (!isfinite(nw) || !isfinite(vw)) f->bad = 1;
+  }
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride)
+    y[i] = (T)(inv * (double)w[i]);
 }
 
 // The signals enter FISTA only through A^T (A y - s), which reads the samples the model's
@@ -378,6 +434,10 @@ __global__ __launch_bounds__(256) void k_fista_step(T* __restrict__ y, T* __rest
 // finish() synchronises once.  The blocking entry points run create + step(all) + finish;
 // the request scheduler interleaves the steps of many solvers on separate streams.
 
+int red_blocks(long long n) {
+  return (int)std::max<long long>(1, std::min<long long>(ceil_div(n, 2 * kRedThreads), kRedBlocks));
+}
+
 int grid_for(long long n) { return (int)std::max<long long>(1, std::min<long long>(ceil_div(n, 256), 4096)); }
 
 int check_dtype(const Model& m, int dt) {
@@ -398,7 +458,7 @@ class SolverT final : public Solver {
     nx_ = (long long)m.grid.ny * m.grid.nx * m.grid.nz;
   }
   ~SolverT() override {
-    for (void* p : allocs_) (void)hipFreeAsync(p, stream);
+    if (arena_) (void)hipFreeAsync(arena_, stream);
   }
 
   // Device bytes the solver allocates (stage buffers, reductions, state, vectors).
@@ -407,7 +467,7 @@ class SolverT final : public Solver {
     const long long nx = (long long)m.grid.ny * m.grid.nx * m.grid.nz;
     size_t b = std::max(stage_bytes(m, false, o.inner), stage_bytes(m, false, o.outer)) +
                std::max(stage_bytes(m, true, o.inner), stage_bytes(m, true, o.outer)) +
-               2 * vec_bytes(kRedBlocks, 8) + 2 * vec_bytes(1, 512);
+               3 * vec_bytes(kRedBlocks, 8) + 2 * vec_bytes(1, 512);
     const size_t e = sizeof(T);
     if (kind == 0) {
       b += 2 * vec_bytes(ns, e) + 3 * vec_bytes(nx, e);  // u, ts; v, w, tx
@@ -425,12 +485,15 @@ class SolverT final : public Solver {
     AROAM_CHECK(s_ && x_, AROAM_EINVAL, "NULL vector");
     AROAM_CHECK(o_.iters >= 0 && o_.refine_sweeps >= 0 && o_.power_iters >= 0, AROAM_EINVAL,
                 "negative iteration count");
+    size_ = footprint(m_, kind_, o_);
+    AROAM_TRY(pool_alloc((void**)&arena_, size_, stream));
     AROAM_TRY(alloc_bytes(&stage_f_, std::max(stage_bytes(m_, false, o_.inner),
                                               stage_bytes(m_, false, o_.outer))));
     AROAM_TRY(alloc_bytes(&stage_a_, std::max(stage_bytes(m_, true, o_.inner),
                                               stage_bytes(m_, true, o_.outer))));
     AROAM_TRY(alloc_bytes((void**)&part0_, kRedBlocks * sizeof(double)));
-    AROAM_TRY(alloc_bytes((void**)&part1_, kRedBlocks * sizeof(double)));
+    AROAM_TRY(alloc_bytes((void**)&part1_, 2 * kRedBlocks * sizeof(double)));
+    partv_ = part1_ + kRedBlocks;
     return kind_ == 0 ? create_lsqr() : create_l1();
   }
 
@@ -446,12 +509,13 @@ class SolverT final : public Solver {
   const T* s_;
   T* x_;
   long long ns_ = 0, nx_ = 0;
-  std::vector<void*> allocs_;
+  char* arena_ = nullptr;  // one allocation of footprint() bytes, handed out by alloc_bytes
+  size_t used_ = 0, size_ = 0;
   void *stage_f_ = nullptr, *stage_a_ = nullptr;
-  double *part0_ = nullptr, *part1_ = nullptr;
+  double *part0_ = nullptr, *part1_ = nullptr, *partv_ = nullptr;
   long long total_ = 0, enqueued_ = 0;
   // LSQR
-  LsqrDev* d_ = nullptr;
+  LsqrDev *d_ = nullptr, *d_next_ = nullptr;  // the state and the copy the next kernel stores
   T *u_ = nullptr, *ts_ = nullptr, *v_ = nullptr, *w_ = nullptr, *tx_ = nullptr, *u2_ = nullptr;
   T *rs_ = nullptr, *gx_ = nullptr, *rx_ = nullptr, *dx_ = nullptr;
   int phase_ = 0, it_ = 0;  // LSQR phase: 0 main solve, k = correction solve of sweep k
@@ -463,8 +527,10 @@ class SolverT final : public Solver {
   double t_ = 1.0;
 
   int alloc_bytes(void** p, size_t b) {
-    AROAM_TRY(pool_alloc(p, std::max<size_t>(1, b), stream));
-    allocs_.push_back(*p);
+    b = (size_t)round_up((long long)std::max<size_t>(1, b), 256);
+    AROAM_CHECK(used_ + b <= size_, AROAM_ENOMEM, "solver state exceeds its footprint");
+    *p = arena_ + used_;
+    used_ += b;
     return AROAM_OK;
   }
   int alloc(T** p, long long n) { return alloc_bytes((void**)p, vec_bytes(n, sizeof(T))); }
@@ -472,10 +538,10 @@ class SolverT final : public Solver {
   int adj(int dt, const T* in, T* out) { return apply(m_, true, dt, in, out, stage_a_, stream); }
 
   int reduce_sq(const T* a, long long n, double* out) {
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream, a,
+    const int nb = red_blocks(n);
+    hipLaunchKernelGGL(k_dot_partial<T>, dim3(nb), dim3(kRedThreads), 0, stream, a,
                        (const T*)nullptr, n, part0_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       (const double*)nullptr, kRedBlocks, false, out);
+    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_, nb, false, out);
     AROAM_HIP(hipGetLastError());
     return AROAM_OK;
   }
@@ -484,56 +550,48 @@ class SolverT final : public Solver {
   // Start one LSQR solve of min ||[b1; b2] - [A; gamma I] x||^2 + damp^2 ||x||^2 into xout
   // (b2 / gamma only for a correction solve of the refinement).
   int lsqr_init(const T* b1, const T* b2, T* xout, double damp, double gamma, int rule, int first) {
-    const int gx = grid_for(nx_);
     hipLaunchKernelGGL(k_lsqr_reset, dim3(1), dim3(1), 0, stream, d_, damp, b2 ? gamma : 0.0, first,
                        phase_ * o_.iters);
     AROAM_HIP(hipMemcpyAsync(u_, b1, ns_ * sizeof(T), hipMemcpyDeviceToDevice, stream));
     if (b2) AROAM_HIP(hipMemcpyAsync(u2_, b2, nx_ * sizeof(T), hipMemcpyDeviceToDevice, stream));
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
+    hipLaunchKernelGGL(k_dot_partial<T>, dim3(red_blocks(ns_)), dim3(kRedThreads), 0, stream,
                        (const T*)u_, (const T*)nullptr, ns_, part0_);
     if (b2)
-      hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
+      hipLaunchKernelGGL(k_dot_partial<T>, dim3(red_blocks(nx_)), dim3(kRedThreads), 0, stream,
                          (const T*)u2_, (const T*)nullptr, nx_, part1_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       b2 ? part1_ : (const double*)nullptr, kRedBlocks, false, &d_->red);
-    hipLaunchKernelGGL(k_lsqr_beta, dim3(1), dim3(1), 0, stream, d_);
+    return lsqr_half(b2 != nullptr, red_blocks(nx_), xout, 1, rule);
+  }
+
+  // v and alpha from u, then x and w: the second half of an iteration, or of the start.  The
+  // partial sums of u are in part0_ (and of the stacked block, nu2 of them, in part1_).
+  int lsqr_half(bool stacked, int nu2, T* xout, int init, int rule) {
     AROAM_TRY(adj(o_.inner, u_, tx_));
-    hipLaunchKernelGGL(k_lsqr_v<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
-                       (const T*)tx_, (const T*)(b2 ? u2_ : nullptr), v_, nx_, 1,
-                       (const LsqrDev*)d_, part0_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       (const double*)nullptr, kRedBlocks, false, &d_->red);
-    hipLaunchKernelGGL(k_lsqr_init_alpha, dim3(1), dim3(1), 0, stream, d_, rule);
-    hipLaunchKernelGGL(k_lsqr_xw<T>, dim3(gx), dim3(256), 0, stream, xout, w_, (const T*)v_,
-                       nx_, 1, (const LsqrDev*)d_);
+    const int nb = red_blocks(nx_);
+    hipLaunchKernelGGL(k_lsqr_v<T>, dim3(nb), dim3(kRedThreads), 0, stream, (const T*)tx_,
+                       (const T*)(stacked ? u2_ : nullptr), v_, nx_, init, d_,
+                       (const double*)part0_, red_blocks(ns_),
+                       (const double*)(stacked ? part1_ : nullptr), nu2, partv_);
+    // a large vector is bandwidth: more workgroups than the reductions' limit keep more in flight
+    const int gx = nx_ < (1ll << 20) ? nb : grid_for(nx_);
+    hipLaunchKernelGGL(k_lsqr_xw<T>, dim3(gx), dim3(kRedThreads), 0, stream, xout, w_,
+                       (const T*)v_, nx_, init, rule, (const LsqrDev*)d_, d_next_,
+                       (const double*)partv_, nb);
+    std::swap(d_, d_next_);
     AROAM_HIP(hipGetLastError());
     return AROAM_OK;
   }
 
   int lsqr_iter(bool stacked, T* xout) {
-    const int gx = grid_for(nx_);
     AROAM_TRY(fwd(o_.inner, v_, ts_));
-    hipLaunchKernelGGL(k_lsqr_u<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
+    hipLaunchKernelGGL(k_lsqr_u<T>, dim3(red_blocks(ns_)), dim3(kRedThreads), 0, stream,
                        (const T*)ts_, u_, ns_, (const T*)v_, stacked ? u2_ : (T*)nullptr, nx_,
                        (const LsqrDev*)d_, part0_, part1_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       stacked ? part1_ : (const double*)nullptr, kRedBlocks, false, &d_->red);
-    hipLaunchKernelGGL(k_lsqr_beta, dim3(1), dim3(1), 0, stream, d_);
-    AROAM_TRY(adj(o_.inner, u_, tx_));
-    hipLaunchKernelGGL(k_lsqr_v<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
-                       (const T*)tx_, (const T*)(stacked ? u2_ : nullptr), v_, nx_, 0,
-                       (const LsqrDev*)d_, part0_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       (const double*)nullptr, kRedBlocks, false, &d_->red);
-    hipLaunchKernelGGL(k_lsqr_rotate, dim3(1), dim3(1), 0, stream, d_);
-    hipLaunchKernelGGL(k_lsqr_xw<T>, dim3(gx), dim3(256), 0, stream, xout, w_, (const T*)v_,
-                       nx_, 0, (const LsqrDev*)d_);
-    AROAM_HIP(hipGetLastError());
-    return AROAM_OK;
+    return lsqr_half(stacked, red_blocks(ns_), xout, 0, 0);
   }
 
   int create_lsqr() {
-    AROAM_TRY(alloc_bytes((void**)&d_, sizeof(LsqrDev)));
+    AROAM_TRY(alloc_bytes((void**)&d_, 2 * sizeof(LsqrDev)));
+    d_next_ = d_ + 1;
     AROAM_TRY(alloc(&u_, ns_));
     AROAM_TRY(alloc(&ts_, ns_));
     AROAM_TRY(alloc(&v_, nx_));
@@ -672,10 +730,11 @@ class SolverT final : public Solver {
     const int rule = o_.lambda < 0;
     if (rule) {
       AROAM_TRY(adj(o_.outer, s_, tx_));
-      hipLaunchKernelGGL(k_amax_partial<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
+      const int nb = red_blocks(nx_);
+      hipLaunchKernelGGL(k_amax_partial<T>, dim3(nb), dim3(kRedThreads), 0, stream,
                          (const T*)tx_, nx_, part0_);
-      hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                         (const double*)nullptr, kRedBlocks, true, &f_->amax);
+      hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_, nb, true,
+                         &f_->amax);
     }
     hipLaunchKernelGGL(k_fista_params, dim3(1), dim3(1), 0, stream, f_, o_.lipschitz, o_.lambda, rule);
     AROAM_HIP(hipGetLastError());
@@ -683,17 +742,13 @@ class SolverT final : public Solver {
   }
 
   int power_iter() {
-    const int gx = grid_for(nx_);
+    const int nb = red_blocks(nx_);
     AROAM_TRY(fwd(o_.outer, v_, ts_));
     AROAM_TRY(adj(o_.outer, ts_, tx_));
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(kRedThreads), 0, stream,
-                       (const T*)v_, (const T*)tx_, nx_, part0_);
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, stream, part0_,
-                       (const double*)nullptr, kRedBlocks, false, &f_->vv);
-    AROAM_TRY(reduce_sq(tx_, nx_, &f_->ww));
-    hipLaunchKernelGGL(k_power_scalars, dim3(1), dim3(1), 0, stream, f_);
-    hipLaunchKernelGGL(k_scale_dev<T>, dim3(gx), dim3(256), 0, stream, v_, (const T*)tx_,
-                       (const double*)&f_->inv, nx_);
+    hipLaunchKernelGGL(k_dot_sq_partial<T>, dim3(nb), dim3(kRedThreads), 0, stream, (const T*)v_,
+                       (const T*)tx_, nx_, part0_, part1_);
+    hipLaunchKernelGGL(k_power_step<T>, dim3(nb), dim3(kRedThreads), 0, stream, v_, (const T*)tx_,
+                       nx_, f_, (const double*)part0_, (const double*)part1_, nb);
     AROAM_HIP(hipGetLastError());
     return AROAM_OK;
   }
