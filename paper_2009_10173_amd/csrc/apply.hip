@@ -122,15 +122,20 @@ __device__ __forceinline__ StageAddr stage_addr(const StagedArgs& a, int lo, int
   return r;
 }
 
-// Fetch up to 256 * PF stage vectors of unit u into registers (the rest is loaded when the
-// unit's rows are written); pf_off = -1 marks an unused slot.
+// Padded patch rows [lo, hi) that unit u loads; the first unit of a piece loads all it reads.
+__device__ __forceinline__ int2 unit_rows(const StagedArgs& a, int u, bool first) {
+  const int R = a.units[u].x + a.K;
+  return first ? make_int2(R, R + kPatchRows) : a.urows[u];
+}
+
+// Fetch up to 256 * PF stage vectors of unit u (rows Rr) into registers (the rest is loaded when
+// the unit's rows are written); pf_off = -1 marks an unused slot.
 template <typename T, int RS, int PF>
 __device__ __forceinline__ void stage_prefetch(const StagedArgs& a, const T* __restrict__ in,
-                                               int u, int py0, int px0, int rowvec, int nvec,
-                                               u32x4 (&pf)[PF], int (&pf_off)[PF]) {
+                                               int u, int2 Rr, int py0, int px0, int rowvec,
+                                               int nvec, u32x4 (&pf)[PF], int (&pf_off)[PF]) {
   constexpr int VEC = 16 / sizeof(T);
   const int4 U = a.units[u];
-  const int2 Rr = a.urows[u];
   const int nv = (Rr.y - Rr.x) * rowvec;
 #pragma unroll
   for (int i = 0; i < PF; ++i) {
@@ -148,14 +153,13 @@ __device__ __forceinline__ void stage_prefetch(const StagedArgs& a, const T* __r
 // ring reload) with four loads in flight per thread.
 template <typename T, int RS, int PF>
 __device__ __forceinline__ void stage_rows(const StagedArgs& a, const T* __restrict__ in, T* lds,
-                                           int u, int py0, int px0, int rowvec, int nvec,
+                                           int u, int2 Rr, int py0, int px0, int rowvec, int nvec,
                                            const u32x4 (&pf)[PF], const int (&pf_off)[PF]) {
   constexpr int VEC = 16 / sizeof(T);
 #pragma unroll
   for (int i = 0; i < PF; ++i)
     if (pf_off[i] >= 0) *reinterpret_cast<u32x4*>(lds + pf_off[i]) = pf[i];
   const int4 U = a.units[u];
-  const int2 Rr = a.urows[u];
   const int nv = (Rr.y - Rr.x) * rowvec;
   for (int base = 256 * PF; base < nv; base += 256 * 4) {
     u32x4 tmp[4];
@@ -257,11 +261,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int j = 0; j < PD; ++j)
         load_a<T, MH>(pack_raw, a.meta, min(U.z + sw + S * j, U.w - 1), g, n, ring[j]);
-      stage_prefetch<T, RS, PF>(a, in, u0, py0, px0, rowvec, nvec, pf, pf_off);
-      stage_rows<T, RS, PF>(a, in, lds, u0, py0, px0, rowvec, nvec, pf, pf_off);
+      const int2 rows = unit_rows(a, u0, true);
+      stage_prefetch<T, RS, PF>(a, in, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
+      stage_rows<T, RS, PF>(a, in, lds, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
       __syncthreads();
       if (u0 + 1 < u1)
-        stage_prefetch<T, RS, PF>(a, in, u0 + 1, py0, px0, rowvec, nvec, pf, pf_off);
+        stage_prefetch<T, RS, PF>(a, in, u0 + 1, unit_rows(a, u0 + 1, false), py0, px0, rowvec,
+                                    nvec, pf, pf_off);
     }
     for (int u = u0; u < u1; ++u) {
       const int4 U = a.units[u];
@@ -291,10 +297,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           load_a<T, MH>(pack_raw, a.meta, min(Un.z + sw + S * j, Un.w - 1), g, n, ring[j]);
         const bool free_slot = Rn.y - Rn.x == 1 && Rn.x == R + BR;
         if (!free_slot) __syncthreads();
-        stage_rows<T, RS, PF>(a, in, lds, u + 1, py0, px0, rowvec, nvec, pf, pf_off);
+        stage_rows<T, RS, PF>(a, in, lds, u + 1, Rn, py0, px0, rowvec, nvec, pf, pf_off);
         __syncthreads();
         if (u + 2 < u1)
-          stage_prefetch<T, RS, PF>(a, in, u + 2, py0, px0, rowvec, nvec, pf, pf_off);
+          stage_prefetch<T, RS, PF>(a, in, u + 2, unit_rows(a, u + 2, false), py0, px0, rowvec,
+                                      nvec, pf, pf_off);
       }
     }
   }
@@ -970,6 +977,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int rowvec = a.NCOL * nvec;
   StagedArgs sa;
   sa.units = a.units;
+  sa.K = a.K;
   sa.urows = a.urows;
   sa.NCOL = a.NCOL;
   sa.CS = a.CS;
@@ -993,11 +1001,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int j = 0; j < PD; ++j) load_f8(pack, min(U.z + sw + S * j, U.w - 1), lane, ring[j]);
 #pragma unroll
       for (int j = 0; j < RQ; ++j) rq[j] = load_rec8(a, min(U.z + sw + S * j, U.w - 1), g, lane);
-      stage_prefetch<uint8_t, RS, PF>(sa, in, u0, py0, px0, rowvec, nvec, pf, pf_off);
-      stage_rows<uint8_t, RS, PF>(sa, in, lds, u0, py0, px0, rowvec, nvec, pf, pf_off);
+      const int2 rows = unit_rows(sa, u0, true);
+      stage_prefetch<uint8_t, RS, PF>(sa, in, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
+      stage_rows<uint8_t, RS, PF>(sa, in, lds, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
       __syncthreads();
       if (u0 + 1 < u1)
-        stage_prefetch<uint8_t, RS, PF>(sa, in, u0 + 1, py0, px0, rowvec, nvec, pf, pf_off);
+        stage_prefetch<uint8_t, RS, PF>(sa, in, u0 + 1, unit_rows(sa, u0 + 1, false), py0, px0, rowvec,
+                                    nvec, pf, pf_off);
     }
     for (int u = u0; u < u1; ++u) {
       const int4 U = a.units[u];
@@ -1038,10 +1048,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           rq[j] = load_rec8(a, min(Un.z + sw + S * j, Un.w - 1), g, lane);
         const bool free_slot = Rn.y - Rn.x == 1 && Rn.x == R + BR;
         if (!free_slot) __syncthreads();
-        stage_rows<uint8_t, RS, PF>(sa, in, lds, u + 1, py0, px0, rowvec, nvec, pf, pf_off);
+        stage_rows<uint8_t, RS, PF>(sa, in, lds, u + 1, Rn, py0, px0, rowvec, nvec, pf, pf_off);
         __syncthreads();
         if (u + 2 < u1)
-          stage_prefetch<uint8_t, RS, PF>(sa, in, u + 2, py0, px0, rowvec, nvec, pf, pf_off);
+          stage_prefetch<uint8_t, RS, PF>(sa, in, u + 2, unit_rows(sa, u + 2, false), py0, px0, rowvec,
+                                      nvec, pf, pf_off);
       }
     }
   }

@@ -537,16 +537,8 @@ std::vector<UnitEntry> order_unit(const std::vector<UnitEntry>& in, int maxcol, 
   return out;
 }
 
-// Plan the staged launch of a layout (plan.h) and upload the pieces.  The partial slots are
-// capped at 1 GiB.
-int plan_pieces(Layout& lay, const std::vector<int>& tile_units,
-                const std::vector<std::vector<int>>& chunk_starts,
-                const std::vector<double>& unit_work, int slots, size_t& bytes,
-                size_t esize = sizeof(float), double max_slots = (double)(1ll << 30),
-                int max_cut = 8, const PlanCosts& costs = PlanCosts()) {
-  const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * esize;
-  const LaunchPlan plan = plan_launch(tile_units, chunk_starts, unit_work, lay.n_patches, slots,
-                                      /*allow_cut=*/true, slot_bytes, max_slots, max_cut, costs);
+// Upload the plan of a layout's launch.
+int set_plan(Layout& lay, const LaunchPlan& plan, size_t& bytes) {
   std::vector<int4> pieces;
   for (const PlanPiece& p : plan.pieces) pieces.push_back(make_int4(p.tile, p.u0, p.u1, p.slot));
   std::vector<int2> split(lay.n_tiles);
@@ -558,6 +550,54 @@ int plan_pieces(Layout& lay, const std::vector<int>& tile_units,
   AROAM_TRY(alloc_copy(&lay.d_tile_split, split, bytes));
   return AROAM_OK;
 }
+
+// What a tile's stage units cost and where they may be cut.
+struct UnitPlan {
+  std::vector<int> tile_units;                 // [tile + 1] first unit of each tile
+  std::vector<std::vector<int>> units;         // [tile] its units: a piece may start at any
+  std::vector<std::vector<int>> chunk_starts;  // [tile] those at which a chunk starts
+  std::vector<double> work;                    // [unit] MFMA row halves it issues
+};
+
+int device_cus(const Model& m, int& cus) {
+  cus = 0;
+  AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
+  cus = std::max(cus, 1);
+  return AROAM_OK;
+}
+
+// Plan and upload a BF16 or FP8 launch (plan.h): two workgroups per CU, slots of at most 1 GiB.
+// `unit_cost` is added to every unit's work.  The allocation-free forward holds a padded input
+// of `input` bytes and the slots in the static scratch array; where cuts at chunk starts alone
+// would fit it, finer ones are limited to fit too.
+int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, double unit_cost,
+                const PlanCosts& costs, double input, size_t& bytes) {
+  int cus = 0;
+  AROAM_TRY(device_cus(m, cus));
+  const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * sizeof(float), most = 1ll << 30;
+  std::vector<double> work(up.work);
+  for (double& w : work) w += unit_cost;
+  auto plan = [&](double limit) {
+    return plan_launch(up.tile_units, up.units, work, lay.n_patches, 2 * cus, /*allow_cut=*/true,
+                       slot_bytes, limit, 64, costs);
+  };
+  LaunchPlan p = plan(most);
+  const double room = (double)kStaticScratchBytes - (1 << 20) - input;
+  const double per_slot = slot_bytes * lay.n_patches;
+  if (!adjoint && room > 0 && p.n_slots * per_slot > room &&
+      plan_launch(up.tile_units, up.chunk_starts, up.work, lay.n_patches, 3 * cus, true, slot_bytes,
+                  most).n_slots * per_slot <= room)
+    p = plan(room);
+  return set_plan(lay, p, bytes);
+}
+
+// Costs of a BF16 launch in half bundles (of the 256 positions of a patch), of an FP8 launch in
+// its own: as kRingCosts below.  With them and cuts at any unit, BF16 and FP8 applies of 40 x 40 to
+// 96 x 96 scans take 0.32 to 0.75 of their time with cuts at chunk starts (forward 96 x 96 x 64,
+// K 20: BF16 172 -> 126 us, FP8 216 -> 151 us).  Larger or smaller costs, and three or four
+// workgroups per CU in the simulation, measured slower.
+constexpr double kBf16Unit = 16, kFp8Unit = 8;
+constexpr PlanCosts kBf16Costs{60, 200, 6}, kFp8Costs{30, 60, 3};
 
 int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int BR, int BC,
                         int esize, Layout& lay, size_t& bytes) {
@@ -591,8 +631,9 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   std::vector<std::vector<char>> hhits((size_t)W * NH, std::vector<char>((size_t)nq + 1));
   std::vector<int> bmask;
   std::vector<char> dx_any(W);
-  std::vector<std::vector<int>> chunk_starts(lay.n_tiles);  // first unit of each chunk
-  std::vector<double> unit_work;                           // MFMA halves a unit issues
+  UnitPlan up;
+  up.units.resize(lay.n_tiles);
+  up.chunk_starts.resize(lay.n_tiles);
   // per (chunk, row-offset slot) list of the current tile's K-groups
   std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
   for (int t = 0; t < lay.n_tiles; ++t) {
@@ -625,7 +666,8 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
       for (int R = 0; R < W; ++R) {
         auto& lst = per[(size_t)c * W + R];
         if (lst.empty()) continue;
-        if (prevR < 0) chunk_starts[t].push_back((int)units.size());
+        up.units[t].push_back((int)units.size());
+        if (prevR < 0) up.chunk_starts[t].push_back((int)units.size());
         const size_t first = groups.size();
         const std::vector<UnitEntry> ord = order_unit(lst, 2 * K, t, NH);
         for (size_t i = 0; i < ord.size(); ++i) {
@@ -645,7 +687,7 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
         double w = 0;
         for (size_t b = first / kLaneGroups; b < groups.size() / kLaneGroups; ++b)
           w += __builtin_popcount((unsigned)bmask[b]);
-        unit_work.push_back(w);
+        up.work.push_back(w);
         prevR = R;
       }
     }
@@ -665,9 +707,8 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.h_tile_start = tile_units;
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
-  int cus = 0;
-  AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
-  return plan_pieces(lay, tile_units, chunk_starts, unit_work, 3 * std::max(cus, 1), bytes);
+  up.tile_units = tile_units;
+  return plan_staged(m, adjoint, lay, up, kBf16Unit, kBf16Costs, 2.0 * lay.in.elems(), bytes);
 }
 
 // Costs of a ring launch in bundles (of the 128 positions of a patch, about 0.1 us): a unit's
@@ -755,9 +796,13 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
   int cus = 0;
-  AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
-  return plan_pieces(lay, tile_units, cuts, unit_work, 3 * std::max(cus, 1), bytes, esize,
-                     std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64, kRingCosts);
+  AROAM_TRY(device_cus(m, cus));
+  return set_plan(lay,
+                  plan_launch(tile_units, cuts, unit_work, lay.n_patches, 3 * cus, /*allow_cut=*/true,
+                              (double)TM * BR * BC * esize,
+                              std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64,
+                              kRingCosts),
+                  bytes);
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
@@ -807,8 +852,9 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   std::vector<std::vector<char>> hits(W, std::vector<char>((size_t)nq + 1));
   std::vector<std::vector<char>> hhits((size_t)W * 2, std::vector<char>((size_t)nq + 1));
   std::vector<char> dx_any(W);
-  std::vector<std::vector<int>> chunk_starts(lay.n_tiles);
-  std::vector<double> unit_work;
+  UnitPlan up;
+  up.units.resize(lay.n_tiles);
+  up.chunk_starts.resize(lay.n_tiles);
   struct Entry {
     int4 group;
     int off;   // LDS offset of the K-group's run
@@ -848,7 +894,8 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
       for (int R = 0; R < W; ++R) {
         auto& lst = per[(size_t)c * W + R];
         if (lst.empty()) continue;
-        if (prevR < 0) chunk_starts[t].push_back((int)units.size());
+        up.units[t].push_back((int)units.size());
+        if (prevR < 0) up.chunk_starts[t].push_back((int)units.size());
         const int first_bundle = (int)(groups.size() / 16);
         // scale blocks: K-groups of equal key, four at a time (a short block is padded with
         // null K-groups, whose table entries are zero).  A block's K-groups 0, 1 and 2, 3 sit
@@ -919,7 +966,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         urows.push_back(make_int2(lo, R + BR));
         double w = 0;
         for (int bi = first_bundle; bi < nb; ++bi) w += __builtin_popcount((unsigned)bmask[bi]);
-        unit_work.push_back(w);
+        up.work.push_back(w);
         prevR = R;
       }
     }
@@ -939,9 +986,8 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.h_tile_start = tile_units;
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
-  int cus = 0;
-  AROAM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m.device));
-  return plan_pieces(lay, tile_units, chunk_starts, unit_work, 3 * std::max(cus, 1), bytes);
+  up.tile_units = tile_units;
+  return plan_staged(m, adjoint, lay, up, kFp8Unit, kFp8Costs, 1.0 * lay.in.elems(), bytes);
 }
 
 template <typename T>
