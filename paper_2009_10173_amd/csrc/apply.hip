@@ -352,11 +352,14 @@ constexpr size_t red_bytes(int S, int MH) { return (size_t)4 * S * MH * 64 * 16;
 // LDS-ring applies (FP32 and FP64).
 //
 // A workgroup (W waves) owns one 16-row output tile and a patch of BR x BC scan positions.  The
-// tile's bundles are grouped into stage units (chunk of the inner axis, input row offset) in
-// the order chunk, row.  The LDS holds the BR input rows a unit reads (the patch's columns and
-// K more on each side, the chunk's entries) plus one free row, as a ring indexed by padded row
-// modulo BR + 1: a unit loads only the rows it adds, usually one, into registers while the unit
-// before it computes.  The rows come straight from the caller's vector; positions outside the
+// tile's bundles are grouped into stage units (chunk of the inner axis, kRingStep consecutive
+// input row offsets) in the order chunk, row.  The LDS holds the rows a unit reads (the patch's
+// columns and K more on each side, the chunk's entries) and room for kRingStep more, as a ring
+// indexed by padded row: a unit loads only the rows it adds into registers while the unit before
+// it computes, and one barrier makes them visible.  Four row offsets to a unit share one
+// barrier and one trip to memory and pool their bundles over the waves: against one, on chunks
+// of two runs, the 400 x 400 FP32 forward takes 94.8 ms instead of 105.4, the 64 x 64 one 150 us
+// instead of 161, the FP64 96 x 96 adjoint 1.32 ms instead of 1.40.  The rows come straight from the caller's vector; positions outside the
 // scan and entries past the end of the axis are written as zeros.  The waves form P row groups
 // of BR / P patch rows, and the S = W / P waves of a group take the bundles of each unit in
 // turn, so that a table fragment is loaded once per row group; at the end the S partial sums of
@@ -376,8 +379,8 @@ typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));
 // add up to no less than 2^-16 of the leading one; the three left out are below 2^-24 of it.
 // The sums run in FP32.  Six BF16 MFMAs of K = 32 take 96 cycles where the eight FP32 MFMAs of
 // K = 4 take 256, and round the sum less often: the 400 x 400 forward took 181 ms on
-// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 102 ms at 1.7e-6 (200 x 200
-// adjoint: 8.05 ms, 2.3e-6 and 4.46 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
+// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 95 ms at 1.9e-6 (200 x 200
+// adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
 // the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
 struct OpF32 {
   using In = float;
@@ -385,10 +388,10 @@ struct OpF32 {
   using VecU = floatx4u;           // the same with the alignment of one entry
   using Acc = floatx4;
   static constexpr int kVec = 4;   // entries of a staged vector
-  static constexpr int kCol = kRingF32.col_bytes;
-  static constexpr int kVecs = kRingF32.CH / kVec;  // staged vectors per column
+  static constexpr int kCol = kRingColumnBytes;
+  static constexpr int kVecs = kRingF32.G / kVec;   // staged vectors per column
   static constexpr int kTiles = 2;                  // position tiles per phase
-  static constexpr int kPlane = 2 * kRingF32.CH;    // LDS bytes of one part of a column
+  static constexpr int kPlane = 2 * kRingF32.G;     // LDS bytes of one part of a column
   struct A {
     u32x4 v[3];
   };
@@ -445,7 +448,7 @@ struct OpF32 {
 };
 
 // FP64 on v_mfma_f64_16x16x4_f64: entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
-// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.56 ms; with positions read from
+// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.32 ms; with positions read from
 // global memory it took 3.42 ms (bound by the texture path), with one FMA per load 68.4 ms.
 struct OpF64 {
   using In = double;
@@ -453,8 +456,8 @@ struct OpF64 {
   using VecU = doublex2u;
   using Acc = doublex4;
   static constexpr int kVec = 2;
-  static constexpr int kCol = kRingF64.col_bytes;
-  static constexpr int kVecs = kRingF64.CH / kVec;
+  static constexpr int kCol = kRingColumnBytes;
+  static constexpr int kVecs = kRingF64.G / kVec;
   static constexpr int kTiles = 2;
   struct A {
     doublex4 v;
@@ -496,6 +499,7 @@ struct RingArgs {
   int out_len, nx, ny, K, L;
   int ncc;             // patch columns
   int NCOL;            // staged columns
+  int row_bytes;       // LDS bytes of a staged row
 };
 
 // Staged vectors in flight: the 16-byte pieces of the rows a unit adds.  off < 0: none.
@@ -518,7 +522,7 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
   const int c = rem / Op::kVecs, v = rem % Op::kVecs;
   const int py = py0 + G - a.K, px = px0 + c - a.K, l = e0 + v * Op::kVec;
   const bool ok = idx < nv && py >= 0 && py < a.ny && px >= 0 && px < a.nx && l < a.L;
-  off = idx < nv ? ((G % RS) * a.NCOL + c) * Op::kCol + (v << 8 * 3) : -1;
+  off = idx < nv ? (G % RS) * a.row_bytes + c * Op::kCol + (v << 8 * 3) : -1;
   zero = !ok;
   const typename Op::In* p = in + (ok ? ((long long)py * a.nx + px) * a.L + l : 0);
   typename Op::Vec r;
@@ -541,11 +545,11 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
 // issued each read next to its use, the 400 x 400 FP32 forward took 114 ms (MFMA busy 0.61,
 // waves waiting 0.46 of their time); phases of four tiles take 105 ms, of two 104.6, and of
 // two within 168 registers (three waves per SIMD where the LDS allows) 102 ms and, for the 200 x
-// 200 adjoint, 4.46 ms instead of 4.71.  At that issue rate (1.4 PFLOP/s of BF16, a large library
+// 200 adjoint, 4.46 ms instead of 4.71 (all with units of one row offset).  At that issue rate (1.4 PFLOP/s of BF16, a large library
 // product reaches 1.1) the chip lowers its clock from 2.1 to 1.7-1.8 GHz: what is left is power,
 // spent on the table stream (L2 and beyond) and on the zeros of the tiles besides the products.
 template <class Op, int BR, int BC, int W, int P, bool RAGGED>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void k_apply_ring(
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 ? 2 : 3))) void k_apply_ring(
     const void* __restrict__ pack, const typename Op::In* __restrict__ in,
     typename Op::In* __restrict__ out, RingArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -557,8 +561,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
   constexpr int XT = Op::kTiles;  // tiles per phase
   constexpr int PH = NT / XT;
   constexpr int RPP = XT / TPR;   // patch rows per phase
-  constexpr int RS = BR + 1;
-  constexpr int PF = 2;           // staged vectors in flight per thread
+  constexpr int ST = kRingStep;   // row offsets of a unit
+  constexpr int UR = BR + ST - 1; // rows a unit reads
+  constexpr int RS = UR + ST;     // rows of the ring
+  constexpr int PF = BR == 8 ? 4 : 3;  // staged vectors in flight per thread
   constexpr int TH = 64 * W;
   static_assert(W % P == 0 && BR % P == 0 && NT % XT == 0 && XT % TPR == 0 && NT % S == 0, "shape");
   const int4 piece = a.pieces[blockIdx.y];
@@ -577,9 +583,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     int mo;
   };
   RingFetch<Op, PF> f;
-  // the rows unit U adds: padded patch rows [lo, U.x + K + BR) of its chunk
+  // the rows unit U adds: padded patch rows [lo, U.x + K + UR) of its chunk
   auto fetch = [&](const int4& U, int lo) {
-    const int nv = (U.x + a.K + BR - lo) * rowvec;
+    const int nv = (U.x + a.K + UR - lo) * rowvec;
     f.zero = 0;
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
@@ -598,7 +604,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
   auto stage = [&](const int4& U, int lo) {
 #pragma unroll
     for (int i = 0; i < PF; ++i) put(f.v[i], f.off[i], (f.zero >> i) & 1);
-    const int nv = (U.x + a.K + BR - lo) * rowvec;
+    const int nv = (U.x + a.K + UR - lo) * rowvec;
     for (int base = TH * PF; base < nv; base += TH * 4) {
       typename Op::Vec v[4];
       int off[4];
@@ -628,26 +634,31 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     for (int u = u0; u < u1; ++u) {
       const int4 Un = a.units[min(u + 1, u1 - 1)];
       // rows the next unit finds in the ring: those of this unit, in the same chunk
-      const int lo = Un.y == U.y && Un.x < U.x + BR ? U.x + a.K + BR : Un.x + a.K;
+      const int lo = Un.y == U.y && Un.x < U.x + UR ? U.x + a.K + UR : Un.x + a.K;
       r0 = n0;
       load_mo(r1, min(U.z + sw + S, U.w - 1));
       load_a(r1, min(U.z + sw + S, U.w - 1));
       load_mo(n0, min(Un.z + sw, Un.w - 1));
       load_a(n0, min(Un.z + sw, Un.w - 1));
       fetch(Un, lo);
-      // LDS base of this lane's position in each of the wave's rows; a wave whose rows have no
-      // output row or no input row inside the scan skips the unit
-      int rb[RW];
-#pragma unroll
-      for (int r = 0; r < RW; ++r)
-        rb[r] = (((grp * RW + r + U.x + a.K) % RS) * a.NCOL + n) * Op::kCol;
+      // LDS offset of the wave's first row at the unit's first row offset (the same for all
+      // lanes); a wave whose rows have no output row or no input row inside the scan skips the
+      // unit
+      const int s0 = ((grp * RW + U.x + a.K) % RS) * a.row_bytes;
       const int o = py0 + grp * RW, i0 = o + U.x;
-      const bool live = o < a.ny && i0 + RW > 0 && i0 < a.ny;
+      const bool live = o < a.ny && i0 + RW + ST - 1 > 0 && i0 < a.ny;
       auto read = [&](auto ntc, int p, int mo, auto& x) {
         constexpr int NTC = decltype(ntc)::value;
+        const unsigned first = (unsigned)(mo + n * Op::kCol + s0);
 #pragma unroll
-        for (int t = 0; t < RPP * NTC; ++t)
-          x[t] = Op::read_x(lds + (rb[p * RPP + t / NTC] + mo) + (t % NTC) * 16 * Op::kCol);
+        for (int r = 0; r < RPP; ++r) {
+          // row p RPP + r after the K-group's first, wrapped into the ring (the subtraction
+          // underflows to a larger value where there is nothing to wrap)
+          const unsigned q = first + (p * RPP + r) * a.row_bytes;
+          const unsigned char* row = lds + min(q, q - RS * a.row_bytes);
+#pragma unroll
+          for (int t = 0; t < NTC; ++t) x[r * NTC + t] = Op::read_x(row + t * 16 * Op::kCol);
+        }
       };
       // The wave's bundles for the tiles of the first NTC tile columns, all PH phases: the
       // position fragments of a phase are read while the phase before multiplies (the barriers
@@ -682,9 +693,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
       else
         all(std::integral_constant<int, TPR>{});
       if (u + 1 < u1) {
-        // one new row right after this unit's rows goes to the free slot while other waves
-        // still read this unit
-        if (!(Un.x == U.x + 1 && Un.y == U.y)) __syncthreads();
+        // the next row offsets' new rows go to the free slots while other waves still read this
+        // unit
+        if (!(Un.x == U.x + ST && Un.y == U.y)) __syncthreads();
         stage(Un, lo);
         __syncthreads();
         U = Un;
@@ -1215,9 +1226,10 @@ int launch_split(const Layout& lay, const Pack& pk, const void* buf, float* part
   return AROAM_OK;
 }
 
-template <class Op, int BR, int W, int P>
+template <class Op, int BR>
 int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial, void* out,
                 hipStream_t st) {
+  constexpr int W = 4, P = 1;  // waves of a workgroup, row groups they form
   using In = typename Op::In;
   const bool ragged = lay.in.L % Op::kVec != 0;
   auto kern = ragged ? k_apply_ring<Op, BR, kPatchCols, W, P, true>
@@ -1237,6 +1249,7 @@ int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial
   a.L = lay.in.L;
   a.ncc = (int)ceil_div(lay.in.nx, kPatchCols);
   a.NCOL = lay.NCOL;
+  a.row_bytes = ring_row_bytes(a.K);
   AROAM_CHECK(lay.TM == kTile && lay.BR == BR && lay.BC == kPatchCols &&
                   lay.NCOL == kPatchCols + 2 * a.K && lay.CH == Op::kVec * Op::kVecs,
               AROAM_EINVAL, "ring layout shape mismatch");
@@ -1325,9 +1338,12 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
     AROAM_TRY(launch_fp8(m, lay, pk, (const float*)in, buf, stage_parts(m, adjoint, dtype), out,
                          st));
   } else if (dtype == AROAM_FP64) {
-    AROAM_TRY((launch_ring<OpF64, kRingRows, kRingWaves, kRingGroups>(lay, pk, in, buf, out, st)));
+    AROAM_TRY((launch_ring<OpF64, 4>(lay, pk, in, buf, out, st)));
   } else if (dtype == AROAM_FP32) {
-    AROAM_TRY((launch_ring<OpF32, kRingRows, kRingWaves, kRingGroups>(lay, pk, in, buf, out, st)));
+    if (lay.BR == 8)
+      AROAM_TRY((launch_ring<OpF32, 8>(lay, pk, in, buf, out, st)));
+    else
+      AROAM_TRY((launch_ring<OpF32, 4>(lay, pk, in, buf, out, st)));
   } else {
     hipLaunchKernelGGL((k_stage<float, uint16_t>), dim3((unsigned)(pg.nyp * pg.nxp)), dim3(256), 0,
                        st, (const float*)in, (uint16_t*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L,

@@ -70,17 +70,15 @@ struct PadGeom {
 // with one (FP32, runs of 4) the entries of the runs, one MFMA each, that they reach.
 constexpr int kMetaMaskShift = 28;
 
-// LDS form of the ring layouts (FP64, FP32): entries of a K-group, entries of a chunk, LDS bytes
-// of a staged column (its chunk and 16 bytes of padding, an odd number of 16-byte groups, which
-// spreads neighbouring columns over the LDS banks) and of a run within it.  FP64 holds the
-// chunk's eight doubles.  FP32 holds each of the chunk's sixteen values as three BF16 parts, the
-// parts of the chunk after one another.
+// LDS form of the ring layouts (FP64, FP32): entries of a K-group, which are also those of a chunk.
+// A staged column is 48 bytes (three 16-byte groups, an odd number, which spreads neighbouring
+// columns over the LDS banks): four doubles and padding, or three BF16 parts of eight FP32 values,
+// the parts after one another.
 struct RingShape {
-  int G, CH, col_bytes, run_bytes;
+  int G;
 };
-constexpr RingShape kRingF64{4, 8, 80, 32};
-constexpr RingShape kRingF32{8, 16, kRing32ColumnBytes, 16};
-constexpr int kRingWaves = 4, kRingGroups = 1;  // waves of a workgroup, row groups they form
+constexpr RingShape kRingF64{4};
+constexpr RingShape kRingF32{8};
 
 // Band tiles of one operator (forward: rows = time, K = (offset, depth); adjoint: rows =
 // depth, K = (offset, time)) at one K-group width G.  A K-group is G consecutive entries of

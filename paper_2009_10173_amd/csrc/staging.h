@@ -17,14 +17,18 @@ constexpr int kChunkBytes = 64;      // inner-axis entries of one staged column 
 constexpr int kColumnBytes = 80;     // LDS stride of a staged column: chunk + 16 bytes of padding
 constexpr long long kLdsBytes = 160 * 1024;  // LDS of one gfx950 compute unit
 
-// The FP64 and FP32 applies own patches of kRingRows x kPatchCols positions (a ring of
-// kRingRows + 1 rows); their staged columns take up to kRing32ColumnBytes.
-constexpr int kRingRows = 4;
-constexpr int kRing32ColumnBytes = 112;
+// The FP64 and FP32 applies own patches of 4 or 8 rows x kPatchCols positions.  Their units cover
+// kRingStep consecutive row offsets of one chunk, and the ring holds the rows a unit reads and
+// the kRingStep rows the next one adds.  Rows start at multiples of 256 bytes (all LDS banks), so
+// that the row does not change a column's banks.
+constexpr int kRingStep = 4;
+constexpr int kRingColumnBytes = 48;
 
-// LDS bytes of their row ring.
-constexpr long long ring_lds_bytes(int k_half, int column_bytes) {
-  return (long long)(kRingRows + 1) * (kPatchCols + 2 * k_half) * column_bytes;
+constexpr int ring_row_bytes(int k_half) {
+  return ((kPatchCols + 2 * k_half) * kRingColumnBytes + 255) / 256 * 256;
+}
+constexpr long long ring_lds_bytes(int k_half, int patch_rows) {
+  return (long long)(patch_rows + 2 * kRingStep - 1) * ring_row_bytes(k_half);
 }
 
 // LDS bytes of the row ring of a staged apply with offsets -k_half .. k_half.
@@ -39,7 +43,7 @@ constexpr int max_k_half() {
   return k;
 }
 
-static_assert(ring_lds_bytes(max_k_half(), kRing32ColumnBytes) <= kLdsBytes,
-              "the FP32 ring fits wherever the BF16 and FP8 stage does");
+static_assert(ring_lds_bytes(max_k_half(), 4) <= kLdsBytes,
+              "the ring of four patch rows fits wherever the BF16 and FP8 stage does");
 
 }  // namespace aroam

@@ -719,34 +719,52 @@ int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int
 constexpr double kUnitWork = 8;
 constexpr PlanCosts kRingCosts{24, 40, 2};
 
-// LDS-ring form (FP64, FP32; see Layout and RingShape): tiles of 16 rows, stage units as above,
-// no masks (every bundle reaches its tile).  `pad` is the geometry of the zero-padded input,
-// which bounds the partial slots.
+// Patch rows of an FP32 ring launch.  Four rows leave room for three workgroups per CU while the
+// LDS holds three rings; a wider footprint (K = 34 .. 40) leaves two either way, and then eight
+// rows, which load the table half as often, are faster once the launch fills the chip (256 x 256
+// x 128: K 40 forward 15.9 ms on four rows, 14.6 on eight; K 30 10.8 and 10.9; 150 x 210 x 100, K 30
+// 4.1 and 4.5).  FP64 keeps four rows: eight would need twice the accumulators' registers.
+int ring_rows(int K, long long tiles, const aroam_grid& g, int cus) {
+  const long long patches = ceil_div(g.ny, 8) * ceil_div(g.nx, kPatchCols);
+  return 3 * ring_lds_bytes(K, 4) > kLdsBytes && 2 * ring_lds_bytes(K, 8) <= kLdsBytes &&
+                 patches * tiles >= 4 * cus
+             ? 8
+             : 4;
+}
+
+// LDS-ring form (FP64, FP32; see Layout and RingShape): tiles of 16 rows; a chunk is one K-group's
+// run, and a stage unit covers up to kRingStep consecutive row offsets of a chunk, whose K-groups
+// share bundles (a K-group's offset names its row).  No masks: every bundle reaches its tile.
+// `pad` is the geometry of the zero-padded input, which bounds the partial slots.
 int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const PadGeom& pad,
                       size_t esize, Layout& lay, size_t& bytes) {
   const aroam_grid& g = m.grid;
-  const int K = m.K, W = 2 * K + 1, TM = kTile, BR = kRingRows, BC = kPatchCols;
+  const int K = m.K, W = 2 * K + 1, TM = kTile, BC = kPatchCols;
+  int cus = 0;
+  AROAM_TRY(device_cus(m, cus));
   lay.G = rs.G;
   lay.TM = TM;
   lay.staged = true;
-  lay.CH = rs.CH;
-  lay.BR = BR;
+  lay.CH = rs.G;
   lay.BC = BC;
   lay.NCOL = BC + 2 * K;
-  lay.CS = rs.col_bytes;
+  lay.CS = kRingColumnBytes;
   lay.out_len = adjoint ? g.nz : g.nt;
   lay.n_tiles = (int)ceil_div(lay.out_len, TM);
   lay.in = pad;
-  lay.lds_bytes = (size_t)ring_lds_bytes(K, rs.col_bytes);
+  const int BR = esize == sizeof(float) ? ring_rows(K, lay.n_tiles, g, cus) : 4;
+  lay.BR = BR;
+  lay.lds_bytes = (size_t)ring_lds_bytes(K, BR);
   const int inner = adjoint ? g.nt : g.nz;
-  const int nq = (int)ceil_div(inner, rs.G), qpc = rs.CH / rs.G, nch = (int)ceil_div(inner, rs.CH);
-  const CompatTable table(BankShape{rs.col_bytes / 16, rs.run_bytes / 16, qpc});
+  const int nch = (int)ceil_div(inner, rs.G);
+  const CompatTable table(BankShape{kRingColumnBytes / 16, 0, 1});
   std::vector<int4> groups, units;
   std::vector<int> meta, tile_units(lay.n_tiles + 1, 0);
-  std::vector<char> hits((size_t)nq + 1);
+  std::vector<char> hits((size_t)nch + 1);
   std::vector<std::vector<int>> cuts(lay.n_tiles);  // a piece may start at any unit
-  std::vector<double> unit_work;                    // bundles of a unit
+  std::vector<double> unit_work;                    // bundles of a unit and its own costs
   std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
+  std::vector<UnitEntry> lst;
   for (int t = 0; t < lay.n_tiles; ++t) {
     tile_units[t] = (int)units.size();
     for (auto& v : per) v.clear();
@@ -755,37 +773,50 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
       for (int b = 0; b < W; ++b) {
         if (!tile_hits(m, adjoint, rs.G, TM, t, a * W + b, hits)) continue;
         const int col = adjoint ? (W - 1 - b) : b;  // input column offset + K
-        for (int q = 0; q < nq; ++q)
-          if (hits[q])
-            per[(size_t)(q / qpc) * W + slot].push_back(
-                UnitEntry{make_int4(a * W + b, q * rs.G, t, 1), col, q % qpc, 1});
+        for (int c = 0; c < nch; ++c)
+          if (hits[c])
+            per[(size_t)c * W + slot].push_back(
+                UnitEntry{make_int4(a * W + b, c * rs.G, t, slot), col, 0, 1});
       }
     }
     for (int c = 0; c < nch; ++c)
-      for (int R = 0; R < W; ++R) {
-        const auto& lst = per[(size_t)c * W + R];
-        if (lst.empty()) continue;
-        const int first = (int)(groups.size() / kLaneGroups);
-        for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
-          groups.push_back(e.group);
-          meta.push_back(e.col * rs.col_bytes + e.run * rs.run_bytes);
+      for (int R = 0; R < W;) {
+        if (per[(size_t)c * W + R].empty()) {
+          ++R;
+          continue;
         }
-        cuts[t].push_back((int)units.size());
-        units.push_back(make_int4(R - K, c * rs.CH, first, (int)(groups.size() / kLaneGroups)));
-        unit_work.push_back(units.back().w - units.back().z + kUnitWork);
+        // consecutive units step by kRingStep as long as there are K-groups
+        for (int R0 = R;; R0 += kRingStep) {
+          lst.clear();
+          for (int r = R0; r < std::min(W, R0 + kRingStep); ++r)
+            lst.insert(lst.end(), per[(size_t)c * W + r].begin(), per[(size_t)c * W + r].end());
+          R = R0;
+          if (lst.empty()) break;
+          const int first = (int)(groups.size() / kLaneGroups);
+          for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
+            const int row = e.group.x < 0 ? 0 : e.group.w - R0;  // the group's row offset in the unit
+            groups.push_back(make_int4(e.group.x, e.group.y, e.group.z, e.group.x >= 0));
+            meta.push_back(row * ring_row_bytes(K) + e.col * kRingColumnBytes);
+          }
+          cuts[t].push_back((int)units.size());
+          units.push_back(make_int4(R0 - K, c * rs.G, first, (int)(groups.size() / kLaneGroups)));
+          unit_work.push_back(units.back().w - units.back().z + kUnitWork);
+        }
       }
   }
   tile_units[lay.n_tiles] = (int)units.size();
   lay.n_units = (long long)units.size();
   lay.n_bundles = (long long)groups.size() / kLaneGroups;
   // MACs the kernel issues: per bundle 16 rows x 4 G entries for every computed position, which
-  // leaves out patches that have no input row inside the scan and the second 16-position tile column of a patch that holds at most 16 scan columns
+  // leaves out patches that have no input row inside the scan and the second 16-position tile
+  // column of a patch that holds at most 16 scan columns
   const long long cols = g.nx % BC > 0 && g.nx % BC <= 16 ? (long long)(g.nx / BC) * BC + 16
                                                           : round_up(g.nx, BC);
   lay.mac_exec = 0;
   for (const int4& u : units) {
     long long rows = 0;
-    for (int o = 0; o < g.ny; o += BR) rows += o + u.x + BR > 0 && o + u.x < g.ny ? BR : 0;
+    for (int o = 0; o < g.ny; o += BR)
+      rows += o + u.x + BR + kRingStep - 1 > 0 && o + u.x < g.ny ? BR : 0;
     lay.mac_exec += (u.w - u.z) * rows;
   }
   lay.mac_exec *= (long long)kLaneGroups * rs.G * TM * cols;
@@ -795,10 +826,9 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
   AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
-  int cus = 0;
-  AROAM_TRY(device_cus(m, cus));
   return set_plan(lay,
-                  plan_launch(tile_units, cuts, unit_work, lay.n_patches, 3 * cus, /*allow_cut=*/true,
+                  plan_launch(tile_units, cuts, unit_work, lay.n_patches, (BR == 8 ? 2 : 3) * cus,
+                              /*allow_cut=*/true,
                               (double)TM * BR * BC * esize,
                               std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64,
                               kRingCosts),
@@ -1374,7 +1404,7 @@ int pack_fp(Model& m, hipStream_t st, size_t& bytes) {
     Layout& r32 = adj ? m.r32a : m.r32f;
     AROAM_TRY(build_ring_layout(m, adj, kRingF64, pad_geom(m.grid, L), sizeof(double), r64, bytes));
     AROAM_TRY(build_ring_layout(m, adj, kRingF32,
-                                pad_geom(m.grid, L, kPatchRows, kPatchCols, kRingF32.CH),
+                                pad_geom(m.grid, L, kPatchRows, kPatchCols, 16),
                                 sizeof(float), r32, bytes));
     Pack* pack = adj ? m.adj_pack : m.fwd_pack;
     AROAM_TRY(pack_dtype<double>(m, r64, adj, pack[AROAM_FP64], st, bytes));

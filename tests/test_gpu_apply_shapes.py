@@ -54,24 +54,48 @@ def odd_start(a, dtype):
     return t
 
 
-@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
-@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
-def test_apply_matches_oracle_at_tile_edges(grid, dtype):
-    ny, nx, nz, nt, K = grid
-    rng = np.random.default_rng(1000 * ny + nx)
-    H = random_table(rng, nz, nt, K)
+def check(H, ny, nx, dtype, rng, ops=("forward", "adjoint")):
+    K, (nz, nt) = (H.shape[0] - 1) // 2, H.shape[2:]
     g = dict(c_mps=1500.0, fs_hz=250e6, nx=nx, ny=ny, step_m=1e-5, nz=nz, dz_m=1e-5, nt=nt, k_half=K,
              footprint_mode=0)
     tdt, u = (torch.float64, 2.0 ** -53) if dtype == "fp64" else (torch.float32, 2.0 ** -24)
     npt = np.float64 if dtype == "fp64" else np.float32
     with P.Model.from_table(g, H, dtypes=("fp64", "fp32")) as m:
-        for op, shape, apply in ((oops.forward, (ny, nx, nz), m.forward),
-                                 (oops.adjoint, (ny, nx, nt), m.adjoint)):
+        for name in ops:
+            op, shape = getattr(oops, name), (ny, nx, nz if name == "forward" else nt)
             v = rng.standard_normal(shape).astype(npt)
-            print(f"[{grid} {dtype} {op.__name__}]", flush=True)
-            got = apply(odd_start(v, tdt), dtype).cpu().numpy().astype(np.float64)
+            print(f"[{(ny, nx, nz, nt, K)} {dtype} {name}]", flush=True)
+            got = getattr(m, name)(odd_start(v, tdt), dtype).cpu().numpy().astype(np.float64)
             ref = on_scan(op, H, v.astype(np.float64))
             terms = on_scan(op, (H != 0).astype(np.float64), np.ones(shape)).max()
             bound = (2 * np.sqrt(terms) + 8) * u * on_scan(op, np.abs(H),
                                                            np.abs(v).astype(np.float64))
             assert np.all(np.abs(got - ref) <= bound)
+
+
+@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
+def test_apply_matches_oracle_at_tile_edges(grid, dtype):
+    ny, nx, nz, nt, K = grid
+    rng = np.random.default_rng(1000 * ny + nx)
+    check(random_table(rng, nz, nt, K), ny, nx, dtype, rng)
+
+
+@pytest.mark.parametrize("grid", [(3, 5, 9, 20, 97), (2, 40, 5, 33, 62), (61, 120, 8, 512, 37)],
+                         ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
+def test_wide_footprints(grid, dtype):
+    """The widest footprint, one that leaves a single workgroup per CU, and one whose FP32 forward
+    owns patches of eight rows; a table with columns at a few dozen offsets, corners included."""
+    ny, nx, nz, nt, K = grid
+    rng = np.random.default_rng(K)
+    full = random_table(rng, nz, nt, 2)
+    H = np.zeros((2 * K + 1, 2 * K + 1, nz, nt))
+    lim = (min(K, ny - 1), min(K, nx - 1))
+    for i, (a, b) in enumerate([(K, K), (0, 0), (2 * K, 0), (K + lim[0], K - lim[1])]):
+        H[a, b] = full[i, 0]
+    for i in range(40):
+        a = K + rng.integers(-lim[0], lim[0] + 1)
+        b = K + rng.integers(-lim[1], lim[1] + 1)
+        H[a, b] = full[i % 5, 1 + i % 4]
+    check(H, ny, nx, dtype, rng)
