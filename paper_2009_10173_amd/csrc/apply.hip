@@ -40,31 +40,30 @@ typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 
-template <typename Tin, typename Tout>
-__device__ inline Tout conv(Tin v);
-template <>
-__device__ inline uint16_t conv<float, uint16_t>(float f) {  // bf16, round to nearest even
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffff) ? 0x40 : 0));
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-// Stage an input vector [ny][nx][L] into the padded layout [nyp][nxp][Lp]; the halo and the
-// tail of every column are written as zeros.  One workgroup per padded column.
-template <typename Tin, typename Tout>
-__global__ __launch_bounds__(256) void k_stage(const Tin* __restrict__ in, Tout* __restrict__ out,
-                                               int K, int nx, int ny, int nxp, int L, int Lp) {
-  const int col = blockIdx.x;
-  const int px = col % nxp - K, py = col / nxp - K;
-  Tout* o = out + (long long)col * Lp;
-  const bool inside = px >= 0 && px < nx && py >= 0 && py < ny;
-  const Tin* src = in + ((long long)py * nx + px) * L;
-  for (int l = threadIdx.x; l < Lp; l += blockDim.x) {
-    Tout v = Tout(0);
-    if (inside && l < L) v = conv<Tin, Tout>(src[l]);
-    o[l] = v;
+// Stage an input vector [ny][nx][L] as zero-padded BF16 in blocks of the ring's chunks,
+// [chunk][nyp][nxp][8 entries]: a row of a chunk is contiguous, so that the ring's loads use whole
+// cache lines (from [nyp][nxp][L] each 128-byte line would be fetched once per chunk in it: 149 GB
+// instead of 76 beyond the L2 in a 400 x 400 adjoint).  A workgroup covers 32 columns of a row
+// (grid.x: rows x column blocks) and eight chunks; reads are runs of 256 bytes, writes of 512.
+__global__ __launch_bounds__(256) void k_stage_bf16(const float* __restrict__ in,
+                                                    u32x4* __restrict__ out, int K, int nx, int ny,
+                                                    int nxp, int nyp, int L, int nch) {
+  const int nb = (nxp + 31) / 32, row = blockIdx.x / nb;
+  const int c = blockIdx.y * 8 + threadIdx.x % 8, col = blockIdx.x % nb * 32 + threadIdx.x / 8;
+  if (c >= nch || col >= nxp) return;
+  const int px = col - K, py = row - K, l0 = 8 * c;
+  u32x4 w = {0, 0, 0, 0};
+  if (px >= 0 && px < nx && py >= 0 && py < ny) {
+    const float* p = in + ((long long)py * nx + px) * L + l0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      floatx2 f;
+      f[0] = l0 + 2 * i < L ? p[2 * i] : 0.0f;
+      f[1] = l0 + 2 * i + 1 < L ? p[2 * i + 1] : 0.0f;
+      w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+    }
   }
+  out[((long long)c * nyp + row) * nxp + col] = w;
 }
 
 struct StagedArgs {
@@ -79,28 +78,6 @@ struct StagedArgs {
   int ncc;            // patch column chunks
   int NCOL, CS;
 };
-
-// Table operand of one bundle for one lane: 16 bytes per 16-row half (MH = TM / 16 halves).
-template <typename T, int MH>
-struct AFrag {
-  u32x4 v[MH];
-  int mo;  // the K-group's meta word: LDS offset (and for MH > 1 the bundle's half mask)
-};
-
-template <typename T, int MH>
-__device__ __forceinline__ void load_a(const void* __restrict__ pack_raw,
-                                       const int* __restrict__ meta,
-                                       int b, int g, int n,
-                                       AFrag<T, MH>& f) {
-  const int q = b * kLaneGroups + g;
-#pragma unroll
-  for (int h = 0; h < MH; ++h) {
-    const long long row = (long long)q * (16 * MH) + 16 * h + n;
-    constexpr int VEC = 16 / sizeof(T);
-    f.v[h] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(pack_raw) + row * VEC);
-  }
-  f.mo = meta[q];  // raw word: for MH > 1 the bundle's half mask sits in its top bits
-}
 
 // Global source and LDS destination of flat stage vector idx of a unit that loads padded
 // patch rows from `lo`, for the chunk starting at inner entry e0.
@@ -180,178 +157,13 @@ __device__ __forceinline__ void stage_rows(const StagedArgs& a, const T* __restr
   }
 }
 
-// Position fragments of one bundle for the NT tiles of this lane, 16 bytes each from the LDS: tile
-// t sits at row base rb[t / TPR] plus column offset (t % TPR) * 16 * CSC (compile-time column
-// stride CSC, so the offsets are immediates).
-template <typename T, int NT, int TPR, int CSC, int NR>
-__device__ __forceinline__ void read_x_rows(const T* lds, const int (&rb)[NR], int mo,
-                                            u32x4 (&x)[NT]) {
-  mo &= (1 << kMetaMaskShift) - 1;  // the top bits hold the bundle's mask
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-    x[t] = *reinterpret_cast<const u32x4*>(lds + rb[t / TPR] + mo + (t % TPR) * 16 * CSC);
-}
-
-// MFMAs of one bundle whose position fragments are already in registers.
-template <typename T, int MH, int NT>
-__device__ __forceinline__ void bundle_mma(const AFrag<T, MH>& f, const u32x4 (&xraw)[NT],
-                                           floatx4 (&acc)[MH][NT]) {
-  // the bundle's mask: the 16-row halves that a K-group's band reaches; uniform over the wave
-  const unsigned bm = (unsigned)__builtin_amdgcn_readfirstlane(f.mo) >> kMetaMaskShift;
-#pragma unroll
-  for (int h = 0; h < MH; ++h) {
-    if (MH > 1 && !((bm >> h) & 1)) continue;  // the bundle's bands miss this half
-    const bf16x8 av = __builtin_bit_cast(bf16x8, f.v[h]);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const bf16x8 xv = __builtin_bit_cast(bf16x8, xraw[t]);
-      acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, xv, acc[h][t], 0, 0, 0);
-    }
-  }
-}
-
-// Waves that share a BF16 stage unit's bundle stream (the split kernel's S).
-constexpr int kSplit = 4;
-
-// BF16 staged kernel with each stage unit's bundle stream split over waves.  The four waves
-// of a workgroup form 4 / S row groups of the BR x BC patch, and the S waves of a row group
-// take every S-th bundle of each unit, so each wave holds NT = BR * BC / (16 * 4 / S)
-// position tiles and every table fragment is loaded once per row group (S times fewer table
-// loads through the texture-address path per MFMA than with S = 1).  Staging and the LDS row
-// ring are those of k_apply_staged.  At the end the S partial sums of a position are added in
-// wave order through the LDS, in phases of S tiles (red_bytes() of LDS).
-template <int BR, int BC, int MH, int S>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_split(
-    const void* __restrict__ pack_raw, const uint16_t* __restrict__ in, float* __restrict__ out,
-    StagedArgs a) {
-  using T = uint16_t;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  T* lds = reinterpret_cast<T*>(lds_raw);
-  constexpr int VEC = 8;
-  constexpr int TPR = BC / 16;
-  constexpr int P = 4 / S;      // row groups
-  constexpr int RW = BR / P;    // patch rows per wave
-  constexpr int NT = RW * TPR;  // 16-position tiles per wave
-  static_assert(4 % S == 0 && BR % P == 0 && NT % S == 0, "split shape");
-  constexpr int PF = 2;         // prefetched stage vectors per thread
-  constexpr int PD = 2;         // table-fragment ring depth
-  constexpr int CSC = kColumnBytes / 2;  // LDS column stride (elements; checked at launch)
-  constexpr int CH = 4 * VEC;
-  const int4 piece = a.pieces[blockIdx.y];
-  const int tile = piece.x;
-  const int py0 = (blockIdx.x / a.ncc) * BR, px0 = (blockIdx.x % a.ncc) * BC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int grp = wave / S, sw = wave % S;
-  const int n = lane % 16, g = lane / 16;
-  constexpr int nvec = CH / VEC;
-  const int rowvec = a.NCOL * nvec;
-  floatx4 acc[MH][NT];
-#pragma unroll
-  for (int h = 0; h < MH; ++h)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[h][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int u0 = piece.y, u1 = piece.z;
-  if (u0 < u1) {
-    constexpr int RS = BR + 1;
-    u32x4 pf[PF];
-    int pf_off[PF];
-    AFrag<T, MH> ring[PD];
-    {
-      const int4 U = a.units[u0];
-#pragma unroll
-      for (int j = 0; j < PD; ++j)
-        load_a<T, MH>(pack_raw, a.meta, min(U.z + sw + S * j, U.w - 1), g, n, ring[j]);
-      const int2 rows = unit_rows(a, u0, true);
-      stage_prefetch<T, RS, PF>(a, in, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
-      stage_rows<T, RS, PF>(a, in, lds, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
-      __syncthreads();
-      if (u0 + 1 < u1)
-        stage_prefetch<T, RS, PF>(a, in, u0 + 1, unit_rows(a, u0 + 1, false), py0, px0, rowvec,
-                                    nvec, pf, pf_off);
-    }
-    for (int u = u0; u < u1; ++u) {
-      const int4 U = a.units[u];
-      const int R = U.x + a.K;
-      // LDS base of this lane's position in each of the wave's rows for the unit's row offset
-      // (eight row bases instead of sixteen tile bases: fewer VGPRs, 3-4 % faster)
-      int rb[RW];
-#pragma unroll
-      for (int r = 0; r < RW; ++r) rb[r] = (((grp * RW + r + R) % RS) * a.NCOL + n) * CSC;
-      for (int b0 = U.z + sw; b0 < U.w; b0 += S * PD) {
-#pragma unroll
-        for (int j = 0; j < PD; ++j) {
-          const int b = b0 + S * j;
-          if (b < U.w) {
-            u32x4 x[NT];
-            read_x_rows<T, NT, TPR, CSC>(lds, rb, ring[j].mo, x);
-            bundle_mma<T, MH, NT>(ring[j], x, acc);
-          }
-          load_a<T, MH>(pack_raw, a.meta, min(b + S * PD, U.w - 1), g, n, ring[j]);
-        }
-      }
-      if (u + 1 < u1) {
-        const int4 Un = a.units[u + 1];
-        const int2 Rn = a.urows[u + 1];
-#pragma unroll
-        for (int j = 0; j < PD; ++j)
-          load_a<T, MH>(pack_raw, a.meta, min(Un.z + sw + S * j, Un.w - 1), g, n, ring[j]);
-        const bool free_slot = Rn.y - Rn.x == 1 && Rn.x == R + BR;
-        if (!free_slot) __syncthreads();
-        stage_rows<T, RS, PF>(a, in, lds, u + 1, Rn, py0, px0, rowvec, nvec, pf, pf_off);
-        __syncthreads();
-        if (u + 2 < u1)
-          stage_prefetch<T, RS, PF>(a, in, u + 2, unit_rows(a, u + 2, false), py0, px0, rowvec,
-                                      nvec, pf, pf_off);
-      }
-    }
-  }
-  constexpr int PS = BR * BC * 16 * MH;  // floats per slot and patch
-  float* slot =
-      piece.w >= 0 ? a.partial + ((long long)piece.w * a.n_patches + blockIdx.x) * PS : nullptr;
-  // partial sums of the S waves of a row group, S tiles per phase: wave sw of the group adds
-  // tile p + sw over the group's waves (in wave order) and writes it
-  floatx4* red = reinterpret_cast<floatx4*>(lds_raw);
-  __syncthreads();  // every wave is done with the row ring
-#pragma unroll
-  for (int p = 0; p < NT; p += S) {
-#pragma unroll
-    for (int k = 0; k < S; ++k)
-#pragma unroll
-      for (int h = 0; h < MH; ++h) red[((wave * S + k) * MH + h) * 64 + lane] = acc[h][p + k];
-    __syncthreads();
-    floatx4 v[MH];
-#pragma unroll
-    for (int h = 0; h < MH; ++h) {
-      v[h] = red[(((grp * S) * S + sw) * MH + h) * 64 + lane];
-#pragma unroll
-      for (int s = 1; s < S; ++s) v[h] += red[(((grp * S + s) * S + sw) * MH + h) * 64 + lane];
-    }
-    const int t = p + sw;
-    const int py = py0 + grp * RW + t / TPR, px = px0 + (t % TPR) * 16 + n;
-    if (py < a.ny && px < a.nx) {
-      const int local = (grp * RW + t / TPR) * BC + (t % TPR) * 16 + n;
-      float* dst = slot ? slot : out;
-      const long long off = slot ? (long long)local * (16 * MH) - 16 * MH * tile
-                                 : ((long long)py * a.nx + px) * a.out_len;
-#pragma unroll
-      for (int h = 0; h < MH; ++h)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * MH * tile + 16 * h + 4 * g + i;
-          if (row < a.out_len) dst[off + row] = v[h][i];
-        }
-    }
-    __syncthreads();  // the next phase overwrites the sums
-  }
-}
-
-// LDS bytes of the split kernel's final sums: S tiles of MH halves per wave, four waves.
+// LDS bytes of the FP8 kernel's final sums: S tiles of MH halves per wave, four waves.
 constexpr size_t red_bytes(int S, int MH) { return (size_t)4 * S * MH * 64 * 16; }
 
 // ------------------------------------------------------------------------------------------
-// LDS-ring applies (FP32 and FP64).
+// LDS-ring applies (FP32, FP64 and BF16).
 //
-// A workgroup (W waves) owns one 16-row output tile and a patch of BR x BC scan positions.  The
+// A workgroup (W waves) owns one output tile of kHalves 16-row halves and a patch of BR x BC scan positions.  The
 // tile's bundles are grouped into stage units (chunk of the inner axis, kRingStep consecutive
 // input row offsets) in the order chunk, row.  The LDS holds the rows a unit reads (the patch's
 // columns and K more on each side, the chunk's entries) and room for kRingStep more, as a ring
@@ -388,9 +200,11 @@ struct OpF32 {
   using VecU = floatx4u;           // the same with the alignment of one entry
   using Acc = floatx4;
   static constexpr int kVec = 4;   // entries of a staged vector
-  static constexpr int kCol = kRingColumnBytes;
+  static constexpr int kCol = kRingColumnBytes;  // LDS bytes of a staged column
   static constexpr int kVecs = kRingF32.G / kVec;   // staged vectors per column
   static constexpr int kTiles = 2;                  // position tiles per phase
+  static constexpr int kHalves = 1;                 // 16-row halves of an output tile
+  static constexpr bool kBlocked = false;           // input staged as [chunk][row][column] before
   static constexpr int kPlane = 2 * kRingF32.G;     // LDS bytes of one part of a column
   struct A {
     u32x4 v[3];
@@ -431,8 +245,8 @@ struct OpF32 {
     for (int i = 0; i < 3; ++i)
       *reinterpret_cast<u32x2*>(col + 8 * v + i * kPlane) = part[i];
   }
-  // the MFMAs of a bundle for NX tiles whose accumulators lie STEP apart
-  template <int NX, int STEP>
+  // the MFMAs of a bundle's half H for NX tiles whose accumulators lie STEP apart
+  template <int NX, int STEP, int H>
   static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
     constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, px[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -459,6 +273,8 @@ struct OpF64 {
   static constexpr int kCol = kRingColumnBytes;
   static constexpr int kVecs = kRingF64.G / kVec;
   static constexpr int kTiles = 2;
+  static constexpr int kHalves = 1;
+  static constexpr bool kBlocked = false;
   struct A {
     doublex4 v;
   };
@@ -478,7 +294,7 @@ struct OpF64 {
   static __device__ __forceinline__ void write(unsigned char* col, int v, Vec f) {
     *reinterpret_cast<doublex2*>(col + 16 * v) = f;
   }
-  template <int NX, int STEP>
+  template <int NX, int STEP, int H>
   static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -490,16 +306,66 @@ struct OpF64 {
   static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
 };
 
+// BF16: output tiles of two 16-row halves that share the position fragments; a unit's bundles
+// come in the order half 0 alone, half 1 alone, both, so that each run's loop issues only the
+// MFMAs its bundles reach (a test per bundle cost 10 %).  Against one row offset to a unit on
+// chunks of 32 entries, reading ahead within a bundle only: the 200 x 200 x 128 forward (K 20)
+// takes 0.86 ms instead of 0.97, the 400 x 400 adjoint the same 20.2 (power), the refined 96 x 96
+// LSQR 39.6 instead of 41.8.  What bounds it are the reads of the position fragments (one LDS read
+// feeds two MFMAs, or one where a bundle reaches one half) and, on large scans, power.
+struct OpBF16 {
+  using In = float;  // outputs; the input is read as k_stage_bf16 leaves it
+  using Vec = u32x4;
+  using Acc = floatx4;
+  static constexpr int kVec = 8;
+  static constexpr int kCol = kRing16ColumnBytes;
+  static constexpr int kVecs = 1;
+  static constexpr int kTiles = 2;
+  static constexpr int kHalves = 2;
+  static constexpr bool kBlocked = true;
+  struct A {
+    u32x4 v[2];
+  };
+  struct X {
+    u32x4 v;
+  };
+  static __device__ __forceinline__ void load_a(const void* __restrict__ pack, int b, int lane,
+                                                A& f) {
+    const u32x4* p =
+        reinterpret_cast<const u32x4*>(pack) + (long long)b * 128 + lane / 16 * 32 + lane % 16;
+    f.v[0] = p[0];
+    f.v[1] = p[16];
+  }
+  static __device__ __forceinline__ X read_x(const unsigned char* p) {
+    return X{*reinterpret_cast<const u32x4*>(p)};
+  }
+  static __device__ __forceinline__ void write(unsigned char* col, int, Vec f) {
+    *reinterpret_cast<u32x4*>(col) = f;
+  }
+  template <int NX, int STEP, int H>
+  static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
+#pragma unroll
+    for (int t = 0; t < NX; ++t)
+      acc[t * STEP] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.v[H]),
+                                                              __builtin_bit_cast(bf16x8, x[t].v),
+                                                              acc[t * STEP], 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+};
+
 struct RingArgs {
   const int4* pieces;  // (tile, unit begin, unit end, partial slot or -1)
   const int4* units;   // (row offset, chunk start, bundle begin, bundle end)
+  const int2* classes; // two halves: per unit, the end of its bundles of half 0 alone and of half 1
+                       // alone; the rest reach both
   const int* meta;     // per K-group: LDS byte offset of its run from the position's column
-  void* partial;       // [slot][patch][position][16 rows] partial sums of cut tiles
+  void* partial;       // [slot][patch][position][tile rows] partial sums of cut tiles
   int n_patches;
   int out_len, nx, ny, K, L;
   int ncc;             // patch columns
   int NCOL;            // staged columns
   int row_bytes;       // LDS bytes of a staged row
+  int nxp, nyp;        // blocked input: padded columns and rows of a chunk
 };
 
 // Staged vectors in flight: the 16-byte pieces of the rows a unit adds.  off < 0: none.
@@ -520,23 +386,32 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
                                                       int px0, int rowvec, int& off, bool& zero) {
   const int G = lo + idx / rowvec, rem = idx % rowvec;
   const int c = rem / Op::kVecs, v = rem % Op::kVecs;
-  const int py = py0 + G - a.K, px = px0 + c - a.K, l = e0 + v * Op::kVec;
-  const bool ok = idx < nv && py >= 0 && py < a.ny && px >= 0 && px < a.nx && l < a.L;
-  off = idx < nv ? (G % RS) * a.row_bytes + c * Op::kCol + (v << 8 * 3) : -1;
-  zero = !ok;
-  const typename Op::In* p = in + (ok ? ((long long)py * a.nx + px) * a.L + l : 0);
-  typename Op::Vec r;
-  if constexpr (RAGGED) {
-#pragma unroll
-    for (int i = 0; i < Op::kVec; ++i) {
-      const bool in_axis = ok && l + i < a.L;
-      const typename Op::In e = p[in_axis ? i : 0];
-      r[i] = in_axis ? e : typename Op::In(0);
-    }
+  if constexpr (Op::kBlocked) {
+    off = idx < nv ? (G % RS) * a.row_bytes + c * Op::kCol : -1;
+    zero = false;
+    // rows past the last padded one belong to row offsets without K-groups
+    const int row = min(py0 + G, a.nyp - 1);
+    return reinterpret_cast<const u32x4*>(
+        in)[((long long)(e0 / Op::kVec) * a.nyp + row) * a.nxp + px0 + c];
   } else {
-    r = *reinterpret_cast<const typename Op::VecU*>(p);
+    const int py = py0 + G - a.K, px = px0 + c - a.K, l = e0 + v * Op::kVec;
+    const bool ok = idx < nv && py >= 0 && py < a.ny && px >= 0 && px < a.nx && l < a.L;
+    off = idx < nv ? (G % RS) * a.row_bytes + c * Op::kCol + (v << 8 * 3) : -1;
+    zero = !ok;
+    const typename Op::In* p = in + (ok ? ((long long)py * a.nx + px) * a.L + l : 0);
+    typename Op::Vec r;
+    if constexpr (RAGGED) {
+#pragma unroll
+      for (int i = 0; i < Op::kVec; ++i) {
+        const bool in_axis = ok && l + i < a.L;
+        const typename Op::In e = p[in_axis ? i : 0];
+        r[i] = in_axis ? e : typename Op::In(0);
+      }
+    } else {
+      r = *reinterpret_cast<const typename Op::VecU*>(p);
+    }
+    return r;
   }
-  return r;
 }
 
 // The bundle loop is a pipeline of phases of kTiles position tiles: the fragments of a phase are
@@ -564,8 +439,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
   constexpr int ST = kRingStep;   // row offsets of a unit
   constexpr int UR = BR + ST - 1; // rows a unit reads
   constexpr int RS = UR + ST;     // rows of the ring
-  constexpr int PF = BR == 8 ? 4 : 3;  // staged vectors in flight per thread
+  constexpr int PF = Op::kBlocked ? 2 : BR == 8 ? 4 : 3;  // staged vectors in flight per thread
   constexpr int TH = 64 * W;
+  constexpr int MH = Op::kHalves, TM = kTile * MH;
   static_assert(W % P == 0 && BR % P == 0 && NT % XT == 0 && XT % TPR == 0 && NT % S == 0, "shape");
   const int4 piece = a.pieces[blockIdx.y];
   const int tile = piece.x;
@@ -574,9 +450,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
   const int grp = wave / S, sw = wave % S;
   const int n = lane % 16, g = lane / 16;
   const int rowvec = a.NCOL * Op::kVecs;
-  Acc acc[NT];
+  Acc acc[MH][NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = Acc{0, 0, 0, 0};
+  for (int h = 0; h < MH; ++h)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[h][t] = Acc{0, 0, 0, 0};
 
   struct Bundle {
     typename Op::A a;
@@ -633,6 +511,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
     __syncthreads();
     for (int u = u0; u < u1; ++u) {
       const int4 Un = a.units[min(u + 1, u1 - 1)];
+      const int2 C = MH > 1 ? a.classes[u] : make_int2(0, 0);
       // rows the next unit finds in the ring: those of this unit, in the same chunk
       const int lo = Un.y == U.y && Un.x < U.x + UR ? U.x + a.K + UR : Un.x + a.K;
       r0 = n0;
@@ -666,13 +545,18 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
       auto all = [&](auto ntc) {
         constexpr int NTC = decltype(ntc)::value, NX = RPP * NTC;
         typename Op::X x[2][NX];
-        auto body = [&](Bundle& r, const int& mo_next, int b) {
+        // bundle b, of the halves in MASK
+        auto body = [&](auto mask, Bundle& r, const int& mo_next, int b) {
+          constexpr int MASK = decltype(mask)::value;
 #pragma unroll
           for (int p = 0; p < PH; ++p) {
             read(ntc, (p + 1) % PH, p + 1 < PH ? r.mo : mo_next, x[(p + 1) % 2]);
             if (p + 2 == PH) load_mo(r, min(b + 2 * S, U.w - 1));
             __builtin_amdgcn_sched_barrier(0);
-            Op::template mma<NX, TPR / NTC>(r.a, x[p % 2], acc + p * XT);
+            if constexpr (MASK & 1)
+              Op::template mma<NX, TPR / NTC, 0>(r.a, x[p % 2], acc[0] + p * XT);
+            if constexpr (MASK & 2)
+              Op::template mma<NX, TPR / NTC, 1>(r.a, x[p % 2], acc[MH - 1] + p * XT);
             __builtin_amdgcn_sched_barrier(0);
           }
           load_a(r, min(b + 2 * S, U.w - 1));
@@ -681,11 +565,32 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
         int b = U.z + sw;
         if (b >= U.w) return;
         read(ntc, 0, r0.mo, x[0]);
-        for (; b + S < U.w; b += 2 * S) {
-          body(r0, r1.mo, b);
-          body(r1, r0.mo, b + S);
+        if constexpr (MH == 1) {
+          std::integral_constant<int, 1> mask;
+          for (; b + S < U.w; b += 2 * S) {
+            body(mask, r0, r1.mo, b);
+            body(mask, r1, r0.mo, b + S);
+          }
+          if (b < U.w) body(mask, r0, r1.mo, b);
+        } else {
+          // bundles of the same halves in turn; r0 holds the first of each run
+          auto run = [&](auto mask, int end) {
+            for (; b + S < end; b += 2 * S) {
+              body(mask, r0, r1.mo, b);
+              body(mask, r1, r0.mo, b + S);
+            }
+            if (b < end) {
+              body(mask, r0, r1.mo, b);
+              const Bundle t = r0;
+              r0 = r1;
+              r1 = t;
+              b += S;
+            }
+          };
+          run(std::integral_constant<int, 1>{}, C.x);
+          run(std::integral_constant<int, 2>{}, C.y);
+          run(std::integral_constant<int, 3>{}, U.w);
         }
-        if (b < U.w) body(r0, r1.mo, b);
       };
       if (!live) {
       } else if (px0 + 16 >= a.nx)  // the patch's second tile column lies outside the scan
@@ -706,30 +611,43 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
   // group in wave order, S tiles per phase
   using In = typename Op::In;
   In* slot = piece.w >= 0 ? reinterpret_cast<In*>(a.partial) +
-                                ((long long)piece.w * a.n_patches + blockIdx.x) * (BR * BC * 16)
+                                ((long long)piece.w * a.n_patches + blockIdx.x) * (BR * BC * TM)
                           : nullptr;
   Acc* red = reinterpret_cast<Acc*>(lds);
 #pragma unroll
   for (int p = 0; p < NT; p += S) {
-    Acc v = acc[p];
+    Acc v[MH];
     if constexpr (S > 1) {
       __syncthreads();  // the ring, or the phase before
 #pragma unroll
-      for (int k = 0; k < S; ++k) red[(wave * S + k) * 64 + lane] = acc[p + k];
-      __syncthreads();
-      v = red[(grp * S * S + sw) * 64 + lane];
+      for (int k = 0; k < S; ++k)
 #pragma unroll
-      for (int s = 1; s < S; ++s) v += red[((grp * S + s) * S + sw) * 64 + lane];
+        for (int h = 0; h < MH; ++h) red[((wave * S + k) * MH + h) * 64 + lane] = acc[h][p + k];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int h = 0; h < MH; ++h) {
+      if constexpr (S > 1) {
+        v[h] = red[((grp * S * S + sw) * MH + h) * 64 + lane];
+#pragma unroll
+        for (int s = 1; s < S; ++s) v[h] += red[(((grp * S + s) * S + sw) * MH + h) * 64 + lane];
+      } else {
+        v[h] = acc[h][p];
+      }
     }
     const int t = p + sw;
     const int r = grp * RW + t / TPR, c = (t % TPR) * 16 + n;
     const int py = py0 + r, px = px0 + c;
     if (py < a.ny && px < a.nx) {
-      In* dst = slot ? slot + (r * BC + c) * 16
-                     : out + ((long long)py * a.nx + px) * a.out_len + kTile * tile;
+      In* dst = slot ? slot + (r * BC + c) * TM
+                     : out + ((long long)py * a.nx + px) * a.out_len + TM * tile;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (kTile * tile + Op::row(i, g) < a.out_len) dst[Op::row(i, g)] = v[i];
+      for (int h = 0; h < MH; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = kTile * h + Op::row(i, g);
+          if (TM * tile + row < a.out_len) dst[row] = v[h][i];
+        }
     }
   }
 }
@@ -1127,12 +1045,11 @@ const Layout& layout_for(const Model& m, bool adjoint, int dtype) {
 
 namespace {
 
-// The stage buffer of an apply.  FP32 and FP64: the partial slots of a layout with cut tiles,
-// [slot][patch][position of the patch][16 rows]; the size is never below that of the zero-padded
+// The stage buffer of an apply.  FP64 and FP32: the partial slots of a layout with cut tiles,
+// [slot][patch][position of the patch][tile rows]; the size is never below that of the zero-padded
 // input, which limits the allocation-free apply and is charged to a solve.  BF16 and FP8: the
-// padded input, then the partial slots [slot][patch][position of the patch][TM rows] (FP32),
-// then for FP8 the operand's chunk scales: partial maxima [chunk][kAmaxParts] (FP32), E8M0
-// bytes [chunk] (int) and inverse scales [chunk] (FP32).
+// padded input, then the partial slots (FP32), then for FP8 the operand's chunk scales: partial
+// maxima [chunk][kAmaxParts] (FP32), E8M0 bytes [chunk] (int) and inverse scales [chunk] (FP32).
 struct StageParts {
   size_t input = 0, partial = 0, scales = 0;
   int chunks = 0;
@@ -1176,62 +1093,12 @@ int allow_full_lds(F kern, std::atomic<unsigned long long>& done) {
   return AROAM_OK;
 }
 
-// Arguments of the staged kernels for a layout (and the partial slots of its cut tiles).
-int staged_args(const Layout& lay, float* partial, int elem_size, StagedArgs& a) {
-  AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
-              "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
-  a.pieces = lay.d_pieces;
-  a.tile_split = lay.d_tile_split;
-  a.partial = partial;
-  a.n_patches = lay.n_patches;
-  a.units = lay.d_units;
-  a.urows = lay.d_ucols;
-  a.meta = lay.d_meta;
-  a.out_len = lay.out_len;
-  a.nx = lay.in.nx;
-  a.ny = lay.in.ny;
-  a.K = lay.in.K;
-  a.nxp = lay.in.nxp;
-  a.Lp = lay.in.Lp;
-  a.ncc = (int)ceil_div(lay.in.nx, kPatchCols);
-  a.NCOL = lay.NCOL;
-  a.CS = lay.CS;
-  AROAM_CHECK(lay.CH == 4 * (16 / elem_size), AROAM_EINVAL, "chunk length mismatch");
-  AROAM_CHECK(lay.n_patches == ceil_div(lay.in.ny, kPatchRows) * a.ncc, AROAM_EINVAL,
-              "patch count mismatch");
-  AROAM_CHECK(lay.n_slots == 0 || partial, AROAM_EINVAL, "no partial slots for a cut layout");
-  return AROAM_OK;
-}
-
-// BF16 apply: the split kernel, then the slot sums of cut tiles.
-template <int MH>
-int launch_split(const Layout& lay, const Pack& pk, const void* buf, float* partial, void* out,
-                 hipStream_t st) {
-  AROAM_CHECK(lay.TM == 16 * MH, AROAM_EINVAL, "tile height mismatch");
-  auto kern = k_apply_split<kPatchRows, kPatchCols, MH, kSplit>;
-  static std::atomic<unsigned long long> attr_set{0};
-  AROAM_TRY(allow_full_lds(kern, attr_set));
-  StagedArgs a;
-  AROAM_TRY(staged_args(lay, partial, 2, a));
-  AROAM_CHECK(lay.CS * 2 == kColumnBytes, AROAM_EINVAL, "BF16 layout column stride mismatch");
-  const size_t lds = std::max(lay.lds_bytes, red_bytes(kSplit, MH));
-  const dim3 grid((unsigned)lay.n_patches, (unsigned)lay.n_pieces);
-  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, (const void*)pk.d, (const uint16_t*)buf,
-                     (float*)out, a);
-  if (lay.n_slots > 0)
-    hipLaunchKernelGGL((k_add_slots<float, kPatchRows, kPatchCols, 16 * MH>),
-                       dim3((unsigned)lay.n_patches, (unsigned)lay.n_tiles), dim3(256), 0, st,
-                       lay.d_tile_split, (const float*)partial, (float*)out, lay.n_patches, a.ncc,
-                       a.nx, a.ny, a.out_len);
-  return AROAM_OK;
-}
-
 template <class Op, int BR>
 int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial, void* out,
                 hipStream_t st) {
   constexpr int W = 4, P = 1;  // waves of a workgroup, row groups they form
   using In = typename Op::In;
-  const bool ragged = lay.in.L % Op::kVec != 0;
+  const bool ragged = !Op::kBlocked && lay.in.L % Op::kVec != 0;
   auto kern = ragged ? k_apply_ring<Op, BR, kPatchCols, W, P, true>
                      : k_apply_ring<Op, BR, kPatchCols, W, P, false>;
   static std::atomic<unsigned long long> attr_set[2];
@@ -1249,18 +1116,22 @@ int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial
   a.L = lay.in.L;
   a.ncc = (int)ceil_div(lay.in.nx, kPatchCols);
   a.NCOL = lay.NCOL;
-  a.row_bytes = ring_row_bytes(a.K);
-  AROAM_CHECK(lay.TM == kTile && lay.BR == BR && lay.BC == kPatchCols &&
-                  lay.NCOL == kPatchCols + 2 * a.K && lay.CH == Op::kVec * Op::kVecs,
+  a.row_bytes = ring_row_bytes(a.K, Op::kCol);
+  a.classes = lay.d_ucols;
+  a.nxp = lay.in.nxp;
+  a.nyp = lay.in.nyp;
+  AROAM_CHECK(lay.TM == kTile * Op::kHalves && lay.BR == BR && lay.BC == kPatchCols &&
+                  lay.NCOL == kPatchCols + 2 * a.K && lay.CH == Op::kVec * Op::kVecs &&
+                  (!Op::kBlocked || lay.in.nxp >= (int)round_up(a.nx, kPatchCols) + 2 * a.K),
               AROAM_EINVAL, "ring layout shape mismatch");
   AROAM_CHECK(lay.n_patches == ceil_div(lay.in.ny, BR) * a.ncc, AROAM_EINVAL, "patch count mismatch");
   AROAM_CHECK(lay.n_slots == 0 || partial, AROAM_EINVAL, "no partial slots for a cut layout");
-  const size_t red = (size_t)W * (W / P) * 64 * sizeof(typename Op::Acc);
+  const size_t red = (size_t)W * (W / P) * Op::kHalves * 64 * sizeof(typename Op::Acc);
   const dim3 grid((unsigned)lay.n_patches, (unsigned)lay.n_pieces);
   hipLaunchKernelGGL(kern, grid, dim3(64 * W), std::max(lay.lds_bytes, red), st, (const void*)pk.d,
                      (const In*)in, (In*)out, a);
   if (lay.n_slots > 0)
-    hipLaunchKernelGGL((k_add_slots<In, BR, kPatchCols, kTile>),
+    hipLaunchKernelGGL((k_add_slots<In, BR, kPatchCols, kTile * Op::kHalves>),
                        dim3((unsigned)lay.n_patches, (unsigned)lay.n_tiles), dim3(256), 0, st,
                        lay.d_tile_split, (const In*)partial, (In*)out, lay.n_patches, a.ncc, a.nx,
                        a.ny, a.out_len);
@@ -1333,7 +1204,6 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
                  hipStream_t st) {
   const Layout& lay = layout_for(m, adjoint, dtype);
   const Pack& pk = adjoint ? m.adj_pack[dtype] : m.fwd_pack[dtype];
-  const PadGeom& pg = lay.in;
   if (dtype == AROAM_FP8E4M3) {
     AROAM_TRY(launch_fp8(m, lay, pk, (const float*)in, buf, stage_parts(m, adjoint, dtype), out,
                          st));
@@ -1345,13 +1215,15 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
     else
       AROAM_TRY((launch_ring<OpF32, 4>(lay, pk, in, buf, out, st)));
   } else {
-    hipLaunchKernelGGL((k_stage<float, uint16_t>), dim3((unsigned)(pg.nyp * pg.nxp)), dim3(256), 0,
-                       st, (const float*)in, (uint16_t*)buf, pg.K, pg.nx, pg.ny, pg.nxp, pg.L,
-                       pg.Lp);
+    const PadGeom& pg = lay.in;
+    const int nch = (int)ceil_div(pg.L, kRingBF16.G);
+    hipLaunchKernelGGL(k_stage_bf16,
+                       dim3((unsigned)(ceil_div(pg.nxp, 32) * pg.nyp), (unsigned)ceil_div(nch, 8)),
+                       dim3(256), 0, st, (const float*)in, (u32x4*)buf, pg.K, pg.nx, pg.ny, pg.nxp,
+                       pg.nyp, pg.L, nch);
     const StageParts sp = stage_parts(m, adjoint, dtype);
-    float* partial =
-        sp.partial > 0 ? reinterpret_cast<float*>(static_cast<char*>(buf) + sp.input) : nullptr;
-    AROAM_TRY((launch_split<kTileRows8 / 16>(lay, pk, buf, partial, out, st)));
+    void* partial = static_cast<char*>(buf) + sp.input;
+    AROAM_TRY((launch_ring<OpBF16, kPatchRows>(lay, pk, buf, partial, out, st)));
   }
   AROAM_HIP(hipGetLastError());
   return AROAM_OK;

@@ -70,15 +70,17 @@ struct PadGeom {
 // with one (FP32, runs of 4) the entries of the runs, one MFMA each, that they reach.
 constexpr int kMetaMaskShift = 28;
 
-// LDS form of the ring layouts (FP64, FP32): entries of a K-group, which are also those of a chunk.
-// A staged column is 48 bytes (three 16-byte groups, an odd number, which spreads neighbouring
-// columns over the LDS banks): four doubles and padding, or three BF16 parts of eight FP32 values,
-// the parts after one another.
+// LDS form of the ring layouts (FP64, FP32, BF16): entries of a K-group, which are also those of a
+// chunk, the bytes of a staged column and the 16-row halves of a tile.  A column is an odd number
+// of 16-byte groups, which spreads neighbouring columns over the LDS banks: four doubles and
+// padding, three BF16 parts of eight FP32 values (the parts after one another), or eight BF16
+// values.
 struct RingShape {
-  int G;
+  int G, col_bytes, halves;
 };
-constexpr RingShape kRingF64{4};
-constexpr RingShape kRingF32{8};
+constexpr RingShape kRingF64{4, kRingColumnBytes, 1};
+constexpr RingShape kRingF32{8, kRingColumnBytes, 1};
+constexpr RingShape kRingBF16{8, kRing16ColumnBytes, 2};
 
 // Band tiles of one operator (forward: rows = time, K = (offset, depth); adjoint: rows =
 // depth, K = (offset, time)) at one K-group width G.  A K-group is G consecutive entries of

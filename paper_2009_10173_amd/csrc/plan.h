@@ -121,7 +121,9 @@ inline LaunchPlan plan_launch(const std::vector<int>& tile_units,
     cut(D, cur, cur_np);
     long long nslots = 0;
     for (int t = 0; t < nT; ++t) nslots += cur_np[t] > 1 ? cur_np[t] : 0;
-    if (D > 1 && (double)nslots * n_patches * slot_bytes > max_slot_bytes) break;
+    if (D > 1 && ((double)nslots * n_patches * slot_bytes > max_slot_bytes ||
+                  cur.size() > 65535))  // rows of a grid
+      break;
     std::vector<PlanPiece> heavy = cur;
     std::stable_sort(heavy.begin(), heavy.end(),
                      [](const PlanPiece& x, const PlanPiece& y) { return x.work > y.work; });

@@ -17,18 +17,18 @@ constexpr int kChunkBytes = 64;      // inner-axis entries of one staged column 
 constexpr int kColumnBytes = 80;     // LDS stride of a staged column: chunk + 16 bytes of padding
 constexpr long long kLdsBytes = 160 * 1024;  // LDS of one gfx950 compute unit
 
-// The FP64 and FP32 applies own patches of 4 or 8 rows x kPatchCols positions.  Their units cover
+// The FP64, FP32 and BF16 applies own patches of 4 or 8 rows x kPatchCols positions.  Their units cover
 // kRingStep consecutive row offsets of one chunk, and the ring holds the rows a unit reads and
 // the kRingStep rows the next one adds.  Rows start at multiples of 256 bytes (all LDS banks), so
 // that the row does not change a column's banks.
 constexpr int kRingStep = 4;
-constexpr int kRingColumnBytes = 48;
+constexpr int kRingColumnBytes = 48, kRing16ColumnBytes = 16;  // FP64 and FP32, BF16
 
-constexpr int ring_row_bytes(int k_half) {
-  return ((kPatchCols + 2 * k_half) * kRingColumnBytes + 255) / 256 * 256;
+constexpr int ring_row_bytes(int k_half, int column_bytes = kRingColumnBytes) {
+  return ((kPatchCols + 2 * k_half) * column_bytes + 255) / 256 * 256;
 }
-constexpr long long ring_lds_bytes(int k_half, int patch_rows) {
-  return (long long)(patch_rows + 2 * kRingStep - 1) * ring_row_bytes(k_half);
+constexpr long long ring_lds_bytes(int k_half, int patch_rows, int column_bytes = kRingColumnBytes) {
+  return (long long)(patch_rows + 2 * kRingStep - 1) * ring_row_bytes(k_half, column_bytes);
 }
 
 // LDS bytes of the row ring of a staged apply with offsets -k_half .. k_half.

@@ -394,7 +394,6 @@ struct BankShape {
   int col, run;  // LDS strides of a column and of a run, in 16-byte groups
   int nrun;      // runs per staged column (at most four)
 };
-constexpr BankShape kBanks16{kColumnBytes / 16, 1, 4};  // BF16
 
 bool pair_conflict_free(const BankShape& sh, int col_a, int run_a, int col_b, int run_b) {
   static const int lo_hi[8] = {0, 1, 2, 3, 12, 13, 14, 15};
@@ -510,33 +509,6 @@ std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<Uni
   return out;
 }
 
-// Order a stage unit's K-groups into bundles of a tile of NH 16-row halves: K-groups are first
-// grouped by the halves their bands reach, so that most bundles reach only one half and the
-// kernel skips the other half's MFMAs.  Each group is paired for the LDS as above.
-std::vector<UnitEntry> order_unit(const std::vector<UnitEntry>& in, int maxcol, int t, int NH) {
-  static const CompatTable table(kBanks16);
-  const BankShape& sh = table.sh;
-  std::vector<UnitEntry> out;
-  for (int mask = 1; mask < 1 << NH; ++mask) {
-    std::vector<UnitEntry> cls;
-    for (const UnitEntry& e : in)
-      if (e.mask == mask) cls.push_back(e);
-    if (cls.empty()) continue;
-    for (const UnitEntry& e : pair_unit(table, cls, maxcol, t, false)) out.push_back(e);
-  }
-  if (out.size() % 4) {
-    UnitEntry p{make_int4(-1, 0, t, 0), 0, 0, 0};
-    for (int r = 1; r < sh.nrun; ++r)
-      if (pair_conflict_free(sh, 0, 0, 0, r)) {
-        p.run = r;
-        break;
-      }
-    out.push_back(UnitEntry{make_int4(-1, 0, t, 0), 0, 0, 0});
-    out.push_back(p);
-  }
-  return out;
-}
-
 // Upload the plan of a layout's launch.
 int set_plan(Layout& lay, const LaunchPlan& plan, size_t& bytes) {
   std::vector<int4> pieces;
@@ -566,10 +538,12 @@ int device_cus(const Model& m, int& cus) {
   return AROAM_OK;
 }
 
+constexpr int kStageChunk = 32;  // entries by which the BF16 input's axis is padded
+
 // Plan and upload a BF16 or FP8 launch (plan.h): two workgroups per CU, slots of at most 1 GiB.
 // `unit_cost` is added to every unit's work.  The allocation-free forward holds a padded input
 // of `input` bytes and the slots in the static scratch array; where cuts at chunk starts alone
-// would fit it, finer ones are limited to fit too.
+// (every kStageChunk entries for BF16, 64 for FP8) would fit it, finer ones are limited to fit too.
 int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, double unit_cost,
                 const PlanCosts& costs, double input, size_t& bytes) {
   int cus = 0;
@@ -596,120 +570,10 @@ int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, d
 // 96 x 96 scans take 0.32 to 0.75 of their time with cuts at chunk starts (forward 96 x 96 x 64,
 // K 20: BF16 172 -> 126 us, FP8 216 -> 151 us).  Larger or smaller costs, and three or four
 // workgroups per CU in the simulation, measured slower.
-constexpr double kBf16Unit = 16, kFp8Unit = 8;
+// A BF16 unit (four row offsets) costs 30: with 16 the batch of three served scans takes 350 us
+// instead of 332, with 44 the 200 x 200 x 128 forward 911 instead of 862.
+constexpr double kBf16Unit = 30, kFp8Unit = 8;
 constexpr PlanCosts kBf16Costs{60, 200, 6}, kFp8Costs{30, 60, 3};
-
-int build_staged_layout(const Model& m, bool adjoint, int G, int TM, int CH, int BR, int BC,
-                        int esize, Layout& lay, size_t& bytes) {
-  const aroam_grid& g = m.grid;
-  const int K = m.K, W = 2 * K + 1, nz = g.nz, nt = g.nt;
-  lay.G = G;
-  lay.TM = TM;
-  lay.staged = true;
-  lay.CH = CH;
-  lay.BR = BR;
-  lay.BC = BC;
-  lay.NCOL = BC + 2 * K;
-  AROAM_CHECK(CH * esize == kChunkBytes && G * esize == 16, AROAM_EINVAL,
-              "staged layout needs 64-byte chunks of four 16-byte runs");
-  lay.CS = kColumnBytes / esize;  // 64 bytes of chunk + 16 bytes of padding
-  lay.out_len = adjoint ? nz : nt;
-  lay.n_tiles = (int)ceil_div(lay.out_len, TM);
-  lay.in = pad_geom(g, adjoint ? nt : nz, BR, BC, CH);
-  lay.lds_bytes = (size_t)(BR + 1) * lay.NCOL * lay.CS * esize;  // BR rows + one free slot
-  AROAM_CHECK(BR == kPatchRows && BC == kPatchCols && (long long)lay.lds_bytes == staged_lds_bytes(K),
-              AROAM_EINVAL, "staged layout shape differs from the LDS stage's");
-  const int inner = adjoint ? nt : nz;
-  const int nq = (int)ceil_div(inner, G);
-  const int qpc = CH / G;  // runs per chunk
-  const int nch = (int)ceil_div(inner, CH);
-  std::vector<int4> groups, units;
-  std::vector<int2> urows;
-  std::vector<int> meta, tile_units(lay.n_tiles + 1, 0);
-  std::vector<std::vector<char>> hits(W, std::vector<char>((size_t)nq + 1));
-  const int NH = TM / kTile;  // 16-row halves per tile
-  std::vector<std::vector<char>> hhits((size_t)W * NH, std::vector<char>((size_t)nq + 1));
-  std::vector<int> bmask;
-  std::vector<char> dx_any(W);
-  UnitPlan up;
-  up.units.resize(lay.n_tiles);
-  up.chunk_starts.resize(lay.n_tiles);
-  // per (chunk, row-offset slot) list of the current tile's K-groups
-  std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
-  for (int t = 0; t < lay.n_tiles; ++t) {
-    tile_units[t] = (int)units.size();
-    for (auto& v : per) v.clear();
-    for (int a = 0; a < W; ++a) {
-      // input row offset: +dy for the forward, -dy for the adjoint; slot = offset + K
-      const int slot = adjoint ? (W - 1 - a) : a;
-      for (int b = 0; b < W; ++b) {
-        dx_any[b] = tile_hits(m, adjoint, G, TM, t, a * W + b, hits[b]);
-        if (dx_any[b])
-          for (int h = 0; h < NH; ++h)
-            tile_hits(m, adjoint, G, kTile, t * NH + h, a * W + b, hhits[(size_t)b * NH + h]);
-      }
-      for (int b = 0; b < W; ++b) {
-        if (!dx_any[b]) continue;
-        const int col = adjoint ? (W - 1 - b) : b;  // input column offset + K
-        for (int q = 0; q < nq; ++q) {
-          if (!hits[b][q]) continue;
-          const int c = q / qpc;
-          int mask = 0;  // the halves the K-group's band reaches
-          for (int h = 0; h < NH; ++h) mask |= hhits[(size_t)b * NH + h][q] ? 1 << h : 0;
-          per[(size_t)c * W + slot].push_back(
-              UnitEntry{make_int4(a * W + b, q * G, t, 1), col, (q * G - c * CH) / G, mask});
-        }
-      }
-    }
-    for (int c = 0; c < nch; ++c) {
-      int prevR = -1;
-      for (int R = 0; R < W; ++R) {
-        auto& lst = per[(size_t)c * W + R];
-        if (lst.empty()) continue;
-        up.units[t].push_back((int)units.size());
-        if (prevR < 0) up.chunk_starts[t].push_back((int)units.size());
-        const size_t first = groups.size();
-        const std::vector<UnitEntry> ord = order_unit(lst, 2 * K, t, NH);
-        for (size_t i = 0; i < ord.size(); ++i) {
-          const UnitEntry& e = ord[i];
-          groups.push_back(e.group);
-          meta.push_back(e.col * lay.CS + e.run * G);
-          if (i % kLaneGroups == 0) bmask.push_back(0);
-          bmask.back() |= e.mask;
-        }
-        // the bundle's mask rides in the top bits of its K-groups' offsets
-        for (size_t q = first; q < groups.size(); ++q)
-          meta[q] = (int)((unsigned)meta[q] | ((unsigned)bmask[q / kLaneGroups] << kMetaMaskShift));
-        const int lo = (prevR < 0 || R >= prevR + BR) ? R : prevR + BR;
-        units.push_back(make_int4(R - K, c * CH, (int)(first / kLaneGroups),
-                                  (int)(groups.size() / kLaneGroups)));
-        urows.push_back(make_int2(lo, R + BR));
-        double w = 0;
-        for (size_t b = first / kLaneGroups; b < groups.size() / kLaneGroups; ++b)
-          w += __builtin_popcount((unsigned)bmask[b]);
-        up.work.push_back(w);
-        prevR = R;
-      }
-    }
-  }
-  tile_units[lay.n_tiles] = (int)units.size();
-  lay.n_units = (long long)units.size();
-  lay.n_bundles = (long long)groups.size() / kLaneGroups;
-  // MACs the kernel issues: per bundle, its 16-row halves times the positions of every patch
-  long long halves = 0;
-  for (int bm : bmask) halves += __builtin_popcount((unsigned)bm);
-  lay.mac_exec = halves * kLaneGroups * kTile * G * round_up(g.ny, BR) * round_up(g.nx, BC);
-  AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
-              "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
-  AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_ucols, urows, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
-  lay.h_tile_start = tile_units;
-  lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
-  up.tile_units = tile_units;
-  return plan_staged(m, adjoint, lay, up, kBf16Unit, kBf16Costs, 2.0 * lay.in.elems(), bytes);
-}
 
 // Costs of a ring launch in bundles (of the 128 positions of a patch, about 0.1 us): a unit's
 // staging and barrier, a workgroup's first and last accesses, the slot sums.  Where few
@@ -732,54 +596,63 @@ int ring_rows(int K, long long tiles, const aroam_grid& g, int cus) {
              : 4;
 }
 
-// LDS-ring form (FP64, FP32; see Layout and RingShape): tiles of 16 rows; a chunk is one K-group's
-// run, and a stage unit covers up to kRingStep consecutive row offsets of a chunk, whose K-groups
-// share bundles (a K-group's offset names its row).  No masks: every bundle reaches its tile.
-// `pad` is the geometry of the zero-padded input, which bounds the partial slots.
-int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const PadGeom& pad,
-                      size_t esize, Layout& lay, size_t& bytes) {
+// LDS-ring form (FP64, FP32, BF16; see Layout and RingShape): a chunk is one K-group's run, and a
+// stage unit covers up to kRingStep consecutive row offsets of a chunk, whose K-groups share
+// bundles (a K-group's offset names its row).  With two halves a unit's bundles are ordered by the
+// halves they reach: half 0 alone, half 1 alone, both (d_ucols holds the ends of the first two).
+// `pad` is the geometry of the zero-padded input.
+int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR, const PadGeom& pad,
+                      Layout& lay, UnitPlan& up, size_t& bytes) {
   const aroam_grid& g = m.grid;
-  const int K = m.K, W = 2 * K + 1, TM = kTile, BC = kPatchCols;
-  int cus = 0;
-  AROAM_TRY(device_cus(m, cus));
+  const int K = m.K, W = 2 * K + 1, NH = rs.halves, BC = kPatchCols;
+  const int row_bytes = ring_row_bytes(K, rs.col_bytes);
   lay.G = rs.G;
-  lay.TM = TM;
+  lay.TM = kTile * NH;
   lay.staged = true;
   lay.CH = rs.G;
+  lay.BR = BR;
   lay.BC = BC;
   lay.NCOL = BC + 2 * K;
-  lay.CS = kRingColumnBytes;
+  lay.CS = rs.col_bytes;
   lay.out_len = adjoint ? g.nz : g.nt;
-  lay.n_tiles = (int)ceil_div(lay.out_len, TM);
+  lay.n_tiles = (int)ceil_div(lay.out_len, lay.TM);
   lay.in = pad;
-  const int BR = esize == sizeof(float) ? ring_rows(K, lay.n_tiles, g, cus) : 4;
-  lay.BR = BR;
-  lay.lds_bytes = (size_t)ring_lds_bytes(K, BR);
+  lay.lds_bytes = (size_t)ring_lds_bytes(K, BR, rs.col_bytes);
   const int inner = adjoint ? g.nt : g.nz;
   const int nch = (int)ceil_div(inner, rs.G);
-  const CompatTable table(BankShape{kRingColumnBytes / 16, 0, 1});
+  const CompatTable table(BankShape{rs.col_bytes / 16, 0, 1});
   std::vector<int4> groups, units;
-  std::vector<int> meta, tile_units(lay.n_tiles + 1, 0);
-  std::vector<char> hits((size_t)nch + 1);
-  std::vector<std::vector<int>> cuts(lay.n_tiles);  // a piece may start at any unit
-  std::vector<double> unit_work;                    // bundles of a unit and its own costs
+  std::vector<int2> classes;
+  std::vector<int> meta;
+  std::vector<std::vector<char>> hits(NH, std::vector<char>((size_t)nch + 1));
+  up.tile_units.assign(lay.n_tiles + 1, 0);
+  up.units.resize(lay.n_tiles);
+  up.chunk_starts.resize(lay.n_tiles);
   std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
   std::vector<UnitEntry> lst;
   for (int t = 0; t < lay.n_tiles; ++t) {
-    tile_units[t] = (int)units.size();
+    up.tile_units[t] = (int)units.size();
     for (auto& v : per) v.clear();
     for (int a = 0; a < W; ++a) {
       const int slot = adjoint ? (W - 1 - a) : a;  // input row offset + K
       for (int b = 0; b < W; ++b) {
-        if (!tile_hits(m, adjoint, rs.G, TM, t, a * W + b, hits)) continue;
+        bool any = false;
+        for (int h = 0; h < NH; ++h)
+          any |= tile_hits(m, adjoint, rs.G, kTile, t * NH + h, a * W + b, hits[h]);
+        if (!any) continue;
         const int col = adjoint ? (W - 1 - b) : b;  // input column offset + K
-        for (int c = 0; c < nch; ++c)
-          if (hits[c])
+        for (int c = 0; c < nch; ++c) {
+          int mask = 0;  // the halves the K-group's band reaches
+          for (int h = 0; h < NH; ++h) mask |= hits[h][c] ? 1 << h : 0;
+          if (mask)
             per[(size_t)c * W + slot].push_back(
-                UnitEntry{make_int4(a * W + b, c * rs.G, t, slot), col, 0, 1});
+                UnitEntry{make_int4(a * W + b, c * rs.G, t, slot), col, 0, mask});
+        }
       }
     }
-    for (int c = 0; c < nch; ++c)
+    bool chunk_start = true;
+    for (int c = 0; c < nch; ++c) {
+      if (c % (kStageChunk / rs.G) == 0) chunk_start = true;
       for (int R = 0; R < W;) {
         if (per[(size_t)c * W + R].empty()) {
           ++R;
@@ -787,52 +660,92 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, const P
         }
         // consecutive units step by kRingStep as long as there are K-groups
         for (int R0 = R;; R0 += kRingStep) {
-          lst.clear();
-          for (int r = R0; r < std::min(W, R0 + kRingStep); ++r)
-            lst.insert(lst.end(), per[(size_t)c * W + r].begin(), per[(size_t)c * W + r].end());
+          const int R1 = std::min(W, R0 + kRingStep);
+          bool any = false;
+          for (int r = R0; r < R1; ++r) any |= !per[(size_t)c * W + r].empty();
           R = R0;
-          if (lst.empty()) break;
-          const int first = (int)(groups.size() / kLaneGroups);
-          for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
-            const int row = e.group.x < 0 ? 0 : e.group.w - R0;  // the group's row offset in the unit
-            groups.push_back(make_int4(e.group.x, e.group.y, e.group.z, e.group.x >= 0));
-            meta.push_back(row * ring_row_bytes(K) + e.col * kRingColumnBytes);
+          if (!any) break;
+          const size_t first = groups.size() / kLaneGroups;
+          int2 ends = make_int2(0, 0);
+          double work = 0;
+          for (int mask = 1; mask < 1 << NH; ++mask) {
+            lst.clear();
+            for (int r = R0; r < R1; ++r)
+              for (const UnitEntry& e : per[(size_t)c * W + r])
+                if (e.mask == mask) lst.push_back(e);
+            const size_t before = groups.size() / kLaneGroups;
+            if (!lst.empty())
+              for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
+                const int row = e.group.x < 0 ? 0 : e.group.w - R0;  // its row offset in the unit
+                groups.push_back(make_int4(e.group.x, e.group.y, e.group.z, e.group.x >= 0));
+                meta.push_back(row * row_bytes + e.col * rs.col_bytes);
+              }
+            const size_t after = groups.size() / kLaneGroups;
+            work += (double)(after - before) * __builtin_popcount((unsigned)mask);
+            if (mask == 1) ends.x = (int)after;
+            if (mask == 2) ends.y = (int)after;
           }
-          cuts[t].push_back((int)units.size());
-          units.push_back(make_int4(R0 - K, c * rs.G, first, (int)(groups.size() / kLaneGroups)));
-          unit_work.push_back(units.back().w - units.back().z + kUnitWork);
+          up.units[t].push_back((int)units.size());
+          if (chunk_start) up.chunk_starts[t].push_back((int)units.size());
+          chunk_start = false;
+          units.push_back(make_int4(R0 - K, c * rs.G, (int)first, (int)(groups.size() / kLaneGroups)));
+          classes.push_back(ends);
+          up.work.push_back(work);
         }
       }
+    }
   }
-  tile_units[lay.n_tiles] = (int)units.size();
+  up.tile_units[lay.n_tiles] = (int)units.size();
   lay.n_units = (long long)units.size();
   lay.n_bundles = (long long)groups.size() / kLaneGroups;
-  // MACs the kernel issues: per bundle 16 rows x 4 G entries for every computed position, which
-  // leaves out patches that have no input row inside the scan and the second 16-position tile
-  // column of a patch that holds at most 16 scan columns
+  // MACs the kernel issues: per bundle half 16 rows x 4 G entries for every computed position,
+  // which leaves out patches that have no input row inside the scan and the second 16-position
+  // tile column of a patch that holds at most 16 scan columns
   const long long cols = g.nx % BC > 0 && g.nx % BC <= 16 ? (long long)(g.nx / BC) * BC + 16
                                                           : round_up(g.nx, BC);
   lay.mac_exec = 0;
-  for (const int4& u : units) {
+  for (size_t u = 0; u < units.size(); ++u) {
     long long rows = 0;
     for (int o = 0; o < g.ny; o += BR)
-      rows += o + u.x + BR + kRingStep - 1 > 0 && o + u.x < g.ny ? BR : 0;
-    lay.mac_exec += (u.w - u.z) * rows;
+      rows += o + units[u].x + BR + kRingStep - 1 > 0 && o + units[u].x < g.ny ? BR : 0;
+    lay.mac_exec += (long long)up.work[u] * rows;
   }
-  lay.mac_exec *= (long long)kLaneGroups * rs.G * TM * cols;
+  lay.mac_exec *= (long long)kLaneGroups * rs.G * kTile * cols;
   AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
               "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
   AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
+  if (NH > 1) AROAM_TRY(alloc_copy(&lay.d_ucols, classes, bytes));
   AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
+  return AROAM_OK;
+}
+
+// The FP64 or FP32 layout of one direction and its launch.
+int build_plain_layout(const Model& m, bool adjoint, const RingShape& rs, const PadGeom& pad,
+                       size_t esize, Layout& lay, size_t& bytes) {
+  int cus = 0;
+  AROAM_TRY(device_cus(m, cus));
+  const int tiles = (int)ceil_div(adjoint ? m.grid.nz : m.grid.nt, kTile);
+  const int BR = esize == sizeof(float) ? ring_rows(m.K, tiles, m.grid, cus) : 4;
+  UnitPlan up;
+  AROAM_TRY(build_ring_layout(m, adjoint, rs, BR, pad, lay, up, bytes));
+  for (double& w : up.work) w += kUnitWork;
   return set_plan(lay,
-                  plan_launch(tile_units, cuts, unit_work, lay.n_patches, (BR == 8 ? 2 : 3) * cus,
-                              /*allow_cut=*/true,
-                              (double)TM * BR * BC * esize,
+                  plan_launch(up.tile_units, up.units, up.work, lay.n_patches,
+                              (BR == 8 ? 2 : 3) * cus, /*allow_cut=*/true,
+                              (double)lay.TM * lay.BR * lay.BC * esize,
                               std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64,
                               kRingCosts),
                   bytes);
+}
+
+int build_bf16_layout(const Model& m, bool adjoint, Layout& lay, size_t& bytes) {
+  const PadGeom pad =
+      pad_geom(m.grid, adjoint ? m.grid.nt : m.grid.nz, kPatchRows, kPatchCols, kStageChunk);
+  UnitPlan up;
+  AROAM_TRY(build_ring_layout(m, adjoint, kRingBF16, kPatchRows, pad, lay, up, bytes));
+  return plan_staged(m, adjoint, lay, up, kBf16Unit, kBf16Costs, 2.0 * lay.in.elems(), bytes);
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
@@ -1402,8 +1315,8 @@ int pack_fp(Model& m, hipStream_t st, size_t& bytes) {
     const int L = adj ? m.grid.nt : m.grid.nz;
     Layout& r64 = adj ? m.r64a : m.r64f;
     Layout& r32 = adj ? m.r32a : m.r32f;
-    AROAM_TRY(build_ring_layout(m, adj, kRingF64, pad_geom(m.grid, L), sizeof(double), r64, bytes));
-    AROAM_TRY(build_ring_layout(m, adj, kRingF32,
+    AROAM_TRY(build_plain_layout(m, adj, kRingF64, pad_geom(m.grid, L), sizeof(double), r64, bytes));
+    AROAM_TRY(build_plain_layout(m, adj, kRingF32,
                                 pad_geom(m.grid, L, kPatchRows, kPatchCols, 16),
                                 sizeof(float), r32, bytes));
     Pack* pack = adj ? m.adj_pack : m.fwd_pack;
@@ -1611,11 +1524,8 @@ int finish_model(Model* m, int rc, unsigned mask, hipStream_t st, Model** out) {
     const bool want8 = (mask & (1u << AROAM_BF16)) != 0;
     size_t bytes = 0;
     if (want8) {
-      rc = build_staged_layout(*m, false, 8, kTileRows8, 32, kPatchRows, kPatchCols, 2, m->s8f,
-                               bytes);
-      if (!rc)
-        rc = build_staged_layout(*m, true, 8, kTileRows8, 32, kPatchRows, kPatchCols, 2, m->s8a,
-                                 bytes);
+      rc = build_bf16_layout(*m, false, m->s8f, bytes);
+      if (!rc) rc = build_bf16_layout(*m, true, m->s8a, bytes);
     }
     if (!rc && (mask & (1u << AROAM_BF16))) {
       rc = pack_dtype<uint16_t>(*m, m->s8f, false, m->fwd_pack[AROAM_BF16], st, bytes);
