@@ -66,97 +66,6 @@ __global__ __launch_bounds__(256) void k_stage_bf16(const float* __restrict__ in
   out[((long long)c * nyp + row) * nxp + col] = w;
 }
 
-struct StagedArgs {
-  const int4* pieces;      // (tile, unit begin, unit end, partial slot or -1)
-  const int2* tile_split;  // per tile: (pieces, first slot)
-  float* partial;          // [slot][patch][position][TM rows] partial sums of cut tiles
-  int n_patches;
-  const int4* units;  // (row offset, chunk start, bundle begin, bundle end)
-  const int2* urows;  // padded patch rows [lo, hi) each unit loads into the LDS ring
-  const int* meta;
-  int out_len, nx, ny, K, nxp, Lp;
-  int ncc;            // patch column chunks
-  int NCOL, CS;
-};
-
-// Global source and LDS destination of flat stage vector idx of a unit that loads padded
-// patch rows from `lo`, for the chunk starting at inner entry e0.
-struct StageAddr {
-  long long src;
-  int lds;
-};
-
-// RS: slots of the LDS row ring (padded row G lives in slot G mod RS).
-template <int RS>
-__device__ __forceinline__ StageAddr stage_addr(const StagedArgs& a, int lo, int e0, int idx,
-                                                int py0, int px0, int rowvec, int nvec, int vec) {
-  const int G = lo + idx / rowvec;
-  const int rem = idx % rowvec;
-  const int c = rem / nvec, v = rem % nvec;
-  StageAddr r;
-  r.lds = ((G % RS) * a.NCOL + c) * a.CS + v * vec;
-  r.src = ((long long)(py0 + G) * a.nxp + (px0 + c)) * a.Lp + e0 + v * vec;
-  return r;
-}
-
-// Padded patch rows [lo, hi) that unit u loads; the first unit of a piece loads all it reads.
-__device__ __forceinline__ int2 unit_rows(const StagedArgs& a, int u, bool first) {
-  const int R = a.units[u].x + a.K;
-  return first ? make_int2(R, R + kPatchRows) : a.urows[u];
-}
-
-// Fetch up to 256 * PF stage vectors of unit u (rows Rr) into registers (the rest is loaded when
-// the unit's rows are written); pf_off = -1 marks an unused slot.
-template <typename T, int RS, int PF>
-__device__ __forceinline__ void stage_prefetch(const StagedArgs& a, const T* __restrict__ in,
-                                               int u, int2 Rr, int py0, int px0, int rowvec,
-                                               int nvec, u32x4 (&pf)[PF], int (&pf_off)[PF]) {
-  constexpr int VEC = 16 / sizeof(T);
-  const int4 U = a.units[u];
-  const int nv = (Rr.y - Rr.x) * rowvec;
-#pragma unroll
-  for (int i = 0; i < PF; ++i) {
-    const int idx = threadIdx.x + 256 * i;
-    pf_off[i] = -1;
-    if (idx < nv) {
-      const StageAddr sa = stage_addr<RS>(a, Rr.x, U.y, idx, py0, px0, rowvec, nvec, VEC);
-      pf_off[i] = sa.lds;
-      pf[i] = *reinterpret_cast<const u32x4*>(in + sa.src);
-    }
-  }
-}
-
-// Write the rows unit u adds to the LDS ring: the prefetched vectors, then the rest (a full
-// ring reload) with four loads in flight per thread.
-template <typename T, int RS, int PF>
-__device__ __forceinline__ void stage_rows(const StagedArgs& a, const T* __restrict__ in, T* lds,
-                                           int u, int2 Rr, int py0, int px0, int rowvec, int nvec,
-                                           const u32x4 (&pf)[PF], const int (&pf_off)[PF]) {
-  constexpr int VEC = 16 / sizeof(T);
-#pragma unroll
-  for (int i = 0; i < PF; ++i)
-    if (pf_off[i] >= 0) *reinterpret_cast<u32x4*>(lds + pf_off[i]) = pf[i];
-  const int4 U = a.units[u];
-  const int nv = (Rr.y - Rr.x) * rowvec;
-  for (int base = 256 * PF; base < nv; base += 256 * 4) {
-    u32x4 tmp[4];
-    int off[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = base + threadIdx.x + 256 * i;
-      off[i] = -1;
-      if (idx < nv) {
-        const StageAddr sa = stage_addr<RS>(a, Rr.x, U.y, idx, py0, px0, rowvec, nvec, VEC);
-        off[i] = sa.lds;
-        tmp[i] = *reinterpret_cast<const u32x4*>(in + sa.src);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (off[i] >= 0) *reinterpret_cast<u32x4*>(lds + off[i]) = tmp[i];
-  }
-}
-
 // LDS bytes of the FP8 kernel's final sums: S tiles of MH halves per wave, four waves.
 constexpr size_t red_bytes(int S, int MH) { return (size_t)4 * S * MH * 64 * 16; }
 
@@ -775,20 +684,21 @@ __global__ __launch_bounds__(64) void k_stage_fp8(const float* __restrict__ in,
 }
 
 struct Fp8Args {
-  const int4* pieces;
-  const int2* tile_split;
-  float* partial;
+  const int4* pieces;  // (tile, unit begin, unit end, partial slot or -1)
+  float* partial;      // [slot][patch][position][TM rows] partial sums of cut tiles
   int n_patches;
-  const int4* units;
-  const int2* urows;
-  const u32x4* rec;   // per bundle and lane group: LDS offsets of its 4 K-groups (16 bits
-                      // each), the E8M0 scale bytes of its block for the two halves; word 3
-                      // of lane group 0: the 16-row halves the bundle's K-groups reach
-  const int* xexp;    // per chunk of the operand: E8M0 scale byte
-  int out_len, nx, ny, K, nxp, Lp;
-  int ncc;
+  const int4* units;   // (row offset, chunk start, bundle begin, bundle end)
+  const int2* classes; // per unit: the end of its bundles of half 0 alone and of half 1 alone
+  const u32x4* rec;    // per bundle and lane group: LDS offsets of its 4 K-groups within a row (16
+                       // bits each), the E8M0 scale bytes of its block for the two halves and, from
+                       // bit 16, the K-groups' row offset in the unit
+  const int* xexp;     // per scale chunk of the operand: E8M0 scale byte
+  int out_len, nx, ny, K, nxp, nyp, Lp;
+  int ncc;             // patch columns
   int NCOL, CS;
 };
+
+constexpr int kFp8Vecs = kFp8Chunk / 16;  // staged vectors per column
 
 // Table operand of one FP8 bundle for one lane: 32 bytes per half.
 struct F8Frag {
@@ -830,24 +740,28 @@ __device__ __forceinline__ X8Offs x8_offsets(uint32_t w) {
   return X8Offs{{(int)(r0 & 0xffff), (int)(r0 >> 16), (int)(r1 & 0xffff), (int)(r1 >> 16)}};
 }
 
-// Position fragments of one FP8 bundle for tiles [t0, t0 + NX) of this lane: for each of the
-// lane group's four K-groups, 8 bytes of the lane's position from the LDS.  Tile t sits at row
-// base rb[t / TPR] plus column offset (t % TPR) * cstep.  The step is a run-time value: as an
-// immediate, the compiler pairs the reads of neighbouring tiles into one instruction whose
-// registers then have to be moved into each MFMA's operand order.
-template <int TPR, int NX, int NR>
-__device__ __forceinline__ void read_x8(const uint8_t* lds, const int (&rb)[NR], int cstep, int t0,
-                                         const X8Offs& o, u32x4 (&x)[NX][2]) {
+// Position fragments of one FP8 bundle for the TPR tiles of row r of the wave's rows: for each of
+// the lane group's four K-groups, 8 bytes of the lane's position from the LDS.  The K-groups' first
+// row is at `first`; rows wrap into the ring of `ring` bytes (the subtraction underflows to a larger
+// value where there is nothing to wrap).  The reads are volatile: otherwise the compiler pairs the
+// reads of neighbouring tiles into one instruction whose registers then have to be moved into
+// each MFMA's operand order (or, with the tiles' distance as a run-time value, needs an addition
+// for each read).
+typedef const volatile __attribute__((address_space(3))) u32x2 LdsPair;
+
+template <int TPR>
+__device__ __forceinline__ void read_x8(const uint8_t* lds, unsigned first, unsigned row_bytes,
+                                        unsigned ring, int r, const X8Offs& o, u32x4 (&x)[TPR][2]) {
+  const unsigned q = first + r * row_bytes;
+  const uint8_t* row = lds + min(q, q - ring);
 #pragma unroll
-  for (int i = 0; i < NX; ++i) {
-    const int t = t0 + i;
-    const uint8_t* p = lds + rb[t / TPR] + (t % TPR) * cstep;
-    const u32x2 q0 = *reinterpret_cast<const u32x2*>(p + o.o[0]);
-    const u32x2 q1 = *reinterpret_cast<const u32x2*>(p + o.o[1]);
-    const u32x2 q2 = *reinterpret_cast<const u32x2*>(p + o.o[2]);
-    const u32x2 q3 = *reinterpret_cast<const u32x2*>(p + o.o[3]);
-    x[i][0] = u32x4{q0.x, q0.y, q1.x, q1.y};
-    x[i][1] = u32x4{q2.x, q2.y, q3.x, q3.y};
+  for (int t = 0; t < TPR; ++t) {
+    u32x2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      v[k] = *((LdsPair*)(row + o.o[k]) + t * 16 * kRingColumnBytes / 8);
+    x[t][0] = u32x4{v[0].x, v[0].y, v[1].x, v[1].y};
+    x[t][1] = u32x4{v[2].x, v[2].y, v[3].x, v[3].y};
   }
 }
 
@@ -869,19 +783,24 @@ __device__ __forceinline__ void fp8_mma_h(const F8Frag& f, int sc, int xs, int t
   }
 }
 
-// FP8 split kernel shape: waves sharing a unit's bundle stream, position-fragment read phases
-// per bundle, table-fragment ring depth.
-constexpr int kSplit8 = 4, kPhases8 = 4, kRing8 = 1;
+constexpr int kSplit8 = 4;  // waves that share a unit's bundles
 
-// LDS-staged FP8 kernel: the BF16 split kernel's workgroup shape, LDS row ring, unit order and
-// bundle split (4 / S row groups of the BR x BC patch; the S waves of a row group take every
-// S-th bundle of each stage unit; the S partial sums of a position are added in wave order
-// through the LDS at the end), with bundles of 16 K-groups: per reached 16-row half and
-// position tile one block-scaled MFMA of K = 128.  Lane (n, g) reads, for each of its lane
-// group's four K-groups, 8 bytes of position n from the LDS (the K-group's column and run) and
-// 32 bytes of table row n per half.  An FP8 position fragment takes 8 VGPRs, so a wave reads
-// its NT fragments in XP phases; the table ring is PD bundles deep.
-template <int BR, int BC, int S, int XP, int PD>
+// LDS-staged FP8 kernel: the ring kernel's units of kRingStep row offsets (of chunks of 32 entries)
+// and order of bundles (half 0 alone, half 1 alone, both), with bundles of 16 K-groups: per reached
+// 16-row half and position tile one block-scaled MFMA of K = 128.  The waves form 4 / S row groups
+// of the BR x BC patch; the S waves of a row group take every S-th bundle of each stage unit, and
+// the S partial sums of a position are added in wave order through the LDS at the end.  Lane (n, g)
+// reads, for each of its lane group's four K-groups, 8 bytes of position n from the LDS (the
+// K-group's row, column and run) and 32 bytes of table row n per half.
+//
+// What bounds it is latency at two waves per SIMD (the accumulators take half the registers).  With
+// one row offset to a unit (of 64 entries) a unit had four bundles or so, which four waves share
+// unevenly and with a barrier each; with a test of the reached halves per bundle the compiler
+// waits for all reads of a row before its MFMAs.  Units of four row offsets, runs of bundles of the
+// same halves, a row's fragments read while the row before multiplies and a staging without
+// registers to spill: 400 x 400 forward 12.2 -> 10.7 ms, 200 x 200 x 128 (K 20) 741 -> 599 us,
+// its adjoint 786 -> 663, 256 x 256 x 64 (K 10) 280 -> 217.
+template <int BR, int BC, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_fp8s(
     const uint8_t* __restrict__ pack, const uint8_t* __restrict__ in, float* __restrict__ out,
     Fp8Args a) {
@@ -891,97 +810,129 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int P = 4 / S;
   constexpr int RW = BR / P;
   constexpr int NT = RW * TPR;
-  static_assert(4 % S == 0 && BR % P == 0 && NT % S == 0 && NT % XP == 0, "split shape");
-  constexpr int NX = NT / XP;          // tiles per position-fragment read phase
-  constexpr int PF = 2;
-  constexpr int RQ = 2;                // record ring depth (a multiple of PD; 4 measured slower)
+  static_assert(4 % S == 0 && BR % P == 0 && NT % S == 0 && RW % 2 == 0, "split shape");
+  constexpr int UR = BR + kRingStep - 1, RS = UR + kRingStep;  // rows of a unit, of the ring
   constexpr int MH = 2;
   const int4 piece = a.pieces[blockIdx.y];
   const int tile = piece.x;
   const int py0 = (blockIdx.x / a.ncc) * BR, px0 = (blockIdx.x % a.ncc) * BC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int grp = wave / S, sw = wave % S;
   const int n = lane % 16, g = lane / 16;
-  constexpr int nvec = 4;
-  const int rowvec = a.NCOL * nvec;
-  StagedArgs sa;
-  sa.units = a.units;
-  sa.K = a.K;
-  sa.urows = a.urows;
-  sa.NCOL = a.NCOL;
-  sa.CS = a.CS;
-  sa.nxp = a.nxp;
-  sa.Lp = a.Lp;
+  const int rowvec = a.NCOL * kFp8Vecs;
+  const unsigned row_bytes = a.NCOL * a.CS;
   floatx4 acc[MH][NT];
 #pragma unroll
   for (int h = 0; h < MH; ++h)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[h][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // Write the rows that unit U adds, padded patch rows [lo, U.x + K + UR), to the ring.  A wave takes
+  // every fourth row, 64 vectors at a time, so that rows are uniform and a lane's offsets within
+  // them fixed.  Nothing is fetched ahead: the registers that takes are spilled (400 x 400 forward
+  // 11.1 ms with one vector ahead, 11.8 with three).
+  const unsigned lane_lds = lane / kFp8Vecs * kRingColumnBytes + lane % kFp8Vecs * 16;
+  const unsigned lane_in = lane / kFp8Vecs * a.Lp + lane % kFp8Vecs * 16;
+  constexpr int kCols = 64 / kFp8Vecs;  // columns of 64 vectors
+  auto stage = [&](const int4& U, int lo) {
+    for (int G = lo + wave; G < U.x + a.K + UR; G += 4) {
+      uint8_t* dst = lds + G % RS * row_bytes + lane_lds;
+      // rows past the last padded one belong to row offsets without K-groups
+      const uint8_t* row =
+          in + ((long long)min(py0 + G, a.nyp - 1) * a.nxp + px0) * a.Lp + U.y;
+      for (int i0 = 0; 64 * i0 < rowvec; i0 += 4) {
+        u32x4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (lane + 64 * (i0 + i) < rowvec)
+            v[i] = *reinterpret_cast<const u32x4*>(
+                row + (lane_in + (unsigned)((i0 + i) * kCols * a.Lp)));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (lane + 64 * (i0 + i) < rowvec)
+            *reinterpret_cast<u32x4*>(dst + (i0 + i) * kCols * kRingColumnBytes) = v[i];
+      }
+    }
+  };
   const int u0 = piece.y, u1 = piece.z;
   if (u0 < u1) {
-    constexpr int RS = BR + 1;
-    u32x4 pf[PF];
-    int pf_off[PF];
-    F8Frag ring[PD];
-    uint32_t rq[RQ];
-    {
-      const int4 U = a.units[u0];
-#pragma unroll
-      for (int j = 0; j < PD; ++j) load_f8(pack, min(U.z + sw + S * j, U.w - 1), lane, ring[j]);
-#pragma unroll
-      for (int j = 0; j < RQ; ++j) rq[j] = load_rec8(a, min(U.z + sw + S * j, U.w - 1), g, lane);
-      const int2 rows = unit_rows(sa, u0, true);
-      stage_prefetch<uint8_t, RS, PF>(sa, in, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
-      stage_rows<uint8_t, RS, PF>(sa, in, lds, u0, rows, py0, px0, rowvec, nvec, pf, pf_off);
-      __syncthreads();
-      if (u0 + 1 < u1)
-        stage_prefetch<uint8_t, RS, PF>(sa, in, u0 + 1, unit_rows(sa, u0 + 1, false), py0, px0, rowvec,
-                                    nvec, pf, pf_off);
-    }
+    // Two bundles of the wave: table fragments and record words.
+    struct Bundle {
+      F8Frag f;
+      uint32_t w;
+    };
+    Bundle r0, r1;
+    auto load = [&](Bundle& r, int b) {
+      load_f8(pack, b, lane, r.f);
+      r.w = load_rec8(a, b, g, lane);
+    };
+    int4 U = a.units[u0];
+    load(r0, min(U.z + sw, U.w - 1));
+    load(r1, min(U.z + sw + S, U.w - 1));
+    stage(U, U.x + a.K);
+    __syncthreads();
     for (int u = u0; u < u1; ++u) {
-      const int4 U = a.units[u];
-      const int xs = a.xexp[U.y / 64];
-      const int R = U.x + a.K;
-      int rb[RW];  // LDS base of this lane's position in each of the wave's rows
+      const int4 Un = a.units[min(u + 1, u1 - 1)];
+      const int2 C = a.classes[u];
+      // rows the next unit finds in the ring: those of this unit, in the same chunk
+      const int lo = Un.y == U.y && Un.x < U.x + UR ? U.x + a.K + UR : Un.x + a.K;
+      const int xs = a.xexp[U.y / kFp8ScaleChunk];
+      const unsigned s0 = (grp * RW + U.x + a.K) % RS * row_bytes + n * kRingColumnBytes;
+      const unsigned ring = RS * row_bytes;
+      int b = U.z + sw;
+      if (b < U.w) {
+        // The fragments of a row are read while the row before multiplies (the barriers keep the
+        // compiler from moving the reads next to their use).
+        u32x4 x[2][TPR][2];
+        X8Offs o = x8_offsets(r0.w);
+        int sc = (int)rec8_word<2>(r0.w);
+        unsigned first = s0 + ((unsigned)sc >> 16) * row_bytes;
+        read_x8<TPR>(lds, first, row_bytes, ring, 0, o, x[0]);
+        // bundle b, of the halves in MASK; `next` holds the wave's next one
+        auto body = [&](auto mask, Bundle& r, const Bundle& next) {
+          constexpr int MASK = decltype(mask)::value;
+          int scn = 0;
 #pragma unroll
-      for (int r = 0; r < RW; ++r) rb[r] = (((grp * RW + r + R) % RS) * a.NCOL + n) * a.CS;
-      const int cstep = 16 * a.CS;
-      for (int b0 = U.z + sw; b0 < U.w; b0 += S * RQ) {
-#pragma unroll
-        for (int j = 0; j < RQ; ++j) {
-          const int b = b0 + S * j;
-          const int sc = (int)rec8_word<2>(rq[j]);
-          const int hm = b < U.w ? __builtin_amdgcn_readfirstlane((int)rec8_word<3>(rq[j])) : 0;
-          if (hm) {
-            const X8Offs o = x8_offsets(rq[j]);
-#pragma unroll
-            for (int ph = 0; ph < XP; ++ph) {
-              u32x4 x[NX][2];
-              read_x8<TPR, NX>(lds, rb, cstep, ph * NX, o, x);
-              if (hm & 1) fp8_mma_h<0, NT, NX>(ring[j % PD], sc, xs, ph * NX, x, acc);
-              if (hm & 2) fp8_mma_h<1, NT, NX>(ring[j % PD], sc, xs, ph * NX, x, acc);
+          for (int p = 0; p < RW; ++p) {
+            if (p + 1 == RW) {
+              o = x8_offsets(next.w);
+              scn = (int)rec8_word<2>(next.w);
+              first = s0 + ((unsigned)scn >> 16) * row_bytes;
             }
+            read_x8<TPR>(lds, first, row_bytes, ring, (p + 1) % RW, o, x[(p + 1) % 2]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (MASK & 1) fp8_mma_h<0, NT, TPR>(r.f, sc, xs, p * TPR, x[p % 2], acc);
+            if constexpr (MASK & 2) fp8_mma_h<1, NT, TPR>(r.f, sc, xs, p * TPR, x[p % 2], acc);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          load_f8(pack, min(b + S * PD, U.w - 1), lane, ring[j % PD]);
-          rq[j] = load_rec8(a, min(b + S * RQ, U.w - 1), g, lane);
-        }
+          sc = scn;
+          b += S;
+        };
+        // bundles of the same halves in turn; r0 holds the first of each run
+        auto run = [&](auto mask, int end) {
+          while (b + S < end) {
+            body(mask, r0, r1);
+            load(r0, min(b + S, U.w - 1));
+            body(mask, r1, r0);
+            load(r1, min(b + S, U.w - 1));
+          }
+          if (b < end) {
+            body(mask, r0, r1);
+            r0 = r1;
+            load(r1, min(b + S, U.w - 1));
+          }
+        };
+        run(std::integral_constant<int, 1>{}, C.x);
+        run(std::integral_constant<int, 2>{}, C.y);
+        run(std::integral_constant<int, 3>{}, U.w);
       }
       if (u + 1 < u1) {
-        const int4 Un = a.units[u + 1];
-        const int2 Rn = a.urows[u + 1];
-#pragma unroll
-        for (int j = 0; j < PD; ++j)
-          load_f8(pack, min(Un.z + sw + S * j, Un.w - 1), lane, ring[j]);
-#pragma unroll
-        for (int j = 0; j < RQ; ++j)
-          rq[j] = load_rec8(a, min(Un.z + sw + S * j, Un.w - 1), g, lane);
-        const bool free_slot = Rn.y - Rn.x == 1 && Rn.x == R + BR;
-        if (!free_slot) __syncthreads();
-        stage_rows<uint8_t, RS, PF>(sa, in, lds, u + 1, Rn, py0, px0, rowvec, nvec, pf, pf_off);
+        load(r0, min(Un.z + sw, Un.w - 1));
+        load(r1, min(Un.z + sw + S, Un.w - 1));
+        // the next row offsets' new rows go to the free slots while other waves still read this unit
+        if (!(Un.x == U.x + kRingStep && Un.y == U.y)) __syncthreads();
+        stage(Un, lo);
         __syncthreads();
-        if (u + 2 < u1)
-          stage_prefetch<uint8_t, RS, PF>(sa, in, u + 2, unit_rows(sa, u + 2, false), py0, px0, rowvec,
-                                      nvec, pf, pf_off);
+        U = Un;
       }
     }
   }
@@ -1063,7 +1014,7 @@ StageParts stage_parts(const Model& m, bool adjoint, int dtype) {
     p.partial = (size_t)lay.n_slots * lay.n_patches * lay.TM * lay.BR * lay.BC *
                 (dtype == AROAM_FP64 ? sizeof(double) : sizeof(float));
   if (dtype == AROAM_FP8E4M3) {
-    p.chunks = (int)ceil_div(lay.in.L, 64);
+    p.chunks = (int)ceil_div(lay.in.L, kFp8ScaleChunk);
     p.scales = (size_t)round_up((size_t)p.chunks * (kAmaxParts + 2) * 4, 256);
   }
   return p;
@@ -1146,11 +1097,13 @@ namespace {
 // and the slot sums of cut tiles.
 int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* in, void* buf,
                const StageParts& sp, void* out, hipStream_t st) {
-  auto kern = k_apply_fp8s<kPatchRows, kPatchCols, kSplit8, kPhases8, kRing8>;
+  auto kern = k_apply_fp8s<kPatchRows, kPatchCols, kSplit8>;
   static std::atomic<unsigned long long> attr_set{0};
   AROAM_TRY(allow_full_lds(kern, attr_set));
-  AROAM_CHECK(lay.TM == kTileRows8 && lay.CH == 64 && lay.CS == kColumnBytes, AROAM_EINVAL,
-              "FP8 layout shape mismatch");
+  AROAM_CHECK(lay.TM == kTileRows8 && lay.CH == kFp8Chunk && lay.CS == kRingColumnBytes &&
+                  lay.NCOL == kPatchCols + 2 * lay.in.K &&
+                  lay.in.nxp >= (int)round_up(lay.in.nx, kPatchCols) + 2 * lay.in.K,
+              AROAM_EINVAL, "FP8 layout shape mismatch");
   const PadGeom& pg = lay.in;
   char* base = static_cast<char*>(buf);
   uint8_t* staged = reinterpret_cast<uint8_t*>(base);
@@ -1169,11 +1122,10 @@ int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* i
                      (const float*)xinv, pg.K, pg.nx, pg.ny, pg.nxp, pg.L, pg.Lp, vec4);
   Fp8Args a;
   a.pieces = lay.d_pieces;
-  a.tile_split = lay.d_tile_split;
   a.partial = partial;
   a.n_patches = lay.n_patches;
   a.units = lay.d_units;
-  a.urows = lay.d_ucols;
+  a.classes = lay.d_ucols;
   a.rec = reinterpret_cast<const u32x4*>(lay.d_meta);
   a.xexp = xexp;
   a.out_len = lay.out_len;
@@ -1181,6 +1133,7 @@ int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* i
   a.ny = pg.ny;
   a.K = pg.K;
   a.nxp = pg.nxp;
+  a.nyp = pg.nyp;
   a.Lp = pg.Lp;
   a.ncc = (int)ceil_div(pg.nx, kPatchCols);
   a.NCOL = lay.NCOL;

@@ -141,6 +141,10 @@ constexpr int kFp8Lane[4][4] = {{0, 0, 1, 1}, {2, 2, 3, 3}, {0, 0, 1, 1}, {2, 2,
 constexpr int kFp8Slot[4][4] = {{0, 1, 0, 1}, {0, 1, 0, 1}, {2, 3, 2, 3}, {2, 3, 2, 3}};
 constexpr int kFp8ScaleLane[4] = {0, 1, 2, 3};
 
+// The FP8 operand takes one power-of-two scale per kFp8ScaleChunk entries of its fast axis; a stage
+// unit holds kFp8Chunk of them.
+constexpr int kFp8ScaleChunk = 64, kFp8Chunk = 32;
+
 struct Model {
   aroam_sensor sensor{};
   aroam_grid grid{};

@@ -571,8 +571,8 @@ int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, d
 // K 20: BF16 172 -> 126 us, FP8 216 -> 151 us).  Larger or smaller costs, and three or four
 // workgroups per CU in the simulation, measured slower.
 // A BF16 unit (four row offsets) costs 30: with 16 the batch of three served scans takes 350 us
-// instead of 332, with 44 the 200 x 200 x 128 forward 911 instead of 862.
-constexpr double kBf16Unit = 30, kFp8Unit = 8;
+// instead of 332, with 44 the 200 x 200 x 128 forward 911 instead of 862.  FP8 units: 8 and 30 within 1 % of 16.
+constexpr double kBf16Unit = 30, kFp8Unit = 16;
 constexpr PlanCosts kBf16Costs{60, 200, 6}, kFp8Costs{30, 60, 3};
 
 // Costs of a ring launch in bundles (of the 128 positions of a patch, about 0.1 us): a unit's
@@ -763,7 +763,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
                      size_t& bytes) {
   const aroam_grid& g = m.grid;
   const int K = m.K, W = 2 * K + 1, nz = g.nz, nt = g.nt;
-  const int G = 8, TM = kTileRows8, CH = kChunkBytes, BR = kPatchRows, BC = kPatchCols;
+  const int G = 8, TM = kTileRows8, CH = kFp8Chunk, BR = kPatchRows, BC = kPatchCols;
   const int nblk = (int)ceil_div(nz, 16);
   lay.G = G;
   lay.TM = TM;
@@ -772,11 +772,11 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   lay.BR = BR;
   lay.BC = BC;
   lay.NCOL = BC + 2 * K;
-  lay.CS = kColumnBytes;  // one byte per entry
+  lay.CS = kRingColumnBytes;  // one byte per entry
   lay.out_len = adjoint ? nz : nt;
   lay.n_tiles = (int)ceil_div(lay.out_len, TM);
-  lay.in = pad_geom(g, adjoint ? nt : nz, BR, BC, CH);
-  lay.lds_bytes = (size_t)(BR + 1) * lay.NCOL * lay.CS;
+  lay.in = pad_geom(g, adjoint ? nt : nz, BR, BC, kFp8ScaleChunk);
+  lay.lds_bytes = (size_t)(BR + 2 * kRingStep - 1) * lay.NCOL * lay.CS;
   AROAM_CHECK((long long)lay.lds_bytes == staged_lds_bytes(K), AROAM_EINVAL,
               "FP8 layout shape differs from the LDS stage's");
   const int inner = adjoint ? nt : nz;
@@ -790,7 +790,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
     return std::max(0, std::min(254, e - 1 + 127));
   };
   std::vector<int4> groups, units;  // groups in operand position order: [bundle][lane][slot]
-  std::vector<int2> urows;
+  std::vector<int2> classes;
   std::vector<int> rec, bmask, tile_units(lay.n_tiles + 1, 0);
   std::vector<std::vector<char>> hits(W, std::vector<char>((size_t)nq + 1));
   std::vector<std::vector<char>> hhits((size_t)W * 2, std::vector<char>((size_t)nq + 1));
@@ -832,85 +832,113 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         }
       }
     }
+    bool chunk_start = true;
     for (int c = 0; c < nch; ++c) {
-      int prevR = -1;
-      for (int R = 0; R < W; ++R) {
-        auto& lst = per[(size_t)c * W + R];
-        if (lst.empty()) continue;
+      if (c % (kFp8ScaleChunk / CH) == 0) chunk_start = true;
+      for (int R = 0; R < W;) {
+        if (per[(size_t)c * W + R].empty()) {
+          ++R;
+          continue;
+        }
+        // a unit takes kRingStep row offsets, whichever of them have K-groups
         up.units[t].push_back((int)units.size());
-        if (prevR < 0) up.chunk_starts[t].push_back((int)units.size());
+        if (chunk_start) up.chunk_starts[t].push_back((int)units.size());
+        chunk_start = false;
         const int first_bundle = (int)(groups.size() / 16);
-        // scale blocks: K-groups of equal key, four at a time (a short block is padded with
-        // null K-groups, whose table entries are zero).  A block's K-groups 0, 1 and 2, 3 sit
-        // in two lane groups at the same two 8-byte slots, and the 32 lanes of a pass of an
+        // scale blocks: K-groups of equal key in one row, four at a time (a short block is padded
+        // with null K-groups, whose table entries are zero).  A block's K-groups 0, 1 and 2, 3
+        // sit in two lane groups at the same two 8-byte slots, and the 32 lanes of a pass of an
         // 8-byte LDS read hit distinct banks only when those two lane groups' runs (8-byte
-        // steps within a column of 80 bytes) differ in parity: a block takes two K-groups of
-        // even and two of odd run where the class has them, evens first.
-        std::stable_sort(lst.begin(), lst.end(),
-                         [](const Entry& x, const Entry& y) { return fp8_key_less(x.key, y.key); });
-        std::vector<std::vector<Entry>> blocks;
-        for (size_t i = 0; i < lst.size();) {
-          size_t j = i;
-          std::vector<Entry> ev, od;
-          while (j < lst.size() && !fp8_key_less(lst[i].key, lst[j].key) &&
-                 !fp8_key_less(lst[j].key, lst[i].key)) {
-            ((lst[j].off / G) % 2 ? od : ev).push_back(lst[j]);
-            ++j;
-          }
-          const Entry null_even{null_group, 0, lst[i].key}, null_odd{null_group, G, lst[i].key};
-          size_t a = 0, b = 0;
-          while (a < ev.size() || b < od.size()) {
-            std::vector<Entry> blk;
-            // two evens then two odds when both are left, else four of what is left
-            const bool both = ev.size() - a >= 2 && od.size() - b >= 2;
-            for (int k = 0; k < 4; ++k) {
-              const bool want_even = both ? k < 2 : (a < ev.size());
-              if (want_even && a < ev.size()) blk.push_back(ev[a++]);
-              else if (!want_even && b < od.size()) blk.push_back(od[b++]);
-              else if (a < ev.size()) blk.push_back(ev[a++]);
-              else if (b < od.size()) blk.push_back(od[b++]);
-              else blk.push_back(k < 2 ? null_even : null_odd);
+        // steps within a column of 48 bytes) differ in parity: a block takes two K-groups of
+        // even and two of odd run where the class has them, evens first.  Two blocks of a row
+        // share two lane groups (pairs below), so that a lane reads one row.
+        std::vector<std::vector<Entry>> pairs[4];  // by half mask: eight K-groups, two blocks
+        for (int r = R; r < std::min(W, R + kRingStep); ++r) {
+          auto& lst = per[(size_t)c * W + r];
+          std::stable_sort(lst.begin(), lst.end(), [](const Entry& x, const Entry& y) {
+            return fp8_key_less(x.key, y.key);
+          });
+          std::vector<std::vector<Entry>> blocks[4];
+          for (size_t i = 0; i < lst.size();) {
+            size_t j = i;
+            std::vector<Entry> ev, od;
+            while (j < lst.size() && !fp8_key_less(lst[i].key, lst[j].key) &&
+                   !fp8_key_less(lst[j].key, lst[i].key)) {
+              ((lst[j].off / G) % 2 ? od : ev).push_back(lst[j]);
+              ++j;
             }
-            blocks.push_back(blk);
-          }
-          i = j;
-        }
-        // bundles: four blocks of one half mask (blocks are sorted by mask first)
-        for (size_t i = 0; i < blocks.size();) {
-          const int mask = blocks[i][0].key.x;
-          std::vector<std::vector<Entry>> bun;
-          while (i < blocks.size() && bun.size() < 4 && blocks[i][0].key.x == mask)
-            bun.push_back(blocks[i++]);
-          while (bun.size() < 4)
-            bun.push_back(std::vector<Entry>(4, Entry{null_group, 0, make_int4(mask, 127, 127, 0)}));
-          const size_t base = groups.size();
-          groups.resize(base + 16, null_group);
-          std::vector<int> off(16, 0), sc(4, 0);
-          for (int bb = 0; bb < 4; ++bb) {
-            for (int k = 0; k < 4; ++k) {
-              const int pos = kFp8Lane[bb][k] * 4 + kFp8Slot[bb][k];
-              groups[base + pos] = bun[bb][k].group;
-              if (groups[base + pos].x >= 0) groups[base + pos].z = t;
-              off[pos] = bun[bb][k].off;
+            const Entry null_even{null_group, 0, lst[i].key}, null_odd{null_group, G, lst[i].key};
+            size_t a = 0, b = 0;
+            while (a < ev.size() || b < od.size()) {
+              std::vector<Entry> blk;
+              // two evens then two odds when both are left, else four of what is left
+              const bool both = ev.size() - a >= 2 && od.size() - b >= 2;
+              for (int k = 0; k < 4; ++k) {
+                const bool want_even = both ? k < 2 : (a < ev.size());
+                if (want_even && a < ev.size()) blk.push_back(ev[a++]);
+                else if (!want_even && b < od.size()) blk.push_back(od[b++]);
+                else if (a < ev.size()) blk.push_back(ev[a++]);
+                else if (b < od.size()) blk.push_back(od[b++]);
+                else blk.push_back(k < 2 ? null_even : null_odd);
+              }
+              blocks[lst[i].key.x].push_back(blk);
             }
-            sc[kFp8ScaleLane[bb]] = bun[bb][0].key.y | (bun[bb][0].key.z << 8);
+            i = j;
           }
-          for (int ln = 0; ln < 4; ++ln) {
-            rec.push_back(off[4 * ln] | (off[4 * ln + 1] << 16));
-            rec.push_back(off[4 * ln + 2] | (off[4 * ln + 3] << 16));
-            rec.push_back(sc[ln]);
-            rec.push_back(ln == 0 ? mask : 0);
-          }
-          bmask.push_back(mask);
+          for (int mask = 1; mask < 4; ++mask)
+            for (size_t i = 0; i < blocks[mask].size(); i += 2) {
+              std::vector<Entry> pr = blocks[mask][i];
+              if (i + 1 < blocks[mask].size())
+                pr.insert(pr.end(), blocks[mask][i + 1].begin(), blocks[mask][i + 1].end());
+              else
+                for (int k = 0; k < 4; ++k)
+                  pr.push_back(Entry{null_group, k < 2 ? 0 : G, make_int4(mask, 127, 127, 0)});
+              pr[0].group.w = r - R;  // the pair's row offset in the unit
+              pairs[mask].push_back(pr);
+            }
         }
-        const int lo = (prevR < 0 || R >= prevR + BR) ? R : prevR + BR;
-        const int nb = (int)(groups.size() / 16);
-        units.push_back(make_int4(R - K, c * CH, first_bundle, nb));
-        urows.push_back(make_int2(lo, R + BR));
         double w = 0;
-        for (int bi = first_bundle; bi < nb; ++bi) w += __builtin_popcount((unsigned)bmask[bi]);
+        int2 ends = make_int2(0, 0);  // of the bundles of half 0 alone, of half 1 alone
+        for (int mask = 1; mask < 4; ++mask) {
+          if (pairs[mask].size() % 2) {
+            std::vector<Entry> none(8, Entry{null_group, 0, make_int4(mask, 127, 127, 0)});
+            for (int k = 0; k < 8; ++k) none[k].off = k % 4 < 2 ? 0 : G;
+            pairs[mask].push_back(none);
+          }
+          // bundles: pair 0 is scale blocks 0 and 2 (lane groups 0 and 1), pair 1 blocks 1 and 3
+          for (size_t i = 0; i < pairs[mask].size(); i += 2) {
+            const size_t base = groups.size();
+            groups.resize(base + 16, null_group);
+            int off[16], sc[4], row[4];
+            for (int bb = 0; bb < 4; ++bb) {
+              const std::vector<Entry>& pr = pairs[mask][i + bb % 2];
+              const int k0 = bb / 2 * 4;
+              for (int k = 0; k < 4; ++k) {
+                const int pos = kFp8Lane[bb][k] * 4 + kFp8Slot[bb][k];
+                groups[base + pos] = pr[k0 + k].group;
+                groups[base + pos].z = t;
+                groups[base + pos].w = pr[k0 + k].group.x >= 0;
+                off[pos] = pr[k0 + k].off;
+                row[kFp8Lane[bb][k]] = pr[0].group.w;
+              }
+              sc[kFp8ScaleLane[bb]] = pr[k0].key.y | (pr[k0].key.z << 8);
+            }
+            for (int ln = 0; ln < 4; ++ln) {
+              rec.push_back(off[4 * ln] | (off[4 * ln + 1] << 16));
+              rec.push_back(off[4 * ln + 2] | (off[4 * ln + 3] << 16));
+              rec.push_back(sc[ln] | (row[ln] << 16));
+              rec.push_back(0);
+            }
+            w += __builtin_popcount((unsigned)mask);
+            bmask.push_back(mask);
+          }
+          if (mask == 1) ends.x = (int)(groups.size() / 16);
+          if (mask == 2) ends.y = (int)(groups.size() / 16);
+        }
+        units.push_back(make_int4(R - K, c * CH, first_bundle, (int)(groups.size() / 16)));
+        classes.push_back(ends);
         up.work.push_back(w);
-        prevR = R;
+        R += kRingStep;
       }
     }
   }
@@ -924,7 +952,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
               "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
   AROAM_CHECK(lay.NCOL * lay.CS < 65536, AROAM_EINVAL, "LDS offsets exceed 16 bits");
   AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_ucols, urows, bytes));
+  AROAM_TRY(alloc_copy(&lay.d_ucols, classes, bytes));
   AROAM_TRY(alloc_copy(&lay.d_meta, rec, bytes));
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.h_tile_start = tile_units;
