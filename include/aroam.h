@@ -16,7 +16,10 @@
  *     The voxel lateral grid coincides with the scan grid (Results, first paragraph).
  *     Element type: double for AROAM_FP64, float for every other dtype (AROAM_BF16 and
  *     AROAM_FP8E4M3 name the precision of the model table and operands inside the apply;
- *     the caller's vectors stay FP32).  AROAM_BF16: table and operand rounded to BF16
+ *     the caller's vectors stay FP32).  AROAM_FP32: every FP32 table entry and operand is split
+ *     into three BF16 values whose sum it is, and a product is the six products of parts above
+ *     2^-24 of it, accumulated in FP32 (results are closer to FP64 than with FP32 products; a
+ *     non-finite entry gives NaN).  AROAM_BF16: table and operand rounded to BF16
  *     (nearest, ties to even), products accumulated in FP32.  AROAM_FP8E4M3: OCP e4m3 table
  *     with a power-of-two scale per (offset, 16-depth block) and e4m3 operand with a
  *     power-of-two scale per 64 entries of its fast axis (chosen from that block's largest
@@ -57,9 +60,9 @@ typedef enum {
 
 typedef enum { AROAM_FP64 = 0, AROAM_FP32 = 1, AROAM_BF16 = 2, AROAM_FP8E4M3 = 3 } aroam_dtype;
 
-/* Largest lateral model extent k_half (offsets -k_half .. k_half).  The staged applies keep,
- * per workgroup, 9 scan rows x (32 + 2 k_half) columns x 80 bytes of input in the 160 KiB LDS
- * of a compute unit.  At the 5 um step this is about 0.97 mm of lateral extent. */
+/* Largest lateral model extent k_half (offsets -k_half .. k_half).  The FP8 applies keep,
+ * per workgroup, 15 scan rows x (32 + 2 k_half) columns x 48 bytes of input in the 160 KiB LDS
+ * of a compute unit (the other dtypes need less).  At the 5 um step this is about 0.97 mm of lateral extent. */
 #define AROAM_MAX_K_HALF 97
 
 /* Spherical-cap sensor (Methods, "Forward modeling", Eq. 3; "AR-OAM set-up").
@@ -114,7 +117,8 @@ typedef struct {
   long long n_columns;   /* (offset, depth) columns kept by the footprint with a non-empty window */
   long long nnz;         /* band entries of the compressed table over all those columns           */
   long long mac_alg;     /* algorithmic multiply-accumulates of one apply of A (or A^T)           */
-  long long mac_exec[4]; /* MACs the forward kernel issues per apply, indexed by aroam_dtype      */
+  long long mac_exec[4]; /* MACs the forward kernel issues per apply, indexed by aroam_dtype (FP32: of
+                          * FP32 values; each is six BF16 MACs)                                   */
   long long mac_exec_adj[4]; /* the same for the adjoint kernel                                   */
   size_t device_bytes;   /* device memory held by the model                                        */
   int n_elements;        /* sensor sub-elements M                                                  */
@@ -230,8 +234,9 @@ int aroam_forward(const aroam_model* model, int dtype, const void* x, void* s, v
 
 /* aroam_forward that allocates nothing, for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation).  The same
- * kernels and result as aroam_forward (bit for bit), but the apply's scratch (the zero-padded
- * staged input and the partial sums of cut tiles) lives in a static device array of 64 MiB
+ * kernels and result as aroam_forward (bit for bit), but the apply's scratch (the padded
+ * input and the partial sums of cut tiles; for FP64 and FP32, which read the caller's vector, the
+ * larger of the two sizes counts) lives in a static device array of 64 MiB
  * that the library holds on each GPU it runs on until the process ends, instead of coming from
  * the memory pool.  Every call on one GPU shares that array: calls that overlap on one GPU
  * (on different streams, or from different threads) race and give undefined results;

@@ -39,7 +39,6 @@ typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-
 // Stage an input vector [ny][nx][L] as zero-padded BF16 in blocks of the ring's chunks,
 // [chunk][nyp][nxp][8 entries]: a row of a chunk is contiguous, so that the ring's loads use whole
 // cache lines (from [nyp][nxp][L] each 128-byte line would be fetched once per chunk in it: 149 GB
@@ -990,7 +989,7 @@ constexpr int kAmaxParts = 512;  // position slices of the FP8 operand's chunk m
 const Layout& layout_for(const Model& m, bool adjoint, int dtype) {
   if (dtype == AROAM_FP64) return adjoint ? m.r64a : m.r64f;
   if (dtype == AROAM_FP32) return adjoint ? m.r32a : m.r32f;
-  if (dtype == AROAM_BF16) return adjoint ? m.s8a : m.s8f;
+  if (dtype == AROAM_BF16) return adjoint ? m.r16a : m.r16f;
   return adjoint ? m.f8a : m.f8f;
 }
 
@@ -1068,7 +1067,7 @@ int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial
   a.ncc = (int)ceil_div(lay.in.nx, kPatchCols);
   a.NCOL = lay.NCOL;
   a.row_bytes = ring_row_bytes(a.K, Op::kCol);
-  a.classes = lay.d_ucols;
+  a.classes = lay.d_classes;
   a.nxp = lay.in.nxp;
   a.nyp = lay.in.nyp;
   AROAM_CHECK(lay.TM == kTile * Op::kHalves && lay.BR == BR && lay.BC == kPatchCols &&
@@ -1125,7 +1124,7 @@ int launch_fp8(const Model& m, const Layout& lay, const Pack& pk, const float* i
   a.partial = partial;
   a.n_patches = lay.n_patches;
   a.units = lay.d_units;
-  a.classes = lay.d_ucols;
+  a.classes = lay.d_classes;
   a.rec = reinterpret_cast<const u32x4*>(lay.d_meta);
   a.xexp = xexp;
   a.out_len = lay.out_len;
@@ -1191,7 +1190,7 @@ int apply(const Model& m, bool adjoint, int dtype, const void* in, void* out, vo
   AROAM_CHECK((m.dtype_mask >> dtype) & 1u, AROAM_EUNSUPPORTED,
               "model was not packed for dtype %d", dtype);
   const Layout& lay = layout_for(m, adjoint, dtype);
-  AROAM_CHECK(!lay.staged || lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
+  AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
               "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
   if (stage) return launch_apply(m, adjoint, dtype, in, out, stage, st);
   // a stage buffer of its own from the pool, returned to the pool on every path
@@ -1240,7 +1239,7 @@ int apply_noalloc(const Model& m, bool adjoint, int dtype, const void* in, void*
   AROAM_CHECK((m.dtype_mask >> dtype) & 1u, AROAM_EUNSUPPORTED,
               "model was not packed for dtype %d", dtype);
   const Layout& lay = layout_for(m, adjoint, dtype);
-  AROAM_CHECK(!lay.staged || lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
+  AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
               "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
   const size_t need = stage_bytes(m, adjoint, dtype);
   AROAM_CHECK(need <= kStaticScratchBytes, AROAM_EINVAL,

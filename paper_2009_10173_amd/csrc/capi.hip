@@ -161,8 +161,8 @@ int aroam_model_query(const aroam_model* model, aroam_model_info* info) {
     const aroam::Layout& a = aroam::layout_for(m, true, d);
     info->row_tiles[d] = packed ? f.n_tiles : 0;
     info->row_tiles_adj[d] = packed ? a.n_tiles : 0;
-    info->pieces[d] = packed ? (f.staged ? f.n_pieces : f.n_tiles) : 0;
-    info->pieces_adj[d] = packed ? (a.staged ? a.n_pieces : a.n_tiles) : 0;
+    info->pieces[d] = packed ? f.n_pieces : 0;
+    info->pieces_adj[d] = packed ? a.n_pieces : 0;
   }
   return AROAM_OK;
 }

@@ -49,26 +49,21 @@ int pool_alloc(void** p, size_t bytes, hipStream_t st);
 
 constexpr int kTile = 16;     // output rows per tile (time samples or depths) = MFMA M
 constexpr int kLaneGroups = 4; // K-groups per bundle = 64-lane wave / 16
-constexpr int kTileRows8 = 32;  // output rows per tile of the G = 8 (BF16 / FP8) layouts
+constexpr int kTileRows8 = 32;  // output rows per tile of the FP8 layouts
 constexpr int kMaxElements = 4096;  // two FP64 values per sub-element fit in 64 KiB of LDS
 static_assert(max_k_half() == AROAM_MAX_K_HALF, "the header's k_half limit is the LDS stage's");
 
 // ------------------------------------------------------------------------------------------
-// Padded operand geometry.  Inputs of an apply are staged into a zero-padded buffer
-// [nyp][nxp][Lp] with a halo of K columns on every lateral side, x rounded up to whole
-// 16-position tiles, and the fast axis padded so that every K-group read stays in bounds.
+// Padded operand geometry.  BF16 and FP8 inputs of an apply are staged into a zero-padded buffer of
+// nyp x nxp x Lp entries with a halo of K columns on every lateral side, the scan rounded up to whole
+// patches and the fast axis to whole chunks.  (FP64 and FP32 are read from the caller's vector; the
+// padded size bounds their partial slots.)
 struct PadGeom {
   int K = 0, nx = 0, ny = 0;
-  int ntx = 0;        // 16-position tiles per scan row
   int nxp = 0, nyp = 0;
   int L = 0, Lp = 0;  // true and padded length of the fast axis of the input
   long long elems() const { return (long long)nyp * nxp * Lp; }
 };
-
-// Staged layouts: bits kMetaMaskShift.. of each K-group's meta word hold its bundle's mask (the
-// LDS offset stays below 2^kMetaMaskShift): with two row halves the halves its K-groups reach,
-// with one (FP32, runs of 4) the entries of the runs, one MFMA each, that they reach.
-constexpr int kMetaMaskShift = 28;
 
 // LDS form of the ring layouts (FP64, FP32, BF16): entries of a K-group, which are also those of a
 // chunk, the bytes of a staged column and the 16-row halves of a tile.  A column is an odd number
@@ -84,41 +79,32 @@ constexpr RingShape kRingBF16{8, kRing16ColumnBytes, 2};
 
 // Band tiles of one operator (forward: rows = time, K = (offset, depth); adjoint: rows =
 // depth, K = (offset, time)) at one K-group width G.  A K-group is G consecutive entries of
-// one table column block; four K-groups form a bundle, which one MFMA step consumes.
-//
-// Two forms:
-//  * direct (staged == false): meta[q] is the element offset of K-group q's input run
-//    relative to the output position, read straight from the padded input;
-//  * LDS-staged (staged == true): each tile's bundles are grouped into stage units
-//    (dy, chunk of CH inner entries).  A workgroup loads the input rows of its position patch
-//    shifted by dy, for the chunk and the unit's dx range, into LDS once, and then sweeps all
-//    (dx, G-run) K-groups of the unit from LDS; meta[q] is then the LDS element offset
-//    (dx + K) * CS + (run start - chunk start), with the bundle's mask in the top bits.
+// one table column block; four K-groups (FP8: sixteen) form a bundle, which one MFMA step
+// consumes.  Each tile's bundles are grouped into stage units (chunk of CH inner entries,
+// kRingStep consecutive input row offsets): a workgroup holds the input rows of its position
+// patch that a unit reads in the LDS and sweeps the unit's K-groups from there.
 struct Layout {
   int G = 0;
   int TM = 16;              // output rows per tile (16 or 32: two MFMA row halves)
   int n_tiles = 0;          // output row tiles
   int out_len = 0;          // rows of the output vector (nt or nz)
   long long n_bundles = 0;
-  int* d_tile_start = nullptr;   // [n_tiles + 1] bundle range of each tile (direct form)
-  int* d_meta = nullptr;         // [n_bundles * 4] per K-group offset (see above)
-  int4* d_groups = nullptr;      // [n_bundles * 4] (offset index, start, tile, active)
-  std::vector<int> h_tile_start;  // bundle (direct) or stage-unit (staged) range of each tile
+  int* d_meta = nullptr;    // per K-group: LDS byte offset of its run from the position's column
+                            // (row within the unit included); FP8: bundle records
+  int4* d_groups = nullptr;      // per K-group (offset index, start, tile, active)
   long long mac_exec = 0;        // MACs issued per apply
-  PadGeom in;                    // staged input geometry
-  // LDS-staged form
-  bool staged = false;
+  PadGeom in;                    // padded input geometry
   int CH = 0, BR = 0, BC = 0;    // chunk length, patch rows, patch columns
-  int CS = 0, NCOL = 0;          // LDS column stride (elements), staged columns BC + 2K
+  int CS = 0, NCOL = 0;          // LDS bytes of a column, staged columns BC + 2K
   long long n_units = 0;
   int4* d_units = nullptr;       // [n_units] (dy, chunk start, bundle begin, bundle end)
-  int2* d_ucols = nullptr;       // [n_units] padded input rows [lo, hi) the unit loads (ring)
+  int2* d_classes = nullptr;     // tiles of two halves: [n_units] the end of the unit's bundles
+                                 // that reach half 0 alone and half 1 alone; the rest reach both
   size_t lds_bytes = 0;
-  // Work split of the staged kernel: a tile's stage units may be cut at chunk starts (where
-  // the LDS ring is reloaded anyway) into pieces of similar work, so that the workgroups of a
-  // launch are many and even, and the pieces may be dispatched heaviest first.  Each piece of a
-  // cut tile leaves its partial sums in a slot of the stage buffer, and a second kernel adds
-  // a tile's slots in slot order (deterministic).
+  // Work split of a launch: a tile's stage units may be cut into pieces of similar work, so that
+  // the workgroups of a launch are many and even, and the pieces may be dispatched heaviest first.
+  // Each piece of a cut tile leaves its partial sums in a slot of the stage buffer, and a second
+  // kernel adds a tile's slots in slot order (deterministic).
   int n_pieces = 0;
   int n_slots = 0;               // partial slots (pieces of the tiles cut into several)
   int n_patches = 0;             // position patches of one launch
@@ -128,8 +114,8 @@ struct Layout {
 };
 
 struct Pack {
-  void* d = nullptr;   // FP32 / BF16: [n_bundles * 4 * TM * G] elements; FP8: [n_bundles][half]
-                       // [lane group][row][32] e4m3 bytes (see kFp8Lane)
+  void* d = nullptr;   // FP64 / BF16: [n_bundles * 4 * TM * G] elements; FP32: three BF16 parts of
+                       // each; FP8: [n_bundles][half][lane group][row][32] e4m3 bytes (kFp8Lane)
   size_t bytes = 0;
 };
 
@@ -165,8 +151,8 @@ struct Model {
   long long* d_off = nullptr;    // [n_stored + 1]
   Layout r64f, r64a;             // LDS ring: FP64 forward / adjoint
   Layout r32f, r32a;             // LDS ring: FP32
-  Layout s8f, s8a;               // LDS-staged, G = 8: BF16
-  Layout f8f, f8a;               // LDS-staged, G = 8, bundles of the block-scaled FP8 MFMA
+  Layout r16f, r16a;             // LDS ring: BF16
+  Layout f8f, f8a;               // bundles of the block-scaled FP8 MFMA
   Pack fwd_pack[4], adj_pack[4]; // indexed by aroam_dtype
   // band-pass filter applied along time to the columns (and, by the caller, to the signals)
   bool filtered = false;

@@ -4,9 +4,8 @@
 //
 // A staged launch has one workgroup per (piece, position patch).  A piece is a range of one
 // output tile's stage units.  An uncut tile is one piece, which writes the output; a cut
-// tile is several pieces, cut where a chunk starts (the LDS ring is reloaded there anyway),
-// and each of them writes its partial sums to its own slot, which a second kernel adds in
-// slot order.  The slots of a tile are consecutive and follow the tile's unit order, so the
+// tile is several pieces (each loads the whole LDS ring for its first unit), and each of them
+// writes its partial sums to its own slot, which a second kernel adds in slot order.  The slots of a tile are consecutive and follow the tile's unit order, so the
 // sum is deterministic.
 #pragma once
 
@@ -67,7 +66,8 @@ inline double simulate_launch(const std::vector<double>& piece_work, int n_patch
 // (its work) / (largest tile work / D) pieces of similar work, each cut at the start
 // whose prefix work is nearest to its share, and the pieces are dispatched in tile order or
 // heaviest first, whichever the simulation (`slots` places, one workgroup per piece and
-// patch, costs.workgroup added to each for its fixed costs and, for a cut, those of adding slots) finishes sooner.  A cut
+// patch, costs.workgroup added to each for its fixed costs and, for a cut, those of adding
+// slots) finishes sooner.  A cut
 // is taken only when `allow_cut`, when it shortens the simulated launch by more than 10 %,
 // and when its slots (slot_bytes per piece and patch) fit in max_slot_bytes.
 inline LaunchPlan plan_launch(const std::vector<int>& tile_units,

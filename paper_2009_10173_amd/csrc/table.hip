@@ -335,7 +335,6 @@ PadGeom pad_geom(const aroam_grid& g, int L, int BR = 1, int BC = 16, int CH = 0
   p.K = g.k_half;
   p.nx = g.nx;
   p.ny = g.ny;
-  p.ntx = (int)ceil_div(g.nx, 16);
   p.nxp = (int)round_up(g.nx, BC) + 2 * p.K;
   p.nyp = (int)round_up(g.ny, BR) + 2 * p.K;
   p.L = L;
@@ -373,77 +372,56 @@ bool tile_hits(const Model& m, bool adjoint, int G, int TM, int t, int oi, std::
   return any;
 }
 
-// LDS-staged form (see Layout).  For tile t, the hit runs of every lateral offset are
-// grouped by chunk (CH inner entries = CH / G runs) and by input row offset; each non-empty
-// (chunk, row offset) is one stage unit whose K-groups (dx, run) are packed four to a
-// bundle.  Units are ordered by chunk, then by ascending row offset, so that the LDS rows
-// form a ring: a unit only loads the input rows that the previous unit of the same chunk did
-// not hold (one row when the offset steps by one).  The row range to load is stored per unit
-// as [lo, hi) in patch-relative padded rows G = row offset + K + r.  A null K-group reads
-// staged column 0 and multiplies zero table entries.
 // LDS bank model of a bundle's position-fragment reads, measured on gfx950 with a probe of
 // single-lane-pair collisions and the SQ_LDS_BANK_CONFLICT counter: a 64-lane 16-byte LDS read
 // is served in four passes of 16 lanes x 16 bytes over the 64 banks.  Lane l belongs to half
 // l / 32 and to the pass given by the parity of the bits of (l / 4) mod 8, so within a half
 // the passes take lanes n in {0-3, 12-15} of lane group g (even) with n in {4-11} of g + 1,
 // and the converse.  A pass is conflict-free when its 16 lanes hit 16 distinct 16-byte bank
-// groups.  Lane (n, g) of a bundle reads vector run_g of staged column c + n + col_g; with a
-// column stride of 80 bytes (5 groups of 16 bytes) its bank group is 5 (c + n + col_g) + run_g
-// (mod 16).  The patch offset c and the row start shift all lanes of a read alike.
-struct BankShape {
-  int col, run;  // LDS strides of a column and of a run, in 16-byte groups
-  int nrun;      // runs per staged column (at most four)
-};
-
-bool pair_conflict_free(const BankShape& sh, int col_a, int run_a, int col_b, int run_b) {
+// groups.  Lane (n, g) of a bundle reads staged column c + n + col_g; with a column stride of
+// `stride` groups of 16 bytes (odd) its bank group is stride (c + n + col_g) (mod 16).  The patch
+// offset c and the row start shift all lanes of a read alike.
+bool pair_conflict_free(int stride, int col_a, int col_b) {
   static const int lo_hi[8] = {0, 1, 2, 3, 12, 13, 14, 15};
   static const int mid[8] = {4, 5, 6, 7, 8, 9, 10, 11};
   for (int pass = 0; pass < 2; ++pass) {
     const int* na = pass ? mid : lo_hi;  // lanes of the even group in this pass
     const int* nb = pass ? lo_hi : mid;  // lanes of the odd group
     unsigned used = 0;
-    for (int i = 0; i < 8; ++i) {
-      const int ba = (sh.col * (na[i] + col_a) + sh.run * run_a) & 15;
-      const int bb = (sh.col * (nb[i] + col_b) + sh.run * run_b) & 15;
-      used |= (1u << ba) | (1u << bb);
-    }
+    for (int i = 0; i < 8; ++i)
+      used |= (1u << (stride * (na[i] + col_a) & 15)) | (1u << (stride * (nb[i] + col_b) & 15));
     if (used != 0xffffu) return false;
   }
   return true;
 }
 
-// One K-group of a stage unit: its group record, staged column offset, vector run, and the
-// 16-row halves of the tile its band reaches (bit h for half h).
+// One K-group of a stage unit: its group record, staged column offset, and the 16-row halves of
+// the tile its band reaches (bit h for half h).
 struct UnitEntry {
   int4 group;
-  int col, run;
+  int col;
   int mask;
 };
 
-// Pair the K-groups of one stage unit so that bundle slots (0, 1) and (2, 3) read the LDS
-// without bank conflicts wherever possible: a greedy matching over the 64 classes
-// (column mod 16, run) that pairs the most constrained class first.  K-groups left without a
-// partner are paired with each other; an odd one out gets a zero padding K-group of a
-// matching class.  The result has an even number of entries; with pad4 it is padded to a
-// multiple of four (whole bundles).
 struct CompatTable {
-  BankShape sh;
-  std::vector<int> partners[64];  // classes whose K-groups pair with this one without conflicts
-  explicit CompatTable(const BankShape& s) : sh(s) {
-    for (int a = 0; a < 64; ++a)
-      for (int b = 0; b < 64; ++b)
-        if ((a & 3) < sh.nrun && (b & 3) < sh.nrun &&
-            pair_conflict_free(sh, a >> 2, a & 3, b >> 2, b & 3))
-          partners[a].push_back(b);
+  int stride;
+  std::vector<int> partners[16];  // classes (column mod 16) that pair with this one without conflicts
+  explicit CompatTable(int column_bytes) : stride(column_bytes / 16) {
+    for (int a = 0; a < 16; ++a)
+      for (int b = 0; b < 16; ++b)
+        if (pair_conflict_free(stride, a, b)) partners[a].push_back(b);
   }
 };
 
+// Pair the K-groups of one stage unit so that bundle slots (0, 1) and (2, 3) read the LDS
+// without bank conflicts wherever possible: a greedy matching over the 16 classes (column mod
+// 16) that pairs the most constrained class first.  K-groups left without a partner are paired
+// with each other; an odd one out gets a zero padding K-group of a matching class (a null K-group
+// multiplies zero table entries).  The result is padded to whole bundles.
 std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<UnitEntry>& in,
-                                 int maxcol, int t, bool pad4 = true) {
-  const BankShape& sh = table.sh;
-  std::vector<int> cls_items[64];
-  for (int i = (int)in.size() - 1; i >= 0; --i)
-    cls_items[((in[i].col & 15) << 2) | in[i].run].push_back(i);
+                                 int maxcol, int t) {
+  std::vector<int> cls_items[16];
+  for (int i = (int)in.size() - 1; i >= 0; --i) cls_items[in[i].col & 15].push_back(i);
   auto avail = [&](int a) {
     int n = 0;
     for (int b : table.partners[a]) n += (int)cls_items[b].size() - (a == b ? 1 : 0);
@@ -454,7 +432,7 @@ std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<Uni
   std::vector<int> left;
   for (;;) {
     int a = -1, best = 1 << 30;
-    for (int c = 0; c < 64; ++c)
+    for (int c = 0; c < 16; ++c)
       if (!cls_items[c].empty()) {
         const int v = avail(c);
         if (v < best) best = v, a = c;
@@ -477,7 +455,7 @@ std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<Uni
     out.push_back(in[ia]);
     out.push_back(in[ib]);
   }
-  const UnitEntry pad0{make_int4(-1, 0, t, 0), 0, 0, 0};
+  const UnitEntry pad0{make_int4(-1, 0, t, 0), 0, 0};
   for (size_t i = 0; i + 1 < left.size(); i += 2) {
     out.push_back(in[left[i]]);
     out.push_back(in[left[i + 1]]);
@@ -485,26 +463,14 @@ std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<Uni
   if (left.size() % 2) {
     const UnitEntry& e = in[left.back()];
     UnitEntry p = pad0;
-    bool found = false;
-    for (int c = 0; c <= maxcol && !found; ++c)
-      for (int r = 0; r < sh.nrun && !found; ++r)
-        if (pair_conflict_free(sh, e.col, e.run, c, r)) {
-          p.col = c;
-          p.run = r;
-          found = true;
-        }
+    for (int c = maxcol; c >= 0; --c)
+      if (pair_conflict_free(table.stride, e.col, c)) p.col = c;
     out.push_back(e);
     out.push_back(p);
   }
-  if (pad4 && out.size() % 4) {
-    UnitEntry p = pad0;
-    for (int r = 1; r < sh.nrun; ++r)
-      if (pair_conflict_free(sh, 0, 0, 0, r)) {
-        p.run = r;
-        break;
-      }
+  if (out.size() % 4) {
     out.push_back(pad0);
-    out.push_back(p);
+    out.push_back(pad0);
   }
   return out;
 }
@@ -599,7 +565,7 @@ int ring_rows(int K, long long tiles, const aroam_grid& g, int cus) {
 // LDS-ring form (FP64, FP32, BF16; see Layout and RingShape): a chunk is one K-group's run, and a
 // stage unit covers up to kRingStep consecutive row offsets of a chunk, whose K-groups share
 // bundles (a K-group's offset names its row).  With two halves a unit's bundles are ordered by the
-// halves they reach: half 0 alone, half 1 alone, both (d_ucols holds the ends of the first two).
+// halves they reach: half 0 alone, half 1 alone, both (d_classes holds the ends of the first two).
 // `pad` is the geometry of the zero-padded input.
 int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR, const PadGeom& pad,
                       Layout& lay, UnitPlan& up, size_t& bytes) {
@@ -608,7 +574,6 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
   const int row_bytes = ring_row_bytes(K, rs.col_bytes);
   lay.G = rs.G;
   lay.TM = kTile * NH;
-  lay.staged = true;
   lay.CH = rs.G;
   lay.BR = BR;
   lay.BC = BC;
@@ -620,7 +585,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
   lay.lds_bytes = (size_t)ring_lds_bytes(K, BR, rs.col_bytes);
   const int inner = adjoint ? g.nt : g.nz;
   const int nch = (int)ceil_div(inner, rs.G);
-  const CompatTable table(BankShape{rs.col_bytes / 16, 0, 1});
+  const CompatTable table(rs.col_bytes);
   std::vector<int4> groups, units;
   std::vector<int2> classes;
   std::vector<int> meta;
@@ -646,7 +611,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
           for (int h = 0; h < NH; ++h) mask |= hits[h][c] ? 1 << h : 0;
           if (mask)
             per[(size_t)c * W + slot].push_back(
-                UnitEntry{make_int4(a * W + b, c * rs.G, t, slot), col, 0, mask});
+                UnitEntry{make_int4(a * W + b, c * rs.G, t, slot), col, mask});
         }
       }
     }
@@ -714,7 +679,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
   AROAM_CHECK(lay.in.elems() < (1ll << 31), AROAM_EINVAL,
               "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
   AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
-  if (NH > 1) AROAM_TRY(alloc_copy(&lay.d_ucols, classes, bytes));
+  if (NH > 1) AROAM_TRY(alloc_copy(&lay.d_classes, classes, bytes));
   AROAM_TRY(alloc_copy(&lay.d_meta, meta, bytes));
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
@@ -767,7 +732,6 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   const int nblk = (int)ceil_div(nz, 16);
   lay.G = G;
   lay.TM = TM;
-  lay.staged = true;
   lay.CH = CH;
   lay.BR = BR;
   lay.BC = BC;
@@ -952,10 +916,9 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
               "grid too large for 32-bit operand offsets (%lld padded elements)", lay.in.elems());
   AROAM_CHECK(lay.NCOL * lay.CS < 65536, AROAM_EINVAL, "LDS offsets exceed 16 bits");
   AROAM_TRY(alloc_copy(&lay.d_units, units, bytes));
-  AROAM_TRY(alloc_copy(&lay.d_ucols, classes, bytes));
+  AROAM_TRY(alloc_copy(&lay.d_classes, classes, bytes));
   AROAM_TRY(alloc_copy(&lay.d_meta, rec, bytes));
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
-  lay.h_tile_start = tile_units;
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
   up.tile_units = tile_units;
   return plan_staged(m, adjoint, lay, up, kFp8Unit, kFp8Costs, 1.0 * lay.in.elems(), bytes);
@@ -1552,12 +1515,12 @@ int finish_model(Model* m, int rc, unsigned mask, hipStream_t st, Model** out) {
     const bool want8 = (mask & (1u << AROAM_BF16)) != 0;
     size_t bytes = 0;
     if (want8) {
-      rc = build_bf16_layout(*m, false, m->s8f, bytes);
-      if (!rc) rc = build_bf16_layout(*m, true, m->s8a, bytes);
+      rc = build_bf16_layout(*m, false, m->r16f, bytes);
+      if (!rc) rc = build_bf16_layout(*m, true, m->r16a, bytes);
     }
     if (!rc && (mask & (1u << AROAM_BF16))) {
-      rc = pack_dtype<uint16_t>(*m, m->s8f, false, m->fwd_pack[AROAM_BF16], st, bytes);
-      if (!rc) rc = pack_dtype<uint16_t>(*m, m->s8a, true, m->adj_pack[AROAM_BF16], st, bytes);
+      rc = pack_dtype<uint16_t>(*m, m->r16f, false, m->fwd_pack[AROAM_BF16], st, bytes);
+      if (!rc) rc = pack_dtype<uint16_t>(*m, m->r16a, true, m->adj_pack[AROAM_BF16], st, bytes);
       if (!rc) m->dtype_mask |= 1u << AROAM_BF16;
     }
     if (!rc && (mask & (1u << AROAM_FP8E4M3))) {
@@ -1576,12 +1539,10 @@ int finish_model(Model* m, int rc, unsigned mask, hipStream_t st, Model** out) {
   // account device memory
   size_t b = (size_t)std::max<long long>(1, m->nnz_stored) * sizeof(double);
   b += m->h_colidx.size() * sizeof(int) + m->n_stored * sizeof(int) + m->h_off.size() * 8;
-  for (const Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->s8f, &m->s8a, &m->f8f, &m->f8a})
+  for (const Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->r16f, &m->r16a, &m->f8f, &m->f8a})
     b += l->n_bundles * kLaneGroups * (sizeof(int) + sizeof(int4)) * (l == &m->f8f || l == &m->f8a ? 4 : 1) +
-         (l->staged ? l->n_bundles * sizeof(int) + l->n_pieces * sizeof(int4) +
-                          l->n_tiles * sizeof(int2)
-                    : l->h_tile_start.size() * sizeof(int)) +
-         l->n_units * (sizeof(int4) + sizeof(int2));
+         l->n_pieces * sizeof(int4) + l->n_tiles * sizeof(int2) +
+         l->n_units * (sizeof(int4) + (l->d_classes ? sizeof(int2) : 0));
   for (int d = 0; d < 4; ++d) b += m->fwd_pack[d].bytes + m->adj_pack[d].bytes;
   m->device_bytes = b;
   *out = m;
@@ -1597,14 +1558,13 @@ void destroy_model(Model* m) {
   (void)hipFree(m->d_colidx);
   (void)hipFree(m->d_lo);
   (void)hipFree(m->d_off);
-  for (Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->s8f, &m->s8a, &m->f8f, &m->f8a}) {
-    (void)hipFree(l->d_tile_start);
+  for (Layout* l : {&m->r64f, &m->r64a, &m->r32f, &m->r32a, &m->r16f, &m->r16a, &m->f8f, &m->f8a}) {
     (void)hipFree(l->d_meta);
     (void)hipFree(l->d_groups);
     (void)hipFree(l->d_pieces);
     (void)hipFree(l->d_tile_split);
     (void)hipFree(l->d_units);
-    (void)hipFree(l->d_ucols);
+    (void)hipFree(l->d_classes);
   }
   for (int d = 0; d < 4; ++d) {
     (void)hipFree(m->fwd_pack[d].d);
