@@ -545,9 +545,11 @@ constexpr PlanCosts kBf16Costs{60, 200, 6}, kFp8Costs{30, 60, 3};
 // staging and barrier, a workgroup's first and last accesses, the slot sums.  Where few
 // workgroups run, these are what a finer cut has to pay for; measured on the 40 x 40 FISTA
 // (1.13 -> 0.80 ms a pair of applies with them, 1.02 with none), the 64 x 64 FP32 forward (177 ->
-// 162 us, 177 with none) and the 23 x 19 FP64 one (75 -> 51 us, 56 with none).
+// 162 us, 177 with none) and the 23 x 19 FP64 one (75 -> 51 us, 56 with none).  Slots at 40 and 2
+// instead of 20 and 1 cut the smallest scans too little: the 23 x 19 forward takes 51.6 us instead
+// of 47.6, an LSQR solve on 16 x 16 368 instead of 356; at 80 and 4 that takes 440.
 constexpr double kUnitWork = 8;
-constexpr PlanCosts kRingCosts{24, 40, 2};
+constexpr PlanCosts kRingCosts{24, 20, 1};
 
 // Patch rows of an FP32 ring launch.  Four rows leave room for three workgroups per CU while the
 // LDS holds three rings; a wider footprint (K = 34 .. 40) leaves two either way, and then eight
