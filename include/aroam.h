@@ -18,8 +18,10 @@
  *     AROAM_FP8E4M3 name the precision of the model table and operands inside the apply;
  *     the caller's vectors stay FP32).  AROAM_FP32: every FP32 table entry and operand is split
  *     into three BF16 values whose sum it is, and a product is the six products of parts above
- *     2^-24 of it, accumulated in FP32 (results are closer to FP64 than with FP32 products; a
- *     non-finite entry gives NaN).  AROAM_BF16: table and operand rounded to BF16
+ *     2^-24 of it, accumulated in FP32 (results are closer to FP64 than with FP32 products).
+ *     AROAM_FP64, AROAM_FP32: an infinite entry times a nonzero table entry is an infinity; in the
+ *     other rows of a 16-row output tile that meets a non-finite entry, the product is 0 times it.
+ *     AROAM_BF16: table and operand rounded to BF16
  *     (nearest, ties to even), products accumulated in FP32.  AROAM_FP8E4M3: OCP e4m3 table
  *     with a power-of-two scale per (offset, 16-depth block) and e4m3 operand with a
  *     power-of-two scale per 64 entries of its fast axis (chosen from that block's largest

@@ -94,13 +94,23 @@ typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));
 
+// Bit j: entry j of the lane's K-group (lane group g) meets a nonzero table entry in some row.
+template <class T, int N>
+__device__ __forceinline__ unsigned live_entries(const T (&v)[N], int g) {
+  unsigned keep = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) keep |= (__ballot(v[j] != T(0)) >> (16 * g) & 0xffff) ? 1u << j : 0u;
+  return keep;
+}
+
 // FP32 on the BF16 MFMA: every FP32 value is the exact sum of three BF16 values (8 bits each,
 // rounded to nearest in turn), and a product is the six products of parts whose exponents
 // add up to no less than 2^-16 of the leading one; the three left out are below 2^-24 of it.
 // The sums run in FP32.  Six BF16 MFMAs of K = 32 take 96 cycles where the eight FP32 MFMAs of
 // K = 4 take 256, and round the sum less often: the 400 x 400 forward took 181 ms on
 // v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 95 ms at 1.9e-6 (200 x 200
-// adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  Non-finite entries give NaN.  Splitting at
+// adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  A workgroup whose sums are not finite takes them
+// again on FP32 MFMAs (ring_guarded), since the parts of an infinity are not its sum.  Splitting at
 // the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
 struct OpF32 {
   using In = float;
@@ -167,6 +177,41 @@ struct OpF32 {
   }
   // output row (within the tile) of accumulator element i of lane group g
   static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+
+  // The guarded sweep: FP32 entries, a column's eight after one another, on FP32 MFMAs.
+  static constexpr bool kGuard = true;
+  struct Guard {
+    float v[8];
+    unsigned keep;
+  };
+  static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
+                                                     int lane) {
+    A f;
+    load_a(pack, b, lane, f);
+    Guard r;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      float e = 0;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const uint32_t w = f.v[i][j / 2];
+        e += __uint_as_float(j % 2 ? w & 0xffff0000u : w << 16);
+      }
+      r.v[j] = e;
+    }
+    r.keep = live_entries(r.v, lane / 16);
+    return r;
+  }
+  static __device__ __forceinline__ void write_guard(unsigned char* col, int v, Vec f) {
+    *reinterpret_cast<Vec*>(col + 16 * v) = f;
+  }
+  static __device__ __forceinline__ void mma_guard(const Guard& a, const unsigned char* p, Acc& acc) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float x = reinterpret_cast<const float*>(p)[j];
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j], a.keep >> j & 1 ? x : 0.0f, acc, 0, 0, 0);
+    }
+  }
 };
 
 // FP64 on v_mfma_f64_16x16x4_f64: entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
@@ -212,6 +257,32 @@ struct OpF64 {
                                                              acc[t * STEP], 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
+
+  static constexpr bool kGuard = true;
+  struct Guard {
+    double v[4];
+    unsigned keep;
+  };
+  static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
+                                                     int lane) {
+    A f;
+    load_a(pack, b, lane, f);
+    Guard r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.v[j] = f.v[j];
+    r.keep = live_entries(r.v, lane / 16);
+    return r;
+  }
+  static __device__ __forceinline__ void write_guard(unsigned char* col, int v, Vec f) {
+    write(col, v, f);
+  }
+  static __device__ __forceinline__ void mma_guard(const Guard& a, const unsigned char* p, Acc& acc) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const double x = reinterpret_cast<const double*>(p)[j];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[j], a.keep >> j & 1 ? x : 0.0, acc, 0, 0, 0);
+    }
+  }
 };
 
 // BF16: output tiles of two 16-row halves that share the position fragments; a unit's bundles
@@ -231,6 +302,7 @@ struct OpBF16 {
   static constexpr int kTiles = 2;
   static constexpr int kHalves = 2;
   static constexpr bool kBlocked = true;
+  static constexpr bool kGuard = false;
   struct A {
     u32x4 v[2];
   };
@@ -322,6 +394,119 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
   }
 }
 
+// The output of a piece, or for a piece of a cut tile its partial slot: the sums over the S waves
+// of a group in wave order, S tiles per phase.  Returns whether the thread's sums are finite.
+template <class Op, int BR, int BC, int W, int P>
+__device__ __forceinline__ bool ring_store(const typename Op::Acc (&acc)[Op::kHalves][BR / P * BC / 16],
+                                           unsigned char* lds, const RingArgs& a, const int4& piece,
+                                           typename Op::In* __restrict__ out, int tid, int py0,
+                                           int px0) {
+  using In = typename Op::In;
+  using Acc = typename Op::Acc;
+  constexpr int S = W / P, RW = BR / P, TPR = BC / 16, NT = RW * TPR;
+  constexpr int MH = Op::kHalves, TM = kTile * MH;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+  const int grp = wave / S, sw = wave % S, n = lane % 16, g = lane / 16;
+  const int tile = piece.x;
+  bool finite = true;
+  In* slot = piece.w >= 0 ? reinterpret_cast<In*>(a.partial) +
+                                ((long long)piece.w * a.n_patches + blockIdx.x) * (BR * BC * TM)
+                          : nullptr;
+  Acc* red = reinterpret_cast<Acc*>(lds);
+#pragma unroll
+  for (int p = 0; p < NT; p += S) {
+    Acc v[MH];
+    if constexpr (S > 1) {
+      __syncthreads();  // the ring, or the phase before
+#pragma unroll
+      for (int k = 0; k < S; ++k)
+#pragma unroll
+        for (int h = 0; h < MH; ++h) red[((wave * S + k) * MH + h) * 64 + lane] = acc[h][p + k];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int h = 0; h < MH; ++h) {
+      if constexpr (S > 1) {
+        v[h] = red[((grp * S * S + sw) * MH + h) * 64 + lane];
+#pragma unroll
+        for (int s = 1; s < S; ++s) v[h] += red[(((grp * S + s) * S + sw) * MH + h) * 64 + lane];
+      } else {
+        v[h] = acc[h][p];
+      }
+    }
+    if constexpr (Op::kGuard)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) finite &= __builtin_isfinite(v[0][i]);
+    const int t = p + sw;
+    const int r = grp * RW + t / TPR, c = (t % TPR) * 16 + n;
+    const int py = py0 + r, px = px0 + c;
+    if (py < a.ny && px < a.nx) {
+      In* dst = slot ? slot + (r * BC + c) * TM
+                     : out + ((long long)py * a.nx + px) * a.out_len + TM * tile;
+#pragma unroll
+      for (int h = 0; h < MH; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = kTile * h + Op::row(i, g);
+          if (TM * tile + row < a.out_len) dst[row] = v[h][i];
+        }
+    }
+  }
+  return finite;
+}
+
+// The sweep over a piece's units in which a non-finite entry meets only outputs whose row tile
+// has a nonzero table entry for it (elsewhere in the K-group's run, and in null K-groups, the
+// others would read 0 * NaN), and in which an infinity stays one.  Taken by a workgroup whose sums
+// were not finite, after it has stored them; plain loads and a barrier per unit, since that is rare.
+// Nothing of it is live in the main loop (written as a second turn of a loop around both, it spilled
+// 90 bytes more a lane there); the test of the sums costs up to 1 % (64 x 64 FP32 forward 148.1 ->
+// 149.5 us, 200 x 200 adjoint 4.18 -> 4.21 ms, 96 x 96 FP64 1.318 -> 1.320).
+template <class Op, int BR, int BC, int W, int P, bool RAGGED>
+__device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
+                                             const typename Op::In* __restrict__ in,
+                                             typename Op::In* __restrict__ out, unsigned char* lds,
+                                             const RingArgs& a, const int4& piece, int tid, int py0,
+                                             int px0) {
+  using Acc = typename Op::Acc;
+  constexpr int S = W / P, RW = BR / P, TPR = BC / 16, NT = RW * TPR;
+  constexpr int UR = BR + kRingStep - 1, RS = UR + kRingStep;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+  const int grp = wave / S, sw = wave % S, n = lane % 16, g = lane / 16;
+  const int rowvec = a.NCOL * Op::kVecs;
+  Acc acc[1][NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[0][t] = Acc{0, 0, 0, 0};
+  for (int u = piece.y; u < piece.z; ++u) {
+    const int4 U = a.units[u];
+    const int lo = U.x + a.K, nv = UR * rowvec;
+    __syncthreads();
+    for (int i = tid; i < nv; i += 64 * W) {
+      int off;
+      bool zero;
+      typename Op::Vec v =
+          ring_load<Op, RS, RAGGED>(a, in, lo, U.y, i, nv, py0, px0, rowvec, off, zero);
+      if (zero) v = typename Op::Vec{};
+      Op::write_guard(lds + (off & 0xffffff), off >> 24, v);
+    }
+    __syncthreads();
+    const int s0 = ((grp * RW + lo) % RS) * a.row_bytes;
+    for (int b = U.z + sw; b < U.w; b += S) {
+      const typename Op::Guard f = Op::load_guard(pack, b, lane);
+      const unsigned first = (unsigned)(a.meta[b * kLaneGroups + g] + n * Op::kCol + s0);
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        const unsigned q = first + r * a.row_bytes;
+        const unsigned char* row = lds + min(q, q - RS * a.row_bytes);
+#pragma unroll
+        for (int t = 0; t < TPR; ++t)
+          Op::mma_guard(f, row + t * 16 * Op::kCol, acc[0][r * TPR + t]);
+      }
+    }
+  }
+  ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, tid, py0, px0);
+}
+
 // The bundle loop is a pipeline of phases of kTiles position tiles: the fragments of a phase are
 // read from the LDS while the phase before multiplies, the LDS offset of a bundle is loaded two
 // bundles ahead and its table fragments between one and two.  Left to the compiler, which
@@ -349,10 +534,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
   constexpr int RS = UR + ST;     // rows of the ring
   constexpr int PF = Op::kBlocked ? 2 : BR == 8 ? 4 : 3;  // staged vectors in flight per thread
   constexpr int TH = 64 * W;
-  constexpr int MH = Op::kHalves, TM = kTile * MH;
+  constexpr int MH = Op::kHalves;
   static_assert(W % P == 0 && BR % P == 0 && NT % XT == 0 && XT % TPR == 0 && NT % S == 0, "shape");
   const int4 piece = a.pieces[blockIdx.y];
-  const int tile = piece.x;
   const int py0 = (blockIdx.x / a.ncc) * BR, px0 = (blockIdx.x % a.ncc) * BC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int grp = wave / S, sw = wave % S;
@@ -515,47 +699,20 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
       }
     }
   }
-  // the output, or for a piece of a cut tile its partial slot: the sums over the S waves of a
-  // group in wave order, S tiles per phase
-  using In = typename Op::In;
-  In* slot = piece.w >= 0 ? reinterpret_cast<In*>(a.partial) +
-                                ((long long)piece.w * a.n_patches + blockIdx.x) * (BR * BC * TM)
-                          : nullptr;
-  Acc* red = reinterpret_cast<Acc*>(lds);
+  const bool finite = ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, threadIdx.x, py0, px0);
+  if constexpr (Op::kGuard) {
+    __syncthreads();
+    int* flag = reinterpret_cast<int*>(lds);
+    const int mine = __any(!finite);
+    if (lane == 0) flag[wave] = mine;
+    __syncthreads();
+    int any = 0;
 #pragma unroll
-  for (int p = 0; p < NT; p += S) {
-    Acc v[MH];
-    if constexpr (S > 1) {
-      __syncthreads();  // the ring, or the phase before
-#pragma unroll
-      for (int k = 0; k < S; ++k)
-#pragma unroll
-        for (int h = 0; h < MH; ++h) red[((wave * S + k) * MH + h) * 64 + lane] = acc[h][p + k];
-      __syncthreads();
-    }
-#pragma unroll
-    for (int h = 0; h < MH; ++h) {
-      if constexpr (S > 1) {
-        v[h] = red[((grp * S * S + sw) * MH + h) * 64 + lane];
-#pragma unroll
-        for (int s = 1; s < S; ++s) v[h] += red[(((grp * S + s) * S + sw) * MH + h) * 64 + lane];
-      } else {
-        v[h] = acc[h][p];
-      }
-    }
-    const int t = p + sw;
-    const int r = grp * RW + t / TPR, c = (t % TPR) * 16 + n;
-    const int py = py0 + r, px = px0 + c;
-    if (py < a.ny && px < a.nx) {
-      In* dst = slot ? slot + (r * BC + c) * TM
-                     : out + ((long long)py * a.nx + px) * a.out_len + TM * tile;
-#pragma unroll
-      for (int h = 0; h < MH; ++h)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = kTile * h + Op::row(i, g);
-          if (TM * tile + row < a.out_len) dst[row] = v[h][i];
-        }
+    for (int w = 0; w < W; ++w) any |= flag[w];
+    if (any) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));  // nothing is kept in registers for this
+      ring_guarded<Op, BR, BC, W, P, RAGGED>(pack, in, out, lds, a, piece, tid, py0, px0);
     }
   }
 }
