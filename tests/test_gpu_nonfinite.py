@@ -1,15 +1,18 @@
-"""NaN and infinities in the vectors of FP64 and FP32 applies.
+"""NaN and infinities in the vectors of FP64 and FP32 applies and of the signal filter.
 
 A row tile (16 outputs of a position) with a nonzero table entry for such a value meets it; in its
 other rows the product is 0 times that value.  An output with a nonzero entry for a NaN is NaN; one
 with a nonzero entry for an infinity, whose tile meets no other such value, is that infinity times
-the entry's sign.  Outputs in tiles that meet none are the sums of the finite values.
+the entry's sign.  Outputs in tiles that meet none are the sums of the finite values.  The filter's
+outputs further than its taps reach from such a sample are those of the samples within reach.
 
-Tolerance: that of the finite sums, as derived where the tile edges are tested."""
+Tolerances: those of the finite sums, as derived where the tile edges are tested."""
 import numpy as np
 import pytest
 
+from oracle import filters as ofil
 from oracle import operators as oops
+import workloads as W
 from test_gpu_apply_shapes import odd_start, on_scan, random_table
 
 pytestmark = pytest.mark.gpu
@@ -72,3 +75,27 @@ def test_applies_keep_nonfinite_values_where_the_table_meets_them(grid, dtype):
             tile = met["nan"] | met["inf"] | met["-inf"]
             assert tile.any() and not tile.all()
             assert np.all(np.abs(got - ref)[~tile] <= bound[~tile])
+
+
+@pytest.mark.parametrize("nt,L", [(64, 5), (257, 16), (40, 0)])
+def test_filter_spreads_a_nonfinite_sample_no_further_than_its_taps(nt, L):
+    cfg = W.config("tiny")
+    g = W.grid(5, 10e-6, 2, 10e-6, nt, 0, 0, ny=3)
+    f = dict(f_lo_hz=0.5e6, f_hi_hz=80e6, half_taps=L)
+    h = ofil.bandpass_taps(f["f_lo_hz"], f["f_hi_hz"], g["fs_hz"], L)
+    rng = np.random.default_rng(nt)
+    with P.Model(cfg["sensor"], g, dtypes=("fp64", "fp32"), filter=f) as m:
+        for npt, u in ((np.float64, 2.0 ** -53), (np.float32, 2.0 ** -24)):
+            v = rng.standard_normal((3, 5, nt)).astype(npt)
+            ref = ofil.filter_time(v.astype(np.float64), h)
+            bound = (2 * np.sqrt(2 * L + 1) + 8) * u * ofil.filter_time(np.abs(v).astype(np.float64),
+                                                                        np.abs(h))
+            at = rng.integers(0, nt, (3, 5))
+            bad = np.where(rng.random((3, 5)) < 0.5, np.nan, np.inf).astype(npt)
+            np.put_along_axis(v, at[..., None], bad[..., None], axis=2)
+            print(f"[filter, non-finite nt {nt} L {L} {npt.__name__}]", flush=True)
+            got = m.filter_signals(torch.from_numpy(v).cuda()).cpu().numpy().astype(np.float64)
+            reached = np.abs(np.arange(nt) - at[..., None]) <= L
+            inner = np.abs(np.arange(nt) - at[..., None]) <= max(0, L - 1)  # the outer taps may be 0
+            assert not np.isfinite(got[inner]).any()
+            assert np.all(np.abs(got - ref)[~reached] <= bound[~reached])
