@@ -103,15 +103,19 @@ __device__ __forceinline__ unsigned live_entries(const T (&v)[N], int g) {
   return keep;
 }
 
-// FP32 on the BF16 MFMA: every FP32 value is the exact sum of three BF16 values (8 bits each,
-// rounded to nearest in turn), and a product is the six products of parts whose exponents
-// add up to no less than 2^-16 of the leading one; the three left out are below 2^-24 of it.
-// The sums run in FP32.  Six BF16 MFMAs of K = 32 take 96 cycles where the eight FP32 MFMAs of
-// K = 4 take 256, and round the sum less often: the 400 x 400 forward took 181 ms on
-// v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes 95 ms at 1.9e-6 (200 x 200
-// adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  A workgroup whose sums are not finite takes them
-// again on FP32 MFMAs (ring_guarded), since the parts of an infinity are not its sum.  Splitting at
-// the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
+// FP32 on the BF16 MFMA: an FP32 value is the exact sum of three BF16 values (8 bits each, rounded
+// to nearest in turn) where the last of them is not below BF16's smallest normal number.  That holds
+// for all FP32 numbers after a scaling by powers of two, which the outputs take back: operands by
+// 2^kF32OperandExp, the table by a power chosen from its range (set_f32_scale; OpF32Far where there
+// is none).  Operands beyond 2^104 become infinite; a workgroup whose sums are not finite, for this
+// or any other reason, takes them again on FP32 MFMAs (ring_guarded).  Without the scaling, operands
+// of 2^-120 lost 6e-5 of their value; it costs nothing that could be measured.
+// A product is the six products of parts whose exponents add up to no less than 2^-16 of the leading
+// one; the three left out are below 2^-24 of it.  The sums run in FP32.  Six BF16 MFMAs of K = 32
+// take 96 cycles where the eight FP32 MFMAs of K = 4 take 256, and round the sum less often: the
+// 400 x 400 forward took 181 ms on v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes
+// 95 ms at 1.9e-6 (200 x 200 adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  Splitting at the staging
+// costs nothing visible: a staged entry feeds hundreds of MFMAs.
 struct OpF32 {
   using In = float;
   using Vec = floatx4;             // 16 staged bytes
@@ -143,17 +147,14 @@ struct OpF32 {
     return x;
   }
   static __device__ __forceinline__ void write(unsigned char* col, int v, Vec f) {
+    constexpr float kScale = 1 << kF32OperandExp;
     u32x2 part[3];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      floatx2 r = {f[2 * h], f[2 * h + 1]};
-      // the largest finite BF16, so that rounding a finite value never gives an infinity
-      constexpr float kMax = 3.3895313892515355e38f;
-      floatx2 c = {__builtin_amdgcn_fmed3f(r[0], -kMax, kMax),
-                   __builtin_amdgcn_fmed3f(r[1], -kMax, kMax)};
+      floatx2 r = {f[2 * h] * kScale, f[2 * h + 1] * kScale};
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(i ? r : c, bf16x2));
+        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
         part[i][h] = w;
         r[0] -= __uint_as_float(w << 16);
         r[1] -= __uint_as_float(w & 0xffff0000u);
@@ -179,13 +180,13 @@ struct OpF32 {
   static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
 
   // The guarded sweep: FP32 entries, a column's eight after one another, on FP32 MFMAs.
-  static constexpr bool kGuard = true;
+  static constexpr bool kGuard = true, kScaled = true;
   struct Guard {
     float v[8];
     unsigned keep;
   };
   static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
-                                                     int lane) {
+                                                     int lane, int exp) {
     A f;
     load_a(pack, b, lane, f);
     Guard r;
@@ -197,7 +198,7 @@ struct OpF32 {
         const uint32_t w = f.v[i][j / 2];
         e += __uint_as_float(j % 2 ? w & 0xffff0000u : w << 16);
       }
-      r.v[j] = e;
+      r.v[j] = ldexpf(e, -exp);
     }
     r.keep = live_entries(r.v, lane / 16);
     return r;
@@ -211,6 +212,52 @@ struct OpF32 {
       const float x = reinterpret_cast<const float*>(p)[j];
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j], a.keep >> j & 1 ? x : 0.0f, acc, 0, 0, 0);
     }
+  }
+};
+
+// FP32 on v_mfma_f32_16x16x4_f32, for tables whose entries are too far apart to be split after one
+// scaling (set_f32_scale): entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
+struct OpF32Far : OpF32 {
+  static constexpr bool kScaled = false;
+  struct A {
+    floatx4 v[2];
+  };
+  struct X {
+    floatx4 v[2];
+  };
+  static __device__ __forceinline__ void load_a(const void* __restrict__ pack, int b, int lane,
+                                                A& f) {
+    const floatx4* p = reinterpret_cast<const floatx4*>(pack) + (long long)b * 128 + lane;
+    f.v[0] = p[0];
+    f.v[1] = p[64];
+  }
+  static __device__ __forceinline__ X read_x(const unsigned char* p) {
+    X x;
+    x.v[0] = *reinterpret_cast<const floatx4*>(p);
+    x.v[1] = *reinterpret_cast<const floatx4*>(p + 16);
+    return x;
+  }
+  static __device__ __forceinline__ void write(unsigned char* col, int v, Vec f) {
+    write_guard(col, v, f);
+  }
+  template <int NX, int STEP, int H>
+  static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int t = 0; t < NX; ++t)
+        acc[t * STEP] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j / 4][j % 4], x[t].v[j / 4][j % 4],
+                                                             acc[t * STEP], 0, 0, 0);
+  }
+  static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
+                                                     int lane, int) {
+    A f;
+    load_a(pack, b, lane, f);
+    Guard r;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r.v[j] = f.v[j / 4][j % 4];
+    r.keep = live_entries(r.v, lane / 16);
+    return r;
   }
 };
 
@@ -258,13 +305,13 @@ struct OpF64 {
   }
   static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
 
-  static constexpr bool kGuard = true;
+  static constexpr bool kGuard = true, kScaled = false;
   struct Guard {
     double v[4];
     unsigned keep;
   };
   static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
-                                                     int lane) {
+                                                     int lane, int) {
     A f;
     load_a(pack, b, lane, f);
     Guard r;
@@ -302,7 +349,7 @@ struct OpBF16 {
   static constexpr int kTiles = 2;
   static constexpr int kHalves = 2;
   static constexpr bool kBlocked = true;
-  static constexpr bool kGuard = false;
+  static constexpr bool kGuard = false, kScaled = false;
   struct A {
     u32x4 v[2];
   };
@@ -346,6 +393,7 @@ struct RingArgs {
   int NCOL;            // staged columns
   int row_bytes;       // LDS bytes of a staged row
   int nxp, nyp;        // blocked input: padded columns and rows of a chunk
+  int exp;             // FP32: the pack holds the parts of the table times 2^exp
 };
 
 // Staged vectors in flight: the 16-byte pieces of the rows a unit adds.  off < 0: none.
@@ -395,12 +443,13 @@ __device__ __forceinline__ typename Op::Vec ring_load(const RingArgs& a,
 }
 
 // The output of a piece, or for a piece of a cut tile its partial slot: the sums over the S waves
-// of a group in wave order, S tiles per phase.  Returns whether the thread's sums are finite.
+// of a group in wave order, S tiles per phase, times 2^-shift.  Returns whether the thread's sums
+// are finite.
 template <class Op, int BR, int BC, int W, int P>
 __device__ __forceinline__ bool ring_store(const typename Op::Acc (&acc)[Op::kHalves][BR / P * BC / 16],
                                            unsigned char* lds, const RingArgs& a, const int4& piece,
                                            typename Op::In* __restrict__ out, int tid, int py0,
-                                           int px0) {
+                                           int px0, int shift) {
   using In = typename Op::In;
   using Acc = typename Op::Acc;
   constexpr int S = W / P, RW = BR / P, TPR = BC / 16, NT = RW * TPR;
@@ -448,7 +497,10 @@ __device__ __forceinline__ bool ring_store(const typename Op::Acc (&acc)[Op::kHa
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int row = kTile * h + Op::row(i, g);
-          if (TM * tile + row < a.out_len) dst[row] = v[h][i];
+          if (TM * tile + row < a.out_len) {
+            if constexpr (Op::kScaled) dst[row] = ldexpf(v[h][i], -shift);
+            else dst[row] = v[h][i];
+          }
         }
     }
   }
@@ -492,7 +544,7 @@ __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
     __syncthreads();
     const int s0 = ((grp * RW + lo) % RS) * a.row_bytes;
     for (int b = U.z + sw; b < U.w; b += S) {
-      const typename Op::Guard f = Op::load_guard(pack, b, lane);
+      const typename Op::Guard f = Op::load_guard(pack, b, lane, a.exp);
       const unsigned first = (unsigned)(a.meta[b * kLaneGroups + g] + n * Op::kCol + s0);
 #pragma unroll
       for (int r = 0; r < RW; ++r) {
@@ -504,7 +556,7 @@ __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
       }
     }
   }
-  ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, tid, py0, px0);
+  ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, tid, py0, px0, 0);
 }
 
 // The bundle loop is a pipeline of phases of kTiles position tiles: the fragments of a phase are
@@ -699,7 +751,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
       }
     }
   }
-  const bool finite = ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, threadIdx.x, py0, px0);
+  const bool finite = ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, threadIdx.x, py0, px0,
+                                                   kF32OperandExp + a.exp);
   if constexpr (Op::kGuard) {
     __syncthreads();
     int* flag = reinterpret_cast<int*>(lds);
@@ -1201,8 +1254,8 @@ int allow_full_lds(F kern, std::atomic<unsigned long long>& done) {
 }
 
 template <class Op, int BR>
-int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial, void* out,
-                hipStream_t st) {
+int launch_ring(const Model& m, const Layout& lay, const Pack& pk, const void* in, void* partial,
+                void* out, hipStream_t st) {
   constexpr int W = 4, P = 1;  // waves of a workgroup, row groups they form
   using In = typename Op::In;
   const bool ragged = !Op::kBlocked && lay.in.L % Op::kVec != 0;
@@ -1227,6 +1280,7 @@ int launch_ring(const Layout& lay, const Pack& pk, const void* in, void* partial
   a.classes = lay.d_classes;
   a.nxp = lay.in.nxp;
   a.nyp = lay.in.nyp;
+  a.exp = m.f32_exp;
   AROAM_CHECK(lay.TM == kTile * Op::kHalves && lay.BR == BR && lay.BC == kPatchCols &&
                   lay.NCOL == kPatchCols + 2 * a.K && lay.CH == Op::kVec * Op::kVecs &&
                   (!Op::kBlocked || lay.in.nxp >= (int)round_up(a.nx, kPatchCols) + 2 * a.K),
@@ -1317,12 +1371,11 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
     AROAM_TRY(launch_fp8(m, lay, pk, (const float*)in, buf, stage_parts(m, adjoint, dtype), out,
                          st));
   } else if (dtype == AROAM_FP64) {
-    AROAM_TRY((launch_ring<OpF64, 4>(lay, pk, in, buf, out, st)));
+    AROAM_TRY((launch_ring<OpF64, 4>(m, lay, pk, in, buf, out, st)));
   } else if (dtype == AROAM_FP32) {
-    if (lay.BR == 8)
-      AROAM_TRY((launch_ring<OpF32, 8>(lay, pk, in, buf, out, st)));
-    else
-      AROAM_TRY((launch_ring<OpF32, 4>(lay, pk, in, buf, out, st)));
+    auto launch = m.f32_far ? (lay.BR == 8 ? launch_ring<OpF32Far, 8> : launch_ring<OpF32Far, 4>)
+                            : (lay.BR == 8 ? launch_ring<OpF32, 8> : launch_ring<OpF32, 4>);
+    AROAM_TRY(launch(m, lay, pk, in, buf, out, st));
   } else {
     const PadGeom& pg = lay.in;
     const int nch = (int)ceil_div(pg.L, kRingBF16.G);
@@ -1332,7 +1385,7 @@ int launch_apply(const Model& m, bool adjoint, int dtype, const void* in, void* 
                        pg.nyp, pg.L, nch);
     const StageParts sp = stage_parts(m, adjoint, dtype);
     void* partial = static_cast<char*>(buf) + sp.input;
-    AROAM_TRY((launch_ring<OpBF16, kPatchRows>(lay, pk, buf, partial, out, st)));
+    AROAM_TRY((launch_ring<OpBF16, kPatchRows>(m, lay, pk, buf, partial, out, st)));
   }
   AROAM_HIP(hipGetLastError());
   return AROAM_OK;

@@ -115,7 +115,8 @@ struct Layout {
 
 struct Pack {
   void* d = nullptr;   // FP64 / BF16: [n_bundles * 4 * TM * G] elements; FP32: three BF16 parts of
-                       // each; FP8: [n_bundles][half][lane group][row][32] e4m3 bytes (kFp8Lane)
+                       // each (f32_far: its value); FP8: [n_bundles][half][lane group][row][32] e4m3
+                       // bytes (kFp8Lane)
   size_t bytes = 0;
 };
 
@@ -130,6 +131,10 @@ constexpr int kFp8ScaleLane[4] = {0, 1, 2, 3};
 // The FP8 operand takes one power-of-two scale per kFp8ScaleChunk entries of its fast axis; a stage
 // unit holds kFp8Chunk of them.
 constexpr int kFp8ScaleChunk = 64, kFp8Chunk = 32;
+
+// FP32 operands are multiplied by 2^kF32OperandExp before they are split into BF16 parts: the last
+// part of the smallest FP32 number is then a normal BF16 number.
+constexpr int kF32OperandExp = 24;
 
 struct Model {
   aroam_sensor sensor{};
@@ -154,6 +159,8 @@ struct Model {
   Layout r16f, r16a;             // LDS ring: BF16
   Layout f8f, f8a;               // bundles of the block-scaled FP8 MFMA
   Pack fwd_pack[4], adj_pack[4]; // indexed by aroam_dtype
+  int f32_exp = 0;               // the FP32 packs hold the parts of the table times 2^f32_exp, or
+  bool f32_far = false;          // its values, where no such power makes all parts normal
   // band-pass filter applied along time to the columns (and, by the caller, to the signals)
   bool filtered = false;
   aroam_filter filter{};

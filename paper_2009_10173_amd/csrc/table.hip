@@ -240,10 +240,34 @@ __global__ void k_pack(long long total, int G, int TM, bool adjoint,
   }
 }
 
-// FP32 pack of the ring layout: part p (three BF16 values whose sum is the FP32 value) of entry j
-// of row m of K-group 4 b + g goes to [b][p][g][m][j].
-__global__ void k_pack_f32(long long total, bool adjoint, const int4* __restrict__ groups, int nz,
-                           int nt, const int* __restrict__ colidx, const int* __restrict__ lo,
+// range[0] = largest, range[1] = smallest nonzero magnitude of the table's FP32 values (as bits).
+__global__ __launch_bounds__(256) void k_band_range(const double* __restrict__ band, long long n,
+                                                    unsigned* __restrict__ range) {
+  unsigned hi = 0, lo = ~0u;
+  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
+    const unsigned b = __float_as_uint((float)band[i]) & 0x7fffffffu;
+    hi = max(hi, b);
+    if (b) lo = min(lo, b);
+  }
+  for (int s = 1; s < 64; s <<= 1) {
+    hi = max(hi, (unsigned)__shfl_xor((int)hi, s));
+    lo = min(lo, (unsigned)__shfl_xor((int)lo, s));
+  }
+  if (threadIdx.x % 64 == 0) {
+    atomicMax(&range[0], hi);
+    atomicMin(&range[1], lo);
+  }
+}
+
+// Index of entry j of row m of K-group q in an FP32 pack of values: [q / 4][j / 4][q % 4][m][j % 4].
+__host__ __device__ inline long long f32_far_index(long long q, int m, int j) {
+  return ((q / kLaneGroups * 2 + j / 4) * 64 + q % kLaneGroups * kTile + m) * 4 + j % 4;
+}
+
+// FP32 pack of the ring layout: part p (three BF16 values whose sum is the FP32 value times 2^exp) of
+// entry j of row m of K-group 4 b + g goes to [b][p][g][m][j]; far: the value to f32_far_index.
+__global__ void k_pack_f32(long long total, bool adjoint, int exp, bool far,
+                           const int4* __restrict__ groups, int nz, int nt, const int* __restrict__ colidx, const int* __restrict__ lo,
                            const long long* __restrict__ off, const double* __restrict__ band,
                            uint16_t* __restrict__ pack) {
   constexpr int G = kRingF32.G;
@@ -255,9 +279,13 @@ __global__ void k_pack_f32(long long total, bool adjoint, const int4* __restrict
     const int n = adjoint ? gd.y + j : kTile * gd.z + m;
     const int k = adjoint ? kTile * gd.z + m : gd.y + j;
     float r = (float)table_value(gd.x, n, k, nz, nt, colidx, lo, off, band);
+    if (far) {
+      reinterpret_cast<float*>(pack)[f32_far_index(grp, m, j)] = r;
+      continue;
+    }
+    r = ldexpf(r, exp);
     for (int p = 0; p < 3; ++p) {
-      const float c = p ? r : fminf(fmaxf(r, -3.3895313892515355e38f), 3.3895313892515355e38f);
-      const uint16_t b = cvt<uint16_t>((double)c);
+      const uint16_t b = cvt<uint16_t>((double)r);
       pack[(((grp / kLaneGroups) * 3 + p) * kLaneGroups + grp % kLaneGroups) * (kTile * G) + m * G + j] = b;
       r -= __uint_as_float((uint32_t)b << 16);
     }
@@ -319,6 +347,35 @@ __global__ void k_pack_fp8(long long total, bool adjoint, const int4* __restrict
     }
     pack[((bi * 2 + h) * 64 + ln * 16 + n) * 32 + slot * 8 + j] = code;
   }
+}
+
+// Choose the power of two by which the FP32 packs' parts are scaled: the largest entry comes to
+// 2^12, with room for sums of products with operands up to 2^80 or so, or is only scaled down by
+// what the operand is scaled up (no bits are lost at either end).  Entries more than 2^115 below the
+// largest would have subnormal parts: such a table is packed as it is, for the FP32 MFMA.
+int set_f32_scale(Model& m, hipStream_t st) {
+  unsigned h[2] = {0, ~0u}, *d = nullptr;
+  AROAM_HIP(hipMalloc((void**)&d, sizeof h));
+  bool ok = hipMemcpyAsync(d, h, sizeof h, hipMemcpyHostToDevice, st) == hipSuccess;
+  if (ok && m.nnz_stored > 0)
+    hipLaunchKernelGGL(k_band_range, dim3((unsigned)std::min<long long>(ceil_div(m.nnz_stored, 256), 2048)),
+                       dim3(256), 0, st, m.d_band, m.nnz_stored, d);
+  ok = ok && hipGetLastError() == hipSuccess &&
+       hipMemcpyAsync(h, d, sizeof h, hipMemcpyDeviceToHost, st) == hipSuccess;
+  ok = hipStreamSynchronize(st) == hipSuccess && ok;
+  (void)hipFree(d);
+  AROAM_CHECK(ok, AROAM_EDEVICE, "the range of the table could not be read");
+  if (h[0] == 0) return AROAM_OK;  // a table of zeros
+  float hi, lo;
+  std::memcpy(&hi, &h[0], 4);
+  std::memcpy(&lo, &h[1], 4);
+  if (!std::isfinite(hi)) {
+    m.f32_far = true;
+    return AROAM_OK;
+  }
+  m.f32_exp = std::max(-kF32OperandExp, 12 - std::ilogb(hi));
+  m.f32_far = std::ilogb(lo) + m.f32_exp < -103;  // the last of 24 bits below 2^-126
+  return AROAM_OK;
 }
 
 template <typename T>
@@ -946,13 +1003,13 @@ int pack_dtype(const Model& m, const Layout& lay, bool adjoint, Pack& p, hipStre
 int pack_f32(const Model& m, const Layout& lay, bool adjoint, Pack& p, hipStream_t st,
              size_t& bytes) {
   const long long total = lay.n_bundles * kLaneGroups * kTile * kRingF32.G;
-  p.bytes = std::max<long long>(1, total) * 3 * sizeof(uint16_t);
+  p.bytes = std::max<long long>(1, total) * (m.f32_far ? sizeof(float) : 3 * sizeof(uint16_t));
   AROAM_HIP(hipMalloc(&p.d, p.bytes));
   bytes += p.bytes;
   if (total > 0) {
     const int blocks = (int)std::min<long long>(ceil_div(total, 256), 1 << 16);
-    hipLaunchKernelGGL(k_pack_f32, dim3(blocks), dim3(256), 0, st, total, adjoint, lay.d_groups,
-                       m.grid.nz, m.grid.nt, m.d_colidx, m.d_lo, m.d_off, m.d_band, (uint16_t*)p.d);
+    hipLaunchKernelGGL(k_pack_f32, dim3(blocks), dim3(256), 0, st, total, adjoint, m.f32_exp,
+                       m.f32_far, lay.d_groups, m.grid.nz, m.grid.nt, m.d_colidx, m.d_lo, m.d_off, m.d_band, (uint16_t*)p.d);
     AROAM_HIP(hipGetLastError());
   }
   return AROAM_OK;
@@ -1303,6 +1360,7 @@ int set_columns(Model& m, const std::vector<int>& foi, const std::vector<int>& f
 
 // Band tiles of the always-packed dtypes (FP64 direct form, FP32 staged form).
 int pack_fp(Model& m, hipStream_t st, size_t& bytes) {
+  AROAM_TRY(set_f32_scale(m, st));
   // band tiles
   for (const bool adj : {false, true}) {
     const int L = adj ? m.grid.nt : m.grid.nz;
@@ -1388,7 +1446,7 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
   const size_t n_groups = (size_t)lay.n_bundles * (fp8 ? 16 : kLaneGroups);
   std::vector<int4> groups;
   AROAM_TRY(download(groups, lay.d_groups, n_groups));
-  const size_t esize = dtype == AROAM_FP32 ? 6 : dtype == AROAM_BF16 ? 2 : 1;
+  const size_t esize = dtype == AROAM_FP32 ? (m.f32_far ? 4 : 6) : dtype == AROAM_BF16 ? 2 : 1;
   std::vector<uint8_t> raw;
   AROAM_TRY(download(raw, pk.d, n_groups * TM * G * esize));
   std::vector<int> rec;
@@ -1407,7 +1465,11 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
         const int k = adjoint ? TM * gd.z + r : gd.y + j;
         if (n >= nt || k >= nz) continue;
         double v;
-        if (dtype == AROAM_FP32) {
+        if (dtype == AROAM_FP32 && m.f32_far) {
+          float f;
+          std::memcpy(&f, &raw[4 * (size_t)f32_far_index((long long)q, r, j)], 4);
+          v = f;
+        } else if (dtype == AROAM_FP32) {
           v = 0;  // the sum of the three parts
           for (size_t p = 0; p < 3; ++p) {
             const size_t e = (((q / kLaneGroups) * 3 + p) * kLaneGroups + q % kLaneGroups) * TM * G +
@@ -1417,6 +1479,7 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
             std::memcpy(&f, &bits, 4);
             v += f;
           }
+          v = std::ldexp(v, -m.f32_exp);
         } else if (dtype == AROAM_BF16) {
           const size_t e = q * TM * G + (size_t)r * G + j;
           const uint32_t bits = (uint32_t)(raw[2 * e] | (raw[2 * e + 1] << 8)) << 16;
