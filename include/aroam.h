@@ -18,8 +18,9 @@
  *     AROAM_FP8E4M3 name the precision of the model table and operands inside the apply;
  *     the caller's vectors stay FP32).  AROAM_FP32: every FP32 table entry and operand, scaled by
  *     a power of two, is split into three BF16 values whose sum it is, and a product is the six
- *     products of parts above 2^-24 of it, accumulated in FP32 (results are closer to FP64 than
- *     with FP32 products); FP32 products for a table with entries more than 2^115 apart.
+ *     products of parts above 2^-24 of it, accumulated in FP32 (the error of a long sum is a
+ *     third to a sixth of that with FP32 products, of a sum of a few up to 1.25 times it); FP32
+ *     products for a table with entries more than 2^115 apart.
  *     AROAM_FP64, AROAM_FP32: an infinite entry times a nonzero table entry is an infinity; in the
  *     other rows of a 16-row output tile that meets a non-finite entry, the product is 0 times it.
  *     AROAM_BF16: table and operand rounded to BF16

@@ -111,11 +111,18 @@ __device__ __forceinline__ unsigned live_entries(const T (&v)[N], int g) {
 // or any other reason, takes them again on FP32 MFMAs (ring_guarded).  Without the scaling, operands
 // of 2^-120 lost 6e-5 of their value; it costs nothing that could be measured.
 // A product is the six products of parts whose exponents add up to no less than 2^-16 of the leading
-// one; the three left out are below 2^-24 of it.  The sums run in FP32.  Six BF16 MFMAs of K = 32
-// take 96 cycles where the eight FP32 MFMAs of K = 4 take 256, and round the sum less often: the
-// 400 x 400 forward took 181 ms on v_mfma_f32_16x16x4_f32 at a relative error of 6.8e-6, and takes
-// 95 ms at 1.9e-6 (200 x 200 adjoint: 8.05 ms, 2.3e-6 and 4.26 ms, 1.2e-6).  Splitting at the staging
-// costs nothing visible: a staged entry feeds hundreds of MFMAs.
+// one; the three left out are below 2^-24 of it (0.24 2^-24 rms).  The BF16 MFMA cuts its sum to
+// FP32 less exactly than an FP32 addition rounds, so a bundle's leading products and its smaller ones
+// are summed from zero (the leading product of a single entry is exact in FP32) and then added to
+// the accumulator.  Six MFMAs in a row on the accumulator cut the running sum six times a bundle: the
+// 400 x 400 forward took 90.0 ms at a relative error of 1.9e-6 instead of 99.6 at 4.2e-7, the
+// 200 x 200 adjoint 4.10 ms at 1.2e-6 instead of 4.55 at 3.0e-7, and outputs of one to ten products
+// came out 1.3 to 1.4 times as far off as sums of FP32 products (now 1.0 to 1.2 times).  Against eight
+// FP32 MFMAs of K = 4, which take 256 cycles where the six take 96 (400 x 400 forward 181 ms at
+// 6.8e-6, 200 x 200 adjoint 8.05 ms at 2.3e-6), the sum is rounded less often.  With two of the three
+// products that are left out the 400 x 400 forward took 126 ms instead of 102, at the same error.
+// Tile after tile: with the MFMAs of two tiles alternating the 200 x 200 adjoint takes 1.5 % longer.
+// Splitting at the staging costs nothing visible: a staged entry feeds hundreds of MFMAs.
 struct OpF32 {
   using In = float;
   using Vec = floatx4;             // 16 staged bytes
@@ -167,14 +174,19 @@ struct OpF32 {
   // the MFMAs of a bundle's half H for NX tiles whose accumulators lie STEP apart
   template <int NX, int STEP, int H>
   static __device__ __forceinline__ void mma(const A& a, const X (&x)[NX], Acc* acc) {
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, px[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int pa[5] = {2, 0, 1, 1, 0}, px[5] = {0, 2, 1, 0, 1};  // ascending size
 #pragma unroll
-    for (int i = 0; i < 6; ++i)
+    for (int t = 0; t < NX; ++t) {
+      const Acc high = product(a, 0, x[t], 0, Acc{0, 0, 0, 0});
+      Acc low = {0, 0, 0, 0};
 #pragma unroll
-      for (int t = 0; t < NX; ++t)
-        acc[t * STEP] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8, a.v[pa[i]]), __builtin_bit_cast(bf16x8, x[t].v[px[i]]),
-            acc[t * STEP], 0, 0, 0);
+      for (int i = 0; i < 5; ++i) low = product(a, pa[i], x[t], px[i], low);
+      acc[t * STEP] += high + low;
+    }
+  }
+  static __device__ __forceinline__ Acc product(const A& a, int i, const X& x, int j, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.v[i]),
+                                                   __builtin_bit_cast(bf16x8, x.v[j]), c, 0, 0, 0);
   }
   // output row (within the tile) of accumulator element i of lane group g
   static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
@@ -642,14 +654,18 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
 
   const int u0 = piece.y, u1 = piece.z;
   if (u0 < u1) {
-    // Table fragments: two bundles of the unit (r0, r1), and the first of the next one (n0), whose
-    // loads are issued when the unit starts.
+    // Table fragments: two bundles of the unit (r0, r1), and on eight rows the first of the next one
+    // (n0), whose loads are issued when the unit starts; on four rows its registers are spilled (200 x
+    // 200 adjoint 4.63 ms without, 5.00 with it; the 400 x 400 forward on eight rows 106 and 104).
+    constexpr bool kAhead = BR == 8;
     Bundle r0, r1, n0;
     auto load_mo = [&](Bundle& r, int b) { r.mo = a.meta[b * kLaneGroups + g]; };
     auto load_a = [&](Bundle& r, int b) { Op::load_a(pack, b, lane, r.a); };
     int4 U = a.units[u0];
-    load_mo(n0, min(U.z + sw, U.w - 1));
-    load_a(n0, min(U.z + sw, U.w - 1));
+    if constexpr (kAhead) {
+      load_mo(n0, min(U.z + sw, U.w - 1));
+      load_a(n0, min(U.z + sw, U.w - 1));
+    }
     fetch(U, U.x + a.K);
     stage(U, U.x + a.K);
     __syncthreads();
@@ -658,11 +674,18 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 
       const int2 C = MH > 1 ? a.classes[u] : make_int2(0, 0);
       // rows the next unit finds in the ring: those of this unit, in the same chunk
       const int lo = Un.y == U.y && Un.x < U.x + UR ? U.x + a.K + UR : Un.x + a.K;
-      r0 = n0;
+      if constexpr (kAhead) {
+        r0 = n0;
+      } else {
+        load_mo(r0, min(U.z + sw, U.w - 1));
+        load_a(r0, min(U.z + sw, U.w - 1));
+      }
       load_mo(r1, min(U.z + sw + S, U.w - 1));
       load_a(r1, min(U.z + sw + S, U.w - 1));
-      load_mo(n0, min(Un.z + sw, Un.w - 1));
-      load_a(n0, min(Un.z + sw, Un.w - 1));
+      if constexpr (kAhead) {
+        load_mo(n0, min(Un.z + sw, Un.w - 1));
+        load_a(n0, min(Un.z + sw, Un.w - 1));
+      }
       fetch(Un, lo);
       // LDS offset of the wave's first row at the unit's first row offset (the same for all
       // lanes); a wave whose rows have no output row or no input row inside the scan skips the
