@@ -245,9 +245,9 @@ int aroam_forward(const aroam_model* model, int dtype, const void* x, void* s, v
  * the memory pool.  Every call on one GPU shares that array: calls that overlap on one GPU
  * (on different streams, or from different threads) race and give undefined results;
  * serialise them.  The array needs no clearing: each call writes all of it that it reads.
- * Errors: as aroam_forward, plus AROAM_EINVAL when the apply needs more than the 64 MiB
- * (the message gives the size; the 200x200 workload's forward needs 33 MB, a 400x400 one
- * with 256 depths about 0.25 GB). */
+ * Errors: as aroam_forward, plus AROAM_EINVAL when the padded input and the scratch come to more
+ * than the 64 MiB (the message gives the size; the 200x200 workload's forward counts 33 MB, a
+ * 400x400 one with 256 depths about 0.25 GB). */
 int aroam_forward_noalloc(const aroam_model* model, int dtype, const void* x, void* s,
                           void* stream);
 

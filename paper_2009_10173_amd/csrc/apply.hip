@@ -1229,8 +1229,7 @@ const Layout& layout_for(const Model& m, bool adjoint, int dtype) {
 namespace {
 
 // The stage buffer of an apply.  FP64 and FP32: the partial slots of a layout with cut tiles,
-// [slot][patch][position of the patch][tile rows]; the size is never below that of the zero-padded
-// input, which limits the allocation-free apply and is charged to a solve.  BF16 and FP8: the
+// [slot][patch][position of the patch][tile rows]; nothing where no tile is cut.  BF16 and FP8: the
 // padded input, then the partial slots (FP32), then for FP8 the operand's chunk scales: partial
 // maxima [chunk][kAmaxParts] (FP32), E8M0 bytes [chunk] (int) and inverse scales [chunk] (FP32).
 struct StageParts {
@@ -1256,7 +1255,7 @@ StageParts stage_parts(const Model& m, bool adjoint, int dtype) {
 
 size_t stage_bytes(const Model& m, bool adjoint, int dtype) {
   const StageParts p = stage_parts(m, adjoint, dtype);
-  if (dtype == AROAM_FP64 || dtype == AROAM_FP32) return std::max(p.input, p.partial);
+  if (dtype == AROAM_FP64 || dtype == AROAM_FP32) return p.partial;
   return p.input + p.partial + p.scales;
 }
 
@@ -1426,9 +1425,11 @@ int apply(const Model& m, bool adjoint, int dtype, const void* in, void* out, vo
   AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
               "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
   if (stage) return launch_apply(m, adjoint, dtype, in, out, stage, st);
+  const size_t need = stage_bytes(m, adjoint, dtype);
+  if (need == 0) return launch_apply(m, adjoint, dtype, in, out, nullptr, st);
   // a stage buffer of its own from the pool, returned to the pool on every path
   void* buf = nullptr;
-  AROAM_TRY(pool_alloc(&buf, stage_bytes(m, adjoint, dtype), st));
+  AROAM_TRY(pool_alloc(&buf, need, st));
   const int rc = launch_apply(m, adjoint, dtype, in, out, buf, st);
   const hipError_t e = hipFreeAsync(buf, st);
   if (rc != AROAM_OK) return rc;
@@ -1474,10 +1475,12 @@ int apply_noalloc(const Model& m, bool adjoint, int dtype, const void* in, void*
   const Layout& lay = layout_for(m, adjoint, dtype);
   AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
               "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
-  const size_t need = stage_bytes(m, adjoint, dtype);
+  // the padded input counts for FP64 and FP32 too, so that the limit is one of the scan's size
+  const size_t need =
+      std::max(stage_bytes(m, adjoint, dtype), stage_parts(m, adjoint, dtype).input);
   AROAM_CHECK(need <= kStaticScratchBytes, AROAM_EINVAL,
-              "the apply needs %zu bytes of scratch; the static buffer holds %zu", need,
-              (size_t)kStaticScratchBytes);
+              "the apply's padded input and scratch come to %zu bytes; the static buffer holds %zu",
+              need, (size_t)kStaticScratchBytes);
   void* buf = nullptr;
   AROAM_TRY(static_scratch(&buf));
   return launch_apply(m, adjoint, dtype, in, out, buf, st);

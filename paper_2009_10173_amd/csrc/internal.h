@@ -57,7 +57,7 @@ static_assert(max_k_half() == AROAM_MAX_K_HALF, "the header's k_half limit is th
 // Padded operand geometry.  BF16 and FP8 inputs of an apply are staged into a zero-padded buffer of
 // nyp x nxp x Lp entries with a halo of K columns on every lateral side, the scan rounded up to whole
 // patches and the fast axis to whole chunks.  (FP64 and FP32 are read from the caller's vector; the
-// padded size bounds their partial slots.)
+// padded size limits their partial slots and the scans of the allocation-free apply.)
 struct PadGeom {
   int K = 0, nx = 0, ny = 0;
   int nxp = 0, nyp = 0;

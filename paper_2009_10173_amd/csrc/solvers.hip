@@ -461,12 +461,18 @@ class SolverT final : public Solver {
     if (arena_) (void)hipFreeAsync(arena_, stream);
   }
 
+  // Stage buffer of one direction's applies, of either precision (never empty: applies without a
+  // buffer would allocate).
+  static size_t stage_room(const Model& m, bool adjoint, const aroam_solve_opts& o) {
+    return vec_bytes((long long)std::max(stage_bytes(m, adjoint, o.inner),
+                                         stage_bytes(m, adjoint, o.outer)), 1);
+  }
+
   // Device bytes the solver allocates (stage buffers, reductions, state, vectors).
   static size_t footprint(const Model& m, int kind, const aroam_solve_opts& o) {
     const long long ns = (long long)m.grid.ny * m.grid.nx * m.grid.nt;
     const long long nx = (long long)m.grid.ny * m.grid.nx * m.grid.nz;
-    size_t b = std::max(stage_bytes(m, false, o.inner), stage_bytes(m, false, o.outer)) +
-               std::max(stage_bytes(m, true, o.inner), stage_bytes(m, true, o.outer)) +
+    size_t b = stage_room(m, false, o) + stage_room(m, true, o) +
                3 * vec_bytes(kRedBlocks, 8) + 2 * vec_bytes(1, 512);
     const size_t e = sizeof(T);
     if (kind == 0) {
@@ -487,10 +493,8 @@ class SolverT final : public Solver {
                 "negative iteration count");
     size_ = footprint(m_, kind_, o_);
     AROAM_TRY(pool_alloc((void**)&arena_, size_, stream));
-    AROAM_TRY(alloc_bytes(&stage_f_, std::max(stage_bytes(m_, false, o_.inner),
-                                              stage_bytes(m_, false, o_.outer))));
-    AROAM_TRY(alloc_bytes(&stage_a_, std::max(stage_bytes(m_, true, o_.inner),
-                                              stage_bytes(m_, true, o_.outer))));
+    AROAM_TRY(alloc_bytes(&stage_f_, stage_room(m_, false, o_)));
+    AROAM_TRY(alloc_bytes(&stage_a_, stage_room(m_, true, o_)));
     AROAM_TRY(alloc_bytes((void**)&part0_, kRedBlocks * sizeof(double)));
     AROAM_TRY(alloc_bytes((void**)&part1_, 2 * kRedBlocks * sizeof(double)));
     partv_ = part1_ + kRedBlocks;
