@@ -1241,17 +1241,20 @@ StageParts stage_parts(const Model& m, bool adjoint, int dtype) {
   const Layout& lay = layout_for(m, adjoint, dtype);
   StageParts p;
   p.input = (size_t)round_up(lay.in.elems() * elem_bytes(dtype), 256);
+  p.chunks = dtype == AROAM_FP8E4M3 ? (int)ceil_div(lay.in.L, kFp8ScaleChunk) : 0;
+  p.scales = (size_t)round_up((size_t)p.chunks * (kAmaxParts + 2) * 4, 256);
   if (lay.n_slots > 0)
     p.partial = (size_t)lay.n_slots * lay.n_patches * lay.TM * lay.BR * lay.BC *
                 (dtype == AROAM_FP64 ? sizeof(double) : sizeof(float));
-  if (dtype == AROAM_FP8E4M3) {
-    p.chunks = (int)ceil_div(lay.in.L, kFp8ScaleChunk);
-    p.scales = (size_t)round_up((size_t)p.chunks * (kAmaxParts + 2) * 4, 256);
-  }
   return p;
 }
 
 }  // namespace
+
+size_t input_bytes(const Model& m, bool adjoint, int dtype) {
+  const StageParts p = stage_parts(m, adjoint, dtype);
+  return p.input + p.scales;
+}
 
 size_t stage_bytes(const Model& m, bool adjoint, int dtype) {
   const StageParts p = stage_parts(m, adjoint, dtype);
@@ -1475,9 +1478,10 @@ int apply_noalloc(const Model& m, bool adjoint, int dtype, const void* in, void*
   const Layout& lay = layout_for(m, adjoint, dtype);
   AROAM_CHECK(lay.lds_bytes <= kLdsBytes, AROAM_EINVAL,
               "lateral footprint too wide for the LDS stage (%zu bytes)", lay.lds_bytes);
-  // the padded input counts for FP64 and FP32 too, so that the limit is one of the scan's size
+  // The padded input counts for FP64 and FP32 too, so that the limit is one of the scan's size; the
+  // launches are planned so that the slots then fit as well.
   const size_t need =
-      std::max(stage_bytes(m, adjoint, dtype), stage_parts(m, adjoint, dtype).input);
+      std::max(stage_bytes(m, adjoint, dtype), input_bytes(m, adjoint, dtype));
   AROAM_CHECK(need <= kStaticScratchBytes, AROAM_EINVAL,
               "the apply's padded input and scratch come to %zu bytes; the static buffer holds %zu",
               need, (size_t)kStaticScratchBytes);

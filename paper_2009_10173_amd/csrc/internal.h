@@ -197,6 +197,8 @@ int export_quantized(const Model& m, int dtype, bool adjoint, double* dense, flo
 // apply.hip
 const Layout& layout_for(const Model& m, bool adjoint, int dtype);
 size_t stage_bytes(const Model& m, bool adjoint, int dtype);
+// Bytes of the padded input (FP8: and of its scales), which the layout has before it is planned.
+size_t input_bytes(const Model& m, bool adjoint, int dtype);
 // Apply A (adjoint = false) or A^T.  `in`/`out` are caller vectors of the dtype's element
 // type (double for FP64, float otherwise).  `stage` is a device buffer of at least
 // stage_bytes() bytes that the call may overwrite.

@@ -550,7 +550,6 @@ int set_plan(Layout& lay, const LaunchPlan& plan, size_t& bytes) {
 struct UnitPlan {
   std::vector<int> tile_units;                 // [tile + 1] first unit of each tile
   std::vector<std::vector<int>> units;         // [tile] its units: a piece may start at any
-  std::vector<std::vector<int>> chunk_starts;  // [tile] those at which a chunk starts
   std::vector<double> work;                    // [unit] MFMA row halves it issues
 };
 
@@ -564,11 +563,12 @@ int device_cus(const Model& m, int& cus) {
 constexpr int kStageChunk = 32;  // entries by which the BF16 input's axis is padded
 
 // Plan and upload a BF16 or FP8 launch (plan.h): two workgroups per CU, slots of at most 1 GiB.
-// `unit_cost` is added to every unit's work.  The allocation-free forward holds a padded input
-// of `input` bytes and the slots in the static scratch array; where cuts at chunk starts alone
-// (every kStageChunk entries for BF16, 64 for FP8) would fit it, finer ones are limited to fit too.
-int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, double unit_cost,
-                const PlanCosts& costs, double input, size_t& bytes) {
+// `unit_cost` is added to every unit's work.  The allocation-free forward holds the padded input and
+// the slots in the static scratch array: the slots of every scan whose input fits it are limited to
+// the rest of it.  That array is 64 MiB and scans of such a size have workgroups enough without cuts
+// (one of 330 x 330 x 160, K 32: 9 240 for 512 places), so the limit shortens no cut that would pay.
+int plan_staged(const Model& m, bool adjoint, int dtype, Layout& lay, const UnitPlan& up,
+                double unit_cost, const PlanCosts& costs, size_t& bytes) {
   int cus = 0;
   AROAM_TRY(device_cus(m, cus));
   const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * sizeof(float), most = 1ll << 30;
@@ -579,12 +579,8 @@ int plan_staged(const Model& m, bool adjoint, Layout& lay, const UnitPlan& up, d
                        slot_bytes, limit, 64, costs);
   };
   LaunchPlan p = plan(most);
-  const double room = (double)kStaticScratchBytes - (1 << 20) - input;
-  const double per_slot = slot_bytes * lay.n_patches;
-  if (!adjoint && room > 0 && p.n_slots * per_slot > room &&
-      plan_launch(up.tile_units, up.chunk_starts, up.work, lay.n_patches, 3 * cus, true, slot_bytes,
-                  most).n_slots * per_slot <= room)
-    p = plan(room);
+  const double room = (double)kStaticScratchBytes - (double)input_bytes(m, adjoint, dtype);
+  if (!adjoint && room >= 0 && p.n_slots * slot_bytes * lay.n_patches > room) p = plan(room);
   return set_plan(lay, p, bytes);
 }
 
@@ -651,7 +647,6 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
   std::vector<std::vector<char>> hits(NH, std::vector<char>((size_t)nch + 1));
   up.tile_units.assign(lay.n_tiles + 1, 0);
   up.units.resize(lay.n_tiles);
-  up.chunk_starts.resize(lay.n_tiles);
   std::vector<std::vector<UnitEntry>> per((size_t)nch * W);
   std::vector<UnitEntry> lst;
   for (int t = 0; t < lay.n_tiles; ++t) {
@@ -674,9 +669,7 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
         }
       }
     }
-    bool chunk_start = true;
     for (int c = 0; c < nch; ++c) {
-      if (c % (kStageChunk / rs.G) == 0) chunk_start = true;
       for (int R = 0; R < W;) {
         if (per[(size_t)c * W + R].empty()) {
           ++R;
@@ -710,8 +703,6 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
             if (mask == 2) ends.y = (int)after;
           }
           up.units[t].push_back((int)units.size());
-          if (chunk_start) up.chunk_starts[t].push_back((int)units.size());
-          chunk_start = false;
           units.push_back(make_int4(R0 - K, c * rs.G, (int)first, (int)(groups.size() / kLaneGroups)));
           classes.push_back(ends);
           up.work.push_back(work);
@@ -769,7 +760,7 @@ int build_bf16_layout(const Model& m, bool adjoint, Layout& lay, size_t& bytes) 
       pad_geom(m.grid, adjoint ? m.grid.nt : m.grid.nz, kPatchRows, kPatchCols, kStageChunk);
   UnitPlan up;
   AROAM_TRY(build_ring_layout(m, adjoint, kRingBF16, kPatchRows, pad, lay, up, bytes));
-  return plan_staged(m, adjoint, lay, up, kBf16Unit, kBf16Costs, 2.0 * lay.in.elems(), bytes);
+  return plan_staged(m, adjoint, AROAM_BF16, lay, up, kBf16Unit, kBf16Costs, bytes);
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
@@ -820,7 +811,6 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   std::vector<char> dx_any(W);
   UnitPlan up;
   up.units.resize(lay.n_tiles);
-  up.chunk_starts.resize(lay.n_tiles);
   struct Entry {
     int4 group;
     int off;   // LDS offset of the K-group's run
@@ -855,9 +845,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         }
       }
     }
-    bool chunk_start = true;
     for (int c = 0; c < nch; ++c) {
-      if (c % (kFp8ScaleChunk / CH) == 0) chunk_start = true;
       for (int R = 0; R < W;) {
         if (per[(size_t)c * W + R].empty()) {
           ++R;
@@ -865,8 +853,6 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         }
         // a unit takes kRingStep row offsets, whichever of them have K-groups
         up.units[t].push_back((int)units.size());
-        if (chunk_start) up.chunk_starts[t].push_back((int)units.size());
-        chunk_start = false;
         const int first_bundle = (int)(groups.size() / 16);
         // scale blocks: K-groups of equal key in one row, four at a time (a short block is padded
         // with null K-groups, whose table entries are zero).  A block's K-groups 0, 1 and 2, 3
@@ -980,7 +966,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
   up.tile_units = tile_units;
-  return plan_staged(m, adjoint, lay, up, kFp8Unit, kFp8Costs, 1.0 * lay.in.elems(), bytes);
+  return plan_staged(m, adjoint, AROAM_FP8E4M3, lay, up, kFp8Unit, kFp8Costs, bytes);
 }
 
 template <typename T>
