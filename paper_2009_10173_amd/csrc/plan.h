@@ -30,6 +30,31 @@ struct PlanCosts {
   double add_slot = 0.0;   // and each slot of its most cut tile
 };
 
+// Costs of a launch: of a unit, added to its work, and those besides.
+struct LaunchCosts {
+  double unit;
+  PlanCosts plan;
+};
+
+// FP64 and FP32, in bundles (of the 128 positions of a patch, about 0.1 us): a unit's staging and
+// barrier, a workgroup's first and last accesses, the slot sums.  Where few workgroups run, these are
+// what a finer cut has to pay for; measured on the 40 x 40 FISTA (1.13 -> 0.80 ms a pair of applies
+// with them, 1.02 with none), the 64 x 64 FP32 forward (177 -> 162 us, 177 with none) and the 23 x 19
+// FP64 one (75 -> 51 us, 56 with none).  Slots at 40 and 2 instead of 20 and 1 cut the smallest scans
+// too little: the 23 x 19 forward takes 51.6 us instead of 47.6, an LSQR solve on 16 x 16 368 instead
+// of 356; at 80 and 4 that takes 440.
+constexpr LaunchCosts kRingCosts{8, {24, 20, 1}};
+
+// BF16 in half bundles (of the 256 positions of a patch), FP8 in its own.  With them and cuts at any
+// unit, BF16 and FP8 applies of 40 x 40 to 96 x 96 scans take 0.32 to 0.75 of their time with cuts at
+// chunk starts (forward 96 x 96 x 64, K 20: BF16 172 -> 126 us, FP8 216 -> 151 us).  Larger or smaller
+// costs, and three or four workgroups per CU in the simulation, measured slower.  A BF16 unit costs
+// 30: with 16 the batch of three served scans takes 350 us instead of 332, with 44 the 200 x 200 x 128
+// forward 911 instead of 862.  FP8 units: 8 and 30 within 1 % of 16.
+constexpr LaunchCosts kBf16Costs{30, {60, 200, 6}}, kFp8Costs{16, {30, 60, 3}};
+
+constexpr int kMaxCut = 64;  // largest D of a launch
+
 struct LaunchPlan {
   std::vector<PlanPiece> pieces;     // in dispatch order
   std::vector<int> tile_pieces;      // [tile] pieces of the tile

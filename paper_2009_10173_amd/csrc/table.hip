@@ -563,58 +563,25 @@ int device_cus(const Model& m, int& cus) {
 constexpr int kStageChunk = 32;  // entries by which the BF16 input's axis is padded
 
 // Plan and upload a BF16 or FP8 launch (plan.h): two workgroups per CU, slots of at most 1 GiB.
-// `unit_cost` is added to every unit's work.  The allocation-free forward holds the padded input and
+// The allocation-free forward holds the padded input and
 // the slots in the static scratch array: the slots of every scan whose input fits it are limited to
 // the rest of it.  That array is 64 MiB and scans of such a size have workgroups enough without cuts
 // (one of 330 x 330 x 160, K 32: 9 240 for 512 places), so the limit shortens no cut that would pay.
 int plan_staged(const Model& m, bool adjoint, int dtype, Layout& lay, const UnitPlan& up,
-                double unit_cost, const PlanCosts& costs, size_t& bytes) {
+                const LaunchCosts& costs, size_t& bytes) {
   int cus = 0;
   AROAM_TRY(device_cus(m, cus));
   const double slot_bytes = (double)lay.TM * lay.BR * lay.BC * sizeof(float), most = 1ll << 30;
   std::vector<double> work(up.work);
-  for (double& w : work) w += unit_cost;
+  for (double& w : work) w += costs.unit;
   auto plan = [&](double limit) {
     return plan_launch(up.tile_units, up.units, work, lay.n_patches, 2 * cus, /*allow_cut=*/true,
-                       slot_bytes, limit, 64, costs);
+                       slot_bytes, limit, kMaxCut, costs.plan);
   };
   LaunchPlan p = plan(most);
   const double room = (double)kStaticScratchBytes - (double)input_bytes(m, adjoint, dtype);
   if (!adjoint && room >= 0 && p.n_slots * slot_bytes * lay.n_patches > room) p = plan(room);
   return set_plan(lay, p, bytes);
-}
-
-// Costs of a BF16 launch in half bundles (of the 256 positions of a patch), of an FP8 launch in
-// its own: as kRingCosts below.  With them and cuts at any unit, BF16 and FP8 applies of 40 x 40 to
-// 96 x 96 scans take 0.32 to 0.75 of their time with cuts at chunk starts (forward 96 x 96 x 64,
-// K 20: BF16 172 -> 126 us, FP8 216 -> 151 us).  Larger or smaller costs, and three or four
-// workgroups per CU in the simulation, measured slower.
-// A BF16 unit (four row offsets) costs 30: with 16 the batch of three served scans takes 350 us
-// instead of 332, with 44 the 200 x 200 x 128 forward 911 instead of 862.  FP8 units: 8 and 30 within 1 % of 16.
-constexpr double kBf16Unit = 30, kFp8Unit = 16;
-constexpr PlanCosts kBf16Costs{60, 200, 6}, kFp8Costs{30, 60, 3};
-
-// Costs of a ring launch in bundles (of the 128 positions of a patch, about 0.1 us): a unit's
-// staging and barrier, a workgroup's first and last accesses, the slot sums.  Where few
-// workgroups run, these are what a finer cut has to pay for; measured on the 40 x 40 FISTA
-// (1.13 -> 0.80 ms a pair of applies with them, 1.02 with none), the 64 x 64 FP32 forward (177 ->
-// 162 us, 177 with none) and the 23 x 19 FP64 one (75 -> 51 us, 56 with none).  Slots at 40 and 2
-// instead of 20 and 1 cut the smallest scans too little: the 23 x 19 forward takes 51.6 us instead
-// of 47.6, an LSQR solve on 16 x 16 368 instead of 356; at 80 and 4 that takes 440.
-constexpr double kUnitWork = 8;
-constexpr PlanCosts kRingCosts{24, 20, 1};
-
-// Patch rows of an FP32 ring launch.  Four rows leave room for three workgroups per CU while the
-// LDS holds three rings; a wider footprint (K = 34 .. 40) leaves two either way, and then eight
-// rows, which load the table half as often, are faster once the launch fills the chip (256 x 256
-// x 128: K 40 forward 15.9 ms on four rows, 14.6 on eight; K 30 10.8 and 10.9; 150 x 210 x 100, K 30
-// 4.1 and 4.5).  FP64 keeps four rows: eight would need twice the accumulators' registers.
-int ring_rows(int K, long long tiles, const aroam_grid& g, int cus) {
-  const long long patches = ceil_div(g.ny, 8) * ceil_div(g.nx, kPatchCols);
-  return 3 * ring_lds_bytes(K, 4) > kLdsBytes && 2 * ring_lds_bytes(K, 8) <= kLdsBytes &&
-                 patches * tiles >= 4 * cus
-             ? 8
-             : 4;
 }
 
 // LDS-ring form (FP64, FP32, BF16; see Layout and RingShape): a chunk is one K-group's run, and a
@@ -742,16 +709,16 @@ int build_plain_layout(const Model& m, bool adjoint, const RingShape& rs, const 
   int cus = 0;
   AROAM_TRY(device_cus(m, cus));
   const int tiles = (int)ceil_div(adjoint ? m.grid.nz : m.grid.nt, kTile);
-  const int BR = esize == sizeof(float) ? ring_rows(m.K, tiles, m.grid, cus) : 4;
+  const int BR = esize == sizeof(float) ? ring_rows(m.K, tiles, m.grid.nx, m.grid.ny, cus) : 4;
   UnitPlan up;
   AROAM_TRY(build_ring_layout(m, adjoint, rs, BR, pad, lay, up, bytes));
-  for (double& w : up.work) w += kUnitWork;
+  for (double& w : up.work) w += kRingCosts.unit;
   return set_plan(lay,
                   plan_launch(up.tile_units, up.units, up.work, lay.n_patches,
                               (BR == 8 ? 2 : 3) * cus, /*allow_cut=*/true,
                               (double)lay.TM * lay.BR * lay.BC * esize,
-                              std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), 64,
-                              kRingCosts),
+                              std::max((double)lay.in.elems() * esize, 32.0 * (1 << 20)), kMaxCut,
+                              kRingCosts.plan),
                   bytes);
 }
 
@@ -760,7 +727,7 @@ int build_bf16_layout(const Model& m, bool adjoint, Layout& lay, size_t& bytes) 
       pad_geom(m.grid, adjoint ? m.grid.nt : m.grid.nz, kPatchRows, kPatchCols, kStageChunk);
   UnitPlan up;
   AROAM_TRY(build_ring_layout(m, adjoint, kRingBF16, kPatchRows, pad, lay, up, bytes));
-  return plan_staged(m, adjoint, AROAM_BF16, lay, up, kBf16Unit, kBf16Costs, bytes);
+  return plan_staged(m, adjoint, AROAM_BF16, lay, up, kBf16Costs, bytes);
 }
 
 // ---- FP8 layouts: bundles of the block-scaled FP8 MFMA ---------------------------------
@@ -966,7 +933,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
   AROAM_TRY(alloc_copy(&lay.d_groups, groups, bytes));
   lay.n_patches = (int)(ceil_div(g.ny, BR) * ceil_div(g.nx, BC));
   up.tile_units = tile_units;
-  return plan_staged(m, adjoint, AROAM_FP8E4M3, lay, up, kFp8Unit, kFp8Costs, bytes);
+  return plan_staged(m, adjoint, AROAM_FP8E4M3, lay, up, kFp8Costs, bytes);
 }
 
 template <typename T>
