@@ -1283,9 +1283,12 @@ int launch_ring(const Model& m, const Layout& lay, const Pack& pk, const void* i
                 void* out, hipStream_t st) {
   constexpr int W = 4, P = 1;  // waves of a workgroup, row groups they form
   using In = typename Op::In;
-  const bool ragged = !Op::kBlocked && lay.in.L % Op::kVec != 0;
-  auto kern = ragged ? k_apply_ring<Op, BR, kPatchCols, W, P, true>
-                     : k_apply_ring<Op, BR, kPatchCols, W, P, false>;
+  auto kern = k_apply_ring<Op, BR, kPatchCols, W, P, false>;
+  bool ragged = false;
+  if constexpr (!Op::kBlocked) {  // a blocked input is padded to whole vectors
+    ragged = lay.in.L % Op::kVec != 0;
+    if (ragged) kern = k_apply_ring<Op, BR, kPatchCols, W, P, true>;
+  }
   static std::atomic<unsigned long long> attr_set[2];
   AROAM_TRY(allow_full_lds(kern, attr_set[ragged]));
   RingArgs a;

@@ -192,8 +192,6 @@ __device__ inline T cvt(double v);
 template <>
 __device__ inline double cvt<double>(double v) { return v; }
 template <>
-__device__ inline float cvt<float>(double v) { return (float)v; }
-template <>
 __device__ inline uint16_t cvt<uint16_t>(double v) {  // bf16, round to nearest even
   float f = (float)v;
   uint32_t u = __float_as_uint(f);
@@ -293,8 +291,7 @@ __global__ void k_pack_f32(long long total, bool adjoint, int exp, bool far,
 }
 
 // Per (offset, 16-depth block) FP32 scale: the smallest power of two >= amax / 448 of the
-// block's table values (powers of two let the kernel apply the scale inside the FP8 -> BF16
-// conversion).
+// block's table values (powers of two, which the block-scaled MFMA applies as E8M0 bytes).
 __global__ void k_block_scale(int n_off, int nz, const int* __restrict__ colidx,
                               const long long* __restrict__ off, const double* __restrict__ band,
                               float* __restrict__ scale) {
@@ -1311,10 +1308,9 @@ int set_columns(Model& m, const std::vector<int>& foi, const std::vector<int>& f
   return AROAM_OK;
 }
 
-// Band tiles of the always-packed dtypes (FP64 direct form, FP32 staged form).
+// Band tiles of the always-packed dtypes.
 int pack_fp(Model& m, hipStream_t st, size_t& bytes) {
   AROAM_TRY(set_f32_scale(m, st));
-  // band tiles
   for (const bool adj : {false, true}) {
     const int L = adj ? m.grid.nt : m.grid.nz;
     Layout& r64 = adj ? m.r64a : m.r64f;
