@@ -62,7 +62,7 @@ def kernel_times(model, dtype, x, s, reps):
 
 
 # Sources that decide what the apply kernels do and launch (kernels, layouts, launch plan).
-KERNEL_SOURCES = ("apply.hip", "table.hip", "plan.h", "internal.h")
+KERNEL_SOURCES = ("apply.hip", "table.hip", "plan.h", "staging.h", "internal.h")
 
 
 def kernel_code_digest():

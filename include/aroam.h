@@ -66,7 +66,8 @@ typedef enum { AROAM_FP64 = 0, AROAM_FP32 = 1, AROAM_BF16 = 2, AROAM_FP8E4M3 = 3
 
 /* Largest lateral model extent k_half (offsets -k_half .. k_half).  The FP8 applies keep,
  * per workgroup, 15 scan rows x (32 + 2 k_half) columns x 48 bytes of input in the 160 KiB LDS
- * of a compute unit (the other dtypes need less).  At the 5 um step this is about 0.97 mm of lateral extent. */
+ * of a compute unit (the other dtypes need less).  At the 5 um step this is about 0.97 mm of
+ * lateral extent. */
 #define AROAM_MAX_K_HALF 97
 
 /* Spherical-cap sensor (Methods, "Forward modeling", Eq. 3; "AR-OAM set-up").

@@ -71,16 +71,17 @@ constexpr size_t red_bytes(int S, int MH) { return (size_t)4 * S * MH * 64 * 16;
 // ------------------------------------------------------------------------------------------
 // LDS-ring applies (FP32, FP64 and BF16).
 //
-// A workgroup (W waves) owns one output tile of kHalves 16-row halves and a patch of BR x BC scan positions.  The
-// tile's bundles are grouped into stage units (chunk of the inner axis, kRingStep consecutive
-// input row offsets) in the order chunk, row.  The LDS holds the rows a unit reads (the patch's
+// A workgroup (W waves) owns one output tile of kHalves 16-row halves and a patch of BR x BC scan
+// positions.  The tile's bundles are grouped into stage units (chunk of the inner axis, kRingStep
+// consecutive input row offsets) in the order chunk, row.  The LDS holds the rows a unit reads (the patch's
 // columns and K more on each side, the chunk's entries) and room for kRingStep more, as a ring
 // indexed by padded row: a unit loads only the rows it adds into registers while the unit before
 // it computes, and one barrier makes them visible.  Four row offsets to a unit share one
 // barrier and one trip to memory and pool their bundles over the waves: against one, on chunks
-// of two runs, the 400 x 400 FP32 forward takes 94.8 ms instead of 105.4, the 64 x 64 one 150 us
-// instead of 161, the FP64 96 x 96 adjoint 1.32 ms instead of 1.40.  The rows come straight from the caller's vector; positions outside the
-// scan and entries past the end of the axis are written as zeros.  The waves form P row groups
+// of two runs, that took 10 % off the 400 x 400 FP32 forward of the time (105.4 -> 94.8 ms), 7 % off
+// the 64 x 64 one (161 -> 150 us) and 6 % off the FP64 96 x 96 adjoint (1.40 -> 1.32 ms).  The rows
+// come straight from the caller's vector (BF16: from k_stage_bf16); positions outside the scan and
+// entries past the end of the axis are written as zeros.  The waves form P row groups
 // of BR / P patch rows, and the S = W / P waves of a group take the bundles of each unit in
 // turn, so that a table fragment is loaded once per row group; at the end the S partial sums of
 // a position are added in wave order through the LDS.
@@ -274,8 +275,10 @@ struct OpF32Far : OpF32 {
 };
 
 // FP64 on v_mfma_f64_16x16x4_f64: entry j of the four K-groups' runs feeds a bundle's j-th MFMA.
-// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.32 ms; with positions read from
-// global memory it took 3.42 ms (bound by the texture path), with one FMA per load 68.4 ms.
+// The adjoint of a 96 x 96 scan (Nz 64, Nt 256, K 20) takes 1.31 ms, which is 61 TFLOP/s on what it
+// issues (of 78.6; MFMA busy 0.86): what is left are the zeros of the tiles, 0.58 of it.  With
+// positions read from global memory it took 3.42 ms (bound by the texture path), with one FMA per
+// load 68.4 ms.
 struct OpF64 {
   using In = double;
   using Vec = doublex2;
@@ -348,9 +351,10 @@ struct OpF64 {
 // come in the order half 0 alone, half 1 alone, both, so that each run's loop issues only the
 // MFMAs its bundles reach (a test per bundle cost 10 %).  Against one row offset to a unit on
 // chunks of 32 entries, reading ahead within a bundle only: the 200 x 200 x 128 forward (K 20)
-// takes 0.86 ms instead of 0.97, the 400 x 400 adjoint the same 20.2 (power), the refined 96 x 96
-// LSQR 39.6 instead of 41.8.  What bounds it are the reads of the position fragments (one LDS read
-// feeds two MFMAs, or one where a bundle reaches one half) and, on large scans, power.
+// takes 0.86 ms instead of 0.97, the refined 96 x 96 LSQR 39.6 instead of 41.8, the 400 x 400 adjoint
+// the same 20.2.  That one is bound by what an MFMA costs besides itself: a read of the position
+// fragments feeds 1.57 of them (MFMA busy 0.66), 50 registers are spilled (4 GB written an apply) and
+// the table stream misses the L2 in 0.58 of its requests (80 GB an apply from beyond it; 36 before).
 struct OpBF16 {
   using In = float;  // outputs; the input is read as k_stage_bf16 leaves it
   using Vec = u32x4;
@@ -573,15 +577,17 @@ __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
 
 // The bundle loop is a pipeline of phases of kTiles position tiles: the fragments of a phase are
 // read from the LDS while the phase before multiplies, the LDS offset of a bundle is loaded two
-// bundles ahead and its table fragments between one and two.  Left to the compiler, which
-// issued each read next to its use, the 400 x 400 FP32 forward took 114 ms (MFMA busy 0.61,
-// waves waiting 0.46 of their time); phases of four tiles take 105 ms, of two 104.6, and of
-// two within 168 registers (three waves per SIMD where the LDS allows) 102 ms and, for the 200 x
-// 200 adjoint, 4.46 ms instead of 4.71 (all with units of one row offset).  At that issue rate (1.4 PFLOP/s of BF16, a large library
-// product reaches 1.1) the chip lowers its clock from 2.1 to 1.7-1.8 GHz: what is left is power,
-// spent on the table stream (L2 and beyond) and on the zeros of the tiles besides the products.
+// bundles ahead and its table fragments between one and two.  Without the scheduling barriers the
+// compiler moves each read next to its use: 400 x 400 FP32 forward 102.5 -> 104.7 ms, 200 x 200
+// adjoint 4.67 -> 4.74, 40 x 40 FISTA 15.25 -> 15.94, 400 x 400 BF16 adjoint 19.9 -> 21.4.  Four rows
+// are held to 168 registers, for three waves per SIMD where the LDS allows; with two, the 200 x 200
+// adjoint takes 5.07 ms, the FISTA 19.3, the 64 x 64 forward 170 us instead of 156.  The FP32 forward
+// issues 1.46 PFLOP/s of BF16 products (a large library product reaches 1.1), at which the chip lowers
+// its clock from 2.1 to 1.7-1.9 GHz: besides the additions of the bundles' sums what is left is
+// power, spent on the table stream (L2 and beyond) and on the zeros of the tiles.
 template <class Op, int BR, int BC, int W, int P, bool RAGGED>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(BR == 8 ? 2 : 3))) void k_apply_ring(
+__global__ __launch_bounds__(64 * W)
+    __attribute__((amdgpu_waves_per_eu(BR == 8 ? 2 : 3))) void k_apply_ring(
     const void* __restrict__ pack, const typename Op::In* __restrict__ in,
     typename Op::In* __restrict__ out, RingArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];

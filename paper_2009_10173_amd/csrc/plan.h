@@ -5,8 +5,8 @@
 // A staged launch has one workgroup per (piece, position patch).  A piece is a range of one
 // output tile's stage units.  An uncut tile is one piece, which writes the output; a cut
 // tile is several pieces (each loads the whole LDS ring for its first unit), and each of them
-// writes its partial sums to its own slot, which a second kernel adds in slot order.  The slots of a tile are consecutive and follow the tile's unit order, so the
-// sum is deterministic.
+// writes its partial sums to its own slot, which a second kernel adds in slot order.  The slots of a
+// tile are consecutive and follow the tile's unit order, so the sum is deterministic.
 #pragma once
 
 #include <algorithm>

@@ -47,8 +47,9 @@ static_assert(ring_lds_bytes(max_k_half(), 4) <= kLdsBytes,
 // Patch rows of an FP32 ring launch.  Four rows leave room for three workgroups per CU while the
 // LDS holds three rings; a wider footprint (K = 35 .. 40) leaves two either way, and then eight
 // rows, which load the table half as often, are faster once the launch fills the chip (256 x 256
-// x 128: K 40 forward 15.9 ms on four rows, 14.6 on eight; K 30 10.8 and 10.9; 150 x 210 x 100, K 30
-// 4.1 and 4.5).  FP64 keeps four rows: eight would need twice the accumulators' registers.
+// x 128 forward: K 40 17.0 ms on four rows, 15.2 on eight; K 35 15.1 and 13.7; 150 x 210 x 100 adjoint,
+// K 38 7.0 and 5.6).  At K 30 four rows hold their third workgroup (11.6 and 11.3 ms; 150 x 210 x 100
+// 4.65 and 5.15).  FP64 keeps four rows: eight would need twice the accumulators' registers.
 inline int ring_rows(int K, long long tiles, int nx, int ny, int cus) {
   const long long patches = (long long)((ny + 7) / 8) * ((nx + kPatchCols - 1) / kPatchCols);
   return 3 * ring_lds_bytes(K, 4) > kLdsBytes && 2 * ring_lds_bytes(K, 8) <= kLdsBytes &&
