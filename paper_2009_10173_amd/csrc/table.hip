@@ -470,10 +470,10 @@ struct CompatTable {
 // Pair the K-groups of one stage unit so that bundle slots (0, 1) and (2, 3) read the LDS
 // without bank conflicts wherever possible: a greedy matching over the 16 classes (column mod
 // 16) that pairs the most constrained class first.  K-groups left without a partner are paired
-// with each other; an odd one out gets a zero padding K-group of a matching class (a null K-group
-// multiplies zero table entries).  The result is padded to whole bundles.
-std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<UnitEntry>& in,
-                                 int maxcol, int t) {
+// with each other.  An odd one out, and then the bundle, is filled up with null K-groups, which
+// multiply zero table entries.  They read what a real one beside them reads: so they meet a
+// non-finite entry only where that one meets it, and columns that agree mod 16 do not conflict.
+std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<UnitEntry>& in, int t) {
   std::vector<int> cls_items[16];
   for (int i = (int)in.size() - 1; i >= 0; --i) cls_items[in[i].col & 15].push_back(i);
   auto avail = [&](int a) {
@@ -509,22 +509,22 @@ std::vector<UnitEntry> pair_unit(const CompatTable& table, const std::vector<Uni
     out.push_back(in[ia]);
     out.push_back(in[ib]);
   }
-  const UnitEntry pad0{make_int4(-1, 0, t, 0), 0, 0};
+  auto null_of = [&](const UnitEntry& e) {
+    return UnitEntry{make_int4(-1, 0, t, e.group.w), e.col, 0};
+  };
   for (size_t i = 0; i + 1 < left.size(); i += 2) {
     out.push_back(in[left[i]]);
     out.push_back(in[left[i + 1]]);
   }
   if (left.size() % 2) {
     const UnitEntry& e = in[left.back()];
-    UnitEntry p = pad0;
-    for (int c = maxcol; c >= 0; --c)
-      if (pair_conflict_free(table.stride, e.col, c)) p.col = c;
     out.push_back(e);
-    out.push_back(p);
+    out.push_back(null_of(e));
   }
   if (out.size() % 4) {
-    out.push_back(pad0);
-    out.push_back(pad0);
+    const UnitEntry p = null_of(out[0]);
+    out.push_back(p);
+    out.push_back(p);
   }
   return out;
 }
@@ -656,8 +656,8 @@ int build_ring_layout(const Model& m, bool adjoint, const RingShape& rs, int BR,
                 if (e.mask == mask) lst.push_back(e);
             const size_t before = groups.size() / kLaneGroups;
             if (!lst.empty())
-              for (const UnitEntry& e : pair_unit(table, lst, 2 * K, t)) {
-                const int row = e.group.x < 0 ? 0 : e.group.w - R0;  // its row offset in the unit
+              for (const UnitEntry& e : pair_unit(table, lst, t)) {
+                const int row = e.group.w - R0;  // its row offset in the unit
                 groups.push_back(make_int4(e.group.x, e.group.y, e.group.z, e.group.x >= 0));
                 meta.push_back(row * row_bytes + e.col * rs.col_bytes);
               }
@@ -819,7 +819,9 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         up.units[t].push_back((int)units.size());
         const int first_bundle = (int)(groups.size() / 16);
         // scale blocks: K-groups of equal key in one row, four at a time (a short block is padded
-        // with null K-groups, whose table entries are zero).  A block's K-groups 0, 1 and 2, 3
+        // with null K-groups, whose table entries are zero and which read what a K-group beside them
+        // reads: the same addresses in the same read, so no bank is hit twice and a NaN code is met
+        // only where the other meets it).  A block's K-groups 0, 1 and 2, 3
         // sit in two lane groups at the same two 8-byte slots, and the 32 lanes of a pass of an
         // 8-byte LDS read hit distinct banks only when those two lane groups' runs (8-byte
         // steps within a column of 48 bytes) differ in parity: a block takes two K-groups of
@@ -840,7 +842,6 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
               ((lst[j].off / G) % 2 ? od : ev).push_back(lst[j]);
               ++j;
             }
-            const Entry null_even{null_group, 0, lst[i].key}, null_odd{null_group, G, lst[i].key};
             size_t a = 0, b = 0;
             while (a < ev.size() || b < od.size()) {
               std::vector<Entry> blk;
@@ -852,7 +853,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
                 else if (!want_even && b < od.size()) blk.push_back(od[b++]);
                 else if (a < ev.size()) blk.push_back(ev[a++]);
                 else if (b < od.size()) blk.push_back(od[b++]);
-                else blk.push_back(k < 2 ? null_even : null_odd);
+                else blk.push_back(Entry{null_group, blk[k < 2 ? k - 1 : k - 2].off, lst[i].key});
               }
               blocks[lst[i].key.x].push_back(blk);
             }
@@ -865,7 +866,7 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
                 pr.insert(pr.end(), blocks[mask][i + 1].begin(), blocks[mask][i + 1].end());
               else
                 for (int k = 0; k < 4; ++k)
-                  pr.push_back(Entry{null_group, k < 2 ? 0 : G, make_int4(mask, 127, 127, 0)});
+                  pr.push_back(Entry{null_group, pr[k].off, make_int4(mask, 127, 127, 0)});
               pr[0].group.w = r - R;  // the pair's row offset in the unit
               pairs[mask].push_back(pr);
             }
@@ -874,8 +875,11 @@ int build_fp8_layout(const Model& m, bool adjoint, const std::vector<float>& bsc
         int2 ends = make_int2(0, 0);  // of the bundles of half 0 alone, of half 1 alone
         for (int mask = 1; mask < 4; ++mask) {
           if (pairs[mask].size() % 2) {
-            std::vector<Entry> none(8, Entry{null_group, 0, make_int4(mask, 127, 127, 0)});
-            for (int k = 0; k < 8; ++k) none[k].off = k % 4 < 2 ? 0 : G;
+            std::vector<Entry> none = pairs[mask].back();
+            for (Entry& e : none) {
+              e.group = make_int4(-1, 0, 0, e.group.w);
+              e.key = make_int4(mask, 127, 127, 0);
+            }
             pairs[mask].push_back(none);
           }
           // bundles: pair 0 is scale blocks 0 and 2 (lane groups 0 and 1), pair 1 blocks 1 and 3

@@ -77,6 +77,37 @@ def test_applies_keep_nonfinite_values_where_the_table_meets_them(grid, dtype):
             assert np.all(np.abs(got - ref)[~tile] <= bound[~tile])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("grid", [(9, 33, 33, 95, 4), (13, 30, 48, 129, 6), (20, 40, 70, 200, 3)],
+                         ids=lambda g: "x".join(map(str, g)))
+def test_reduced_precision_spreads_nonfinite_values_by_whole_runs_alone(grid, dtype):
+    """BF16 and FP8 applies multiply runs of eight entries by row tiles of 16: a non-finite entry
+    reaches the outputs of tiles with a nonzero table entry for its run, and no others."""
+    ny, nx, nz, nt, K = grid
+    rng = np.random.default_rng(nt + K)
+    H = random_table(rng, nz, nt, K)
+    H[:, :, ::3] = 0  # runs and offsets without entries, so that bundles are filled up
+    H[rng.random(H.shape[:2]) < 0.6] = 0
+    g = dict(c_mps=1500.0, fs_hz=250e6, nx=nx, ny=ny, step_m=1e-5, nz=nz, dz_m=1e-5, nt=nt, k_half=K,
+             footprint_mode=0)
+    with P.Model.from_table(g, H, dtypes=("fp64", "fp32", dtype)) as m:
+        for name in ("forward", "adjoint"):
+            op, n_in = getattr(oops, name), nz if name == "forward" else nt
+            for value in (np.nan, np.inf):
+                v = rng.standard_normal((ny, nx, n_in)).astype(np.float32)
+                at = (int(rng.integers(ny)), int(rng.integers(nx)), int(rng.integers(n_in)))
+                v[at] = value
+                run, one = np.zeros(v.shape), np.zeros(v.shape)
+                run[at[0], at[1], at[2] // 8 * 8:at[2] // 8 * 8 + 8] = 1
+                one[at] = 1
+                print(f"[non-finite {grid} {dtype} {name} {value}]", flush=True)
+                got = getattr(m, name)(torch.from_numpy(v).cuda(), dtype).cpu().numpy()
+                bad = ~np.isfinite(got)
+                assert bad[on_scan(op, H, one) != 0].all()
+                met = tiles(on_scan(op, (H != 0).astype(np.float64), run) != 0)
+                assert not met.all() and not bad[~met].any()
+
+
 @pytest.mark.parametrize("nt,L", [(64, 5), (257, 16), (40, 0)])
 def test_filter_spreads_a_nonfinite_sample_no_further_than_its_taps(nt, L):
     cfg = W.config("tiny")
