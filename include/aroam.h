@@ -21,8 +21,9 @@
  *     products of parts above 2^-24 of it, accumulated in FP32 (the error of a long sum is a
  *     third to a sixth of that with FP32 products, of a sum of a few up to 1.25 times it); FP32
  *     products for a table with entries more than 2^115 apart.
- *     AROAM_FP64, AROAM_FP32: an infinite entry times a nonzero table entry is an infinity; in the
- *     other rows of a 16-row output tile that meets a non-finite entry, the product is 0 times it.
+ *     AROAM_FP64, AROAM_FP32, AROAM_BF16: an infinite entry times a nonzero table entry is an
+ *     infinity; in the other rows of a 16-row output tile that meets a non-finite entry, the product
+ *     is 0 times it.
  *     AROAM_BF16: table and operand rounded to BF16
  *     (nearest, ties to even), products accumulated in FP32.  AROAM_FP8E4M3: OCP e4m3 table
  *     with a power-of-two scale per (offset, 16-depth block) and e4m3 operand with a

@@ -193,7 +193,7 @@ struct OpF32 {
   static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
 
   // The guarded sweep: FP32 entries, a column's eight after one another, on FP32 MFMAs.
-  static constexpr bool kGuard = true, kScaled = true;
+  static constexpr bool kScaled = true;
   struct Guard {
     float v[8];
     unsigned keep;
@@ -219,6 +219,7 @@ struct OpF32 {
   static __device__ __forceinline__ void write_guard(unsigned char* col, int v, Vec f) {
     *reinterpret_cast<Vec*>(col + 16 * v) = f;
   }
+  template <int H>
   static __device__ __forceinline__ void mma_guard(const Guard& a, const unsigned char* p, Acc& acc) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -320,7 +321,7 @@ struct OpF64 {
   }
   static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
 
-  static constexpr bool kGuard = true, kScaled = false;
+  static constexpr bool kScaled = false;
   struct Guard {
     double v[4];
     unsigned keep;
@@ -338,6 +339,7 @@ struct OpF64 {
   static __device__ __forceinline__ void write_guard(unsigned char* col, int v, Vec f) {
     write(col, v, f);
   }
+  template <int H>
   static __device__ __forceinline__ void mma_guard(const Guard& a, const unsigned char* p, Acc& acc) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -365,7 +367,7 @@ struct OpBF16 {
   static constexpr int kTiles = 2;
   static constexpr int kHalves = 2;
   static constexpr bool kBlocked = true;
-  static constexpr bool kGuard = false, kScaled = false;
+  static constexpr bool kScaled = false;
   struct A {
     u32x4 v[2];
   };
@@ -394,6 +396,36 @@ struct OpBF16 {
                                                               acc[t * STEP], 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+
+  struct Guard {
+    A a;
+    u32x4 keep[2];  // per half: all bits of the live entries
+  };
+  static __device__ __forceinline__ Guard load_guard(const void* __restrict__ pack, int b,
+                                                     int lane, int) {
+    Guard r;
+    load_a(pack, b, lane, r.a);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t v[8];  // magnitudes
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = r.a.v[h][j / 2] >> 16 * (j % 2) & 0x7fff;
+      const unsigned keep = live_entries(v, lane / 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        r.keep[h][i] = (keep >> 2 * i & 1 ? 0xffffu : 0) | (keep >> (2 * i + 1) & 1 ? 0xffff0000u : 0);
+    }
+    return r;
+  }
+  static __device__ __forceinline__ void write_guard(unsigned char* col, int v, Vec f) {
+    write(col, v, f);
+  }
+  template <int H>
+  static __device__ __forceinline__ void mma_guard(const Guard& a, const unsigned char* p, Acc& acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.a.v[H]),
+                                                  __builtin_bit_cast(bf16x8, read_x(p).v & a.keep[H]),
+                                                  acc, 0, 0, 0);
+  }
 };
 
 struct RingArgs {
@@ -499,9 +531,10 @@ __device__ __forceinline__ bool ring_store(const typename Op::Acc (&acc)[Op::kHa
         v[h] = acc[h][p];
       }
     }
-    if constexpr (Op::kGuard)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) finite &= __builtin_isfinite(v[0][i]);
+    for (int h = 0; h < MH; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) finite &= __builtin_isfinite(v[h][i]);
     const int t = p + sw;
     const int r = grp * RW + t / TPR, c = (t % TPR) * 16 + n;
     const int py = py0 + r, px = px0 + c;
@@ -529,7 +562,7 @@ __device__ __forceinline__ bool ring_store(const typename Op::Acc (&acc)[Op::kHa
 // were not finite, after it has stored them; plain loads and a barrier per unit, since that is rare.
 // Nothing of it is live in the main loop (written as a second turn of a loop around both, it spilled
 // 90 bytes more a lane there); the test of the sums costs up to 1 % (64 x 64 FP32 forward 148.1 ->
-// 149.5 us, 200 x 200 adjoint 4.18 -> 4.21 ms, 96 x 96 FP64 1.318 -> 1.320).
+// 149.5 us, 200 x 200 adjoint 4.18 -> 4.21 ms, 96 x 96 FP64 1.318 -> 1.320; BF16 nothing measurable).
 template <class Op, int BR, int BC, int W, int P, bool RAGGED>
 __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
                                              const typename Op::In* __restrict__ in,
@@ -542,9 +575,11 @@ __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
   const int grp = wave / S, sw = wave % S, n = lane % 16, g = lane / 16;
   const int rowvec = a.NCOL * Op::kVecs;
-  Acc acc[1][NT];
+  Acc acc[Op::kHalves][NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[0][t] = Acc{0, 0, 0, 0};
+  for (int h = 0; h < Op::kHalves; ++h)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[h][t] = Acc{0, 0, 0, 0};
   for (int u = piece.y; u < piece.z; ++u) {
     const int4 U = a.units[u];
     const int lo = U.x + a.K, nv = UR * rowvec;
@@ -567,8 +602,12 @@ __device__ __forceinline__ void ring_guarded(const void* __restrict__ pack,
         const unsigned q = first + r * a.row_bytes;
         const unsigned char* row = lds + min(q, q - RS * a.row_bytes);
 #pragma unroll
-        for (int t = 0; t < TPR; ++t)
-          Op::mma_guard(f, row + t * 16 * Op::kCol, acc[0][r * TPR + t]);
+        for (int t = 0; t < TPR; ++t) {
+          const unsigned char* p = row + t * 16 * Op::kCol;
+          Op::template mma_guard<0>(f, p, acc[0][r * TPR + t]);
+          if constexpr (Op::kHalves > 1)
+            Op::template mma_guard<1>(f, p, acc[Op::kHalves - 1][r * TPR + t]);
+        }
       }
     }
   }
@@ -782,20 +821,18 @@ __global__ __launch_bounds__(64 * W)
   }
   const bool finite = ring_store<Op, BR, BC, W, P>(acc, lds, a, piece, out, threadIdx.x, py0, px0,
                                                    kF32OperandExp + a.exp);
-  if constexpr (Op::kGuard) {
-    __syncthreads();
-    int* flag = reinterpret_cast<int*>(lds);
-    const int mine = __any(!finite);
-    if (lane == 0) flag[wave] = mine;
-    __syncthreads();
-    int any = 0;
+  __syncthreads();
+  int* flag = reinterpret_cast<int*>(lds);
+  const int mine = __any(!finite);
+  if (lane == 0) flag[wave] = mine;
+  __syncthreads();
+  int any = 0;
 #pragma unroll
-    for (int w = 0; w < W; ++w) any |= flag[w];
-    if (any) {
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));  // nothing is kept in registers for this
-      ring_guarded<Op, BR, BC, W, P, RAGGED>(pack, in, out, lds, a, piece, tid, py0, px0);
-    }
+  for (int w = 0; w < W; ++w) any |= flag[w];
+  if (any) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // nothing is kept in registers for this
+    ring_guarded<Op, BR, BC, W, P, RAGGED>(pack, in, out, lds, a, piece, tid, py0, px0);
   }
 }
 

@@ -1,4 +1,4 @@
-"""NaN and infinities in the vectors of FP64 and FP32 applies and of the signal filter.
+"""NaN and infinities in the vectors of applies and of the signal filter.
 
 A row tile (16 outputs of a position) with a nonzero table entry for such a value meets it; in its
 other rows the product is 0 times that value.  An output with a nonzero entry for a NaN is NaN; one
@@ -80,9 +80,10 @@ def test_applies_keep_nonfinite_values_where_the_table_meets_them(grid, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("grid", [(9, 33, 33, 95, 4), (13, 30, 48, 129, 6), (20, 40, 70, 200, 3)],
                          ids=lambda g: "x".join(map(str, g)))
-def test_reduced_precision_spreads_nonfinite_values_by_whole_runs_alone(grid, dtype):
-    """BF16 and FP8 applies multiply runs of eight entries by row tiles of 16: a non-finite entry
-    reaches the outputs of tiles with a nonzero table entry for its run, and no others."""
+def test_reduced_precision_spreads_nonfinite_values_no_further_than_runs(grid, dtype):
+    """FP8 applies multiply runs of eight entries by row tiles of 16: a non-finite entry, which has
+    the NaN code, reaches the outputs of tiles with a nonzero table entry for its run, and no others.
+    In BF16 those with one for the entry itself, and an infinity times a nonzero entry is one."""
     ny, nx, nz, nt, K = grid
     rng = np.random.default_rng(nt + K)
     H = random_table(rng, nz, nt, K)
@@ -100,11 +101,16 @@ def test_reduced_precision_spreads_nonfinite_values_by_whole_runs_alone(grid, dt
                 run, one = np.zeros(v.shape), np.zeros(v.shape)
                 run[at[0], at[1], at[2] // 8 * 8:at[2] // 8 * 8 + 8] = 1
                 one[at] = 1
+                hit = on_scan(op, H, one)
                 print(f"[non-finite {grid} {dtype} {name} {value}]", flush=True)
                 got = getattr(m, name)(torch.from_numpy(v).cuda(), dtype).cpu().numpy()
                 bad = ~np.isfinite(got)
-                assert bad[on_scan(op, H, one) != 0].all()
+                assert bad[hit != 0].all()
                 met = tiles(on_scan(op, (H != 0).astype(np.float64), run) != 0)
+                if dtype == "bf16":
+                    met = tiles(hit != 0)
+                    if value == np.inf:
+                        assert np.array_equal(got[hit != 0], np.sign(hit[hit != 0]) * np.inf)
                 assert not met.all() and not bad[~met].any()
 
 
